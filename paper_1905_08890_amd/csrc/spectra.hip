@@ -7,16 +7,17 @@
 // Steps, all on the device:
 //   1. curl and divergence by 3-point central differences, packed as two
 //      complex fields z1 = curl_x + i curl_y, z2 = curl_z + i div (two real
-//      transforms for the price of one complex transform each);
-//   2. 3-D FFT of z1 and z2: one pass per axis, each workgroup transforming a
-//      bundle of lines in LDS (radix-2 butterflies taken two stages at a time,
-//      decimation in time from bit-reversed loads; y and z bundles take
-//      consecutive x so every load is a row);
+//      transforms for the price of one complex transform each), formed by the
+//      first transform pass as it reads the three input fields;
+//   2. 3-D FFT of z1 and z2, one pass per axis, each pass keeping only the modes
+//      |m_i| <= nbins that a shell can hold;
 //   3. per mode of the cube |m_i| <= nbins: separate the four transforms with
 //      F[a](m) = (Z(m) + conj Z(-m)) / 2, F[b](m) = (Z(m) - conj Z(-m)) / (2i),
 //      form the curl and divergence power and their ratio to |k_eff|^2, and
-//      add them to the mode's shell in a fixed order (per-block partial sums
-//      over 256-mode chunks, then a fixed-order sum over blocks).
+//      add them to the mode's shell in a fixed order (per shell and plane m_z, then
+//      over the planes).
+// gr_spectra_fft, the whole transform of a caller's array, moves line bundles
+// through LDS with radix-2 stages.
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -34,7 +35,6 @@ constexpr int TPB = 256;
 constexpr int kFftLds = 4096;  // complex doubles of line data per workgroup (64 KiB)
 constexpr int kMaxN = 1024;    // twiddle table in LDS: n / 2 entries
 constexpr int kRows = 6;       // k, count, P_curl, P_div, P_vector, P_scalar
-constexpr int kTargetBlocks = 512;
 
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
@@ -46,69 +46,6 @@ __global__ void k_twiddles(double2 *__restrict__ tw, int n)
     double s, c;
     sincospi(-2.0 * j / n, &s, &c);
     tw[j] = double2{c, s};
-}
-
-// z1 = curl_x + i curl_y, z2 = curl_z + i div at every cell
-__global__ void __launch_bounds__(TPB) k_curl_div(const double *__restrict__ vx, const double *__restrict__ vy,
-                                                  const double *__restrict__ vz, int n, double2 *__restrict__ z1,
-                                                  double2 *__restrict__ z2)
-{
-    const long N = (long)n * n * n;
-    const long p = (long)blockIdx.x * TPB + threadIdx.x;
-    if (p >= N) return;
-    const int x = (int)(p % n), y = (int)((p / n) % n), z = (int)(p / ((long)n * n));
-    const long row = p - x, plane = (long)n * n;
-    const long xp = row + wrapi(x + 1, n), xm = row + wrapi(x - 1, n);
-    const long yp = p + (long)(wrapi(y + 1, n) - y) * n, ym = p + (long)(wrapi(y - 1, n) - y) * n;
-    const long zp = p + (long)(wrapi(z + 1, n) - z) * plane, zm = p + (long)(wrapi(z - 1, n) - z) * plane;
-    const double f = 0.5 * n;
-    const double dyvz = (vz[yp] - vz[ym]) * f, dzvy = (vy[zp] - vy[zm]) * f;
-    const double dzvx = (vx[zp] - vx[zm]) * f, dxvz = (vz[xp] - vz[xm]) * f;
-    const double dxvy = (vy[xp] - vy[xm]) * f, dyvx = (vx[yp] - vx[ym]) * f;
-    const double dxvx = (vx[xp] - vx[xm]) * f, dyvy = (vy[yp] - vy[ym]) * f, dzvz = (vz[zp] - vz[zm]) * f;
-    z1[p] = double2{dyvz - dzvy, dzvx - dxvz};
-    z2[p] = double2{dxvy - dyvx, dxvx + dyvy + dzvz};
-}
-
-// The same for n >= 64 by z-marching columns: a workgroup takes a 64 x 4
-// tile of (x, y) columns over kCdz planes, each thread keeping its column's
-// values at z - 1, z and z + 1 in registers (x and y neighbours are the
-// adjacent columns' loads, cache hits when the neighbouring tile ran on the
-// same XCD); identical arithmetic per cell.
-constexpr int kCdx = 64, kCdy = 4, kCdz = 16;
-__global__ void __launch_bounds__(TPB) k_curl_div_march(const double *__restrict__ vx, const double *__restrict__ vy,
-                                                        const double *__restrict__ vz, int n,
-                                                        double2 *__restrict__ z1, double2 *__restrict__ z2)
-{
-    const int ntx = n / kCdx, nty = n / kCdy;
-    // XCD-contiguous order (the grid is a multiple of 8): each XCD takes one run
-    // of consecutive tiles, so the y-neighbour rows of a tile sit in its L2
-    const int G = gridDim.x, v = (int)(blockIdx.x & 7) * (G >> 3) + (int)(blockIdx.x >> 3);
-    const int bx = v % ntx, by = (v / ntx) % nty, bz = v / (ntx * nty);
-    const int x = bx * kCdx + (threadIdx.x & (kCdx - 1)), y = by * kCdy + (threadIdx.x >> 6), z0 = bz * kCdz;
-    const int xp = wrapi(x + 1, n), xm = wrapi(x - 1, n), yp = wrapi(y + 1, n), ym = wrapi(y - 1, n);
-    const double f = 0.5 * n;
-    auto at = [&](int xx, int yy, int zz) { return ((long)zz * n + yy) * n + xx; };
-    const long pm = at(x, y, wrapi(z0 - 1, n)), pc = at(x, y, z0);
-    double px = vx[pm], py = vy[pm], pz = vz[pm];
-    double cx = vx[pc], cy = vy[pc], cz = vz[pc];
-    for (int z = z0; z < z0 + kCdz; ++z) {
-        const long p = at(x, y, z), pn = at(x, y, wrapi(z + 1, n));
-        const double nx = vx[pn], ny = vy[pn], nz = vz[pn];
-        const long xP = p - x + xp, xM = p - x + xm, yP = p + (long)(yp - y) * n, yM = p + (long)(ym - y) * n;
-        const double dyvz = (vz[yP] - vz[yM]) * f, dzvy = (ny - py) * f;
-        const double dzvx = (nx - px) * f, dxvz = (vz[xP] - vz[xM]) * f;
-        const double dxvy = (vy[xP] - vy[xM]) * f, dyvx = (vx[yP] - vx[yM]) * f;
-        const double dxvx = (vx[xP] - vx[xM]) * f, dyvy = (vy[yP] - vy[yM]) * f, dzvz = (nz - pz) * f;
-        z1[p] = double2{dyvz - dzvy, dzvx - dxvz};
-        z2[p] = double2{dxvy - dyvx, dxvx + dyvy + dzvz};
-        px = cx;
-        py = cy;
-        pz = cz;
-        cx = nx;
-        cy = ny;
-        cz = nz;
-    }
 }
 
 // In-place forward transform of every line along AXIS (0 = x, 1 = y, 2 = z)
@@ -185,30 +122,213 @@ __global__ void __launch_bounds__(TPB) k_fft_lines(double2 *__restrict__ data, i
     }
 }
 
-// Shell sums over the modes m in [-R, R]^3 (R = nbins), 256 modes per chunk,
-// `chunks` chunks per block; thread t < nbins adds shell t's entries of each
-// chunk in mode order.  part[block][row][nbins].
-__global__ void __launch_bounds__(TPB) k_bin_modes(const double2 *__restrict__ z1, const double2 *__restrict__ z2,
-                                                   int n, int nbins, long nmodes, int chunks,
+// ---- the pruned transform of the two packed fields ----
+//
+// Only the modes |m_i| <= R (R = nbins <= n / 4) reach a shell, so every axis
+// pass keeps S = 2 R + 1 of its n outputs: the y pass then transforms S / n and
+// the z pass (S / n)^2 of the lines of a full transform, and no pass writes what
+// is not read.  Each pass writes its kept modes with the next axis fastest
+// (x pass [a][z][sx][y], y pass [a][sx][sy][z], z pass [a][sz][sx][sy], a = the
+// array z1 or z2, s = m + R), so every pass reads contiguous lines.
+//
+// A line of n = R1 R2 points (R1 = R2 or 2 R2) is transformed in two rounds by R2
+// threads: R1-point transforms in registers over x = R2 j1 + j2, a twiddle, one
+// exchange through LDS, R2-point transforms, mode k1 + R1 k2.  One LDS round trip
+// per point instead of one per two radix-2 stages: the LDS traffic of a pass falls
+// from ~210 to ~50 bytes per point.  At 256^3 with 32 shells one field's
+// extraction took 1.43 ms with full transforms of separately written curls (curl
+// 297 us, six passes of 150-176 us, serial shell sums 165 us) and takes 0.34 ms
+// here: x pass 252 us (bound by the L2: 18 neighbour reads a cell), y 36 us, z 13 us,
+// shells 29 us.
+template <int LOGN> struct FftSplit {
+    static constexpr int N = 1 << LOGN, R1 = 1 << ((LOGN + 1) / 2), R2 = 1 << (LOGN / 2);
+    static constexpr int LINES = TPB / R2, PITCH = LINES + 1; // lines per workgroup; LDS pitch in points
+};
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b)
+{
+    return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+}
+
+// In-register R-point transform, decimation in frequency; v[i] ends as mode
+// bitrev(i).  w[j] = exp(-2 pi i j / n), n the table's length of the whole line.
+template <int R, int N> __device__ __forceinline__ void fft_reg(double2 (&v)[R], const double2 *__restrict__ w)
+{
+#pragma unroll
+    for (int len = R; len > 1; len >>= 1)
+#pragma unroll
+        for (int b = 0; b < R; b += len)
+#pragma unroll
+            for (int i = 0; i < len / 2; ++i) {
+                const double2 p = v[b + i], q = v[b + i + len / 2];
+                v[b + i] = double2{p.x + q.x, p.y + q.y};
+                const double2 d{p.x - q.x, p.y - q.y};
+                if (i == 0) v[b + i + len / 2] = d;
+                else if (4 * i == len) v[b + i + len / 2] = double2{d.y, -d.x}; // times -i
+                else v[b + i + len / 2] = cmul(d, w[i * (N / len)]);
+            }
+}
+template <int R> __device__ __forceinline__ constexpr int bitrev(int i)
+{
+    int r = 0;
+    for (int b = 1; b < R; b <<= 1) r = 2 * r + ((i / b) & 1);
+    return r;
+}
+
+struct Fields {
+    const double *vx, *vy, *vz;
+};
+
+// Points R2 j + j2 (j < R1) of row (y, z) of array A by 3-point central
+// differences: A = 0 curl_x + i curl_y, A = 1 curl_z + i div.  Row pointers and
+// compile-time offsets; only the first and the last x neighbour can wrap.
+template <int A, int R1, int R2>
+__device__ __forceinline__ void curl_row(const Fields &F, int y, int z, int j2, double2 (&v)[R1])
+{
+    constexpr int N = R1 * R2;
+    const double f = 0.5 * N;
+    auto row = [&](const double *p, int yy, int zz) { return p + ((long)zz * N + yy) * N + j2; };
+    const int yp = wrapi(y + 1, N), ym = wrapi(y - 1, N), zp = wrapi(z + 1, N), zm = wrapi(z - 1, N);
+    const int first = j2 == 0 ? N - 1 : -1;                 // x - 1 of j = 0, from the row's j2
+    const int last = j2 == R2 - 1 ? 1 - N : 1;              // x + 1 of j = R1 - 1, from its x
+    auto dx = [&](const double *p, int j) {
+        return (p[R2 * j + (j == R1 - 1 ? last : 1)] - p[R2 * j + (j == 0 ? first : -1)]) * f;
+    };
+    if constexpr (A == 0) {
+        const double *zyp = row(F.vz, yp, z), *zym = row(F.vz, ym, z), *yzp = row(F.vy, y, zp);
+        const double *yzm = row(F.vy, y, zm), *xzp = row(F.vx, y, zp), *xzm = row(F.vx, y, zm);
+        const double *zc = row(F.vz, y, z);
+#pragma unroll
+        for (int j = 0; j < R1; ++j) {
+            const double dyvz = (zyp[R2 * j] - zym[R2 * j]) * f, dzvy = (yzp[R2 * j] - yzm[R2 * j]) * f;
+            const double dzvx = (xzp[R2 * j] - xzm[R2 * j]) * f, dxvz = dx(zc, j);
+            v[j] = double2{dyvz - dzvy, dzvx - dxvz};
+        }
+    } else {
+        const double *xyp = row(F.vx, yp, z), *xym = row(F.vx, ym, z), *yyp = row(F.vy, yp, z);
+        const double *yym = row(F.vy, ym, z), *zzp = row(F.vz, y, zp), *zzm = row(F.vz, y, zm);
+        const double *xc = row(F.vx, y, z), *yc = row(F.vy, y, z);
+#pragma unroll
+        for (int j = 0; j < R1; ++j) {
+            const double dxvy = dx(yc, j), dyvx = (xyp[R2 * j] - xym[R2 * j]) * f;
+            const double dxvx = dx(xc, j), dyvy = (yyp[R2 * j] - yym[R2 * j]) * f;
+            const double dzvz = (zzp[R2 * j] - zzm[R2 * j]) * f;
+            v[j] = double2{dxvy - dyvx, dxvx + dyvy + dzvz};
+        }
+    }
+}
+
+// One pass over lines [0, nlines) of the array a = blockIdx.x % 2 of a pair (the
+// two workgroups of one group of lines run side by side: they read the same rows
+// of v).  AXIS 0 forms its input from the fields; the others read `in`, a line's n
+// points contiguous.
+//   AXIS 0: line r = z n + y           -> out[a][z][s][y]
+//   AXIS 1: line r = s n + z           (in [a][z][s][:])       -> out[a][s][sy][z]
+//   AXIS 2: line r = sx S + sy         (in [a][r][:])          -> out[a][sz][r]
+template <int LOGN, int AXIS>
+__global__ void __launch_bounds__(TPB, LOGN <= 8 ? 2 : 1) k_fft_pruned(Fields src, const double2 *__restrict__ in,
+                                                                       double2 *__restrict__ out, long nlines, int R,
+                                                                       const double2 *__restrict__ tw)
+{
+    using F = FftSplit<LOGN>;
+    constexpr int N = F::N, R1 = F::R1, R2 = F::R2, LINES = F::LINES, PITCH = F::PITCH, PER = R1 / R2;
+    __shared__ double2 s[N * PITCH];
+    const int S = 2 * R + 1;
+    // contiguous runs of lines per XCD: the rows that neighbouring groups share stay in one L2
+    const unsigned G = gridDim.x;
+    const unsigned w = G % 8 == 0 ? (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const int a = w & 1;
+    const long line0 = (long)(w >> 1) * LINES;
+    const int j2 = threadIdx.x % R2, la = threadIdx.x / R2;          // round 1: consecutive threads along the line
+    const int lb = threadIdx.x % LINES, kq = threadIdx.x / LINES;    // round 2: consecutive threads across lines
+    const long ra = line0 + la, rb = line0 + lb;
+    if (ra < nlines) {
+        double2 v[R1];
+        if constexpr (AXIS == 0) {
+            const int y = (int)(ra % N), z = (int)(ra / N);
+            if (a == 0) curl_row<0, R1, R2>(src, y, z, j2, v);
+            else curl_row<1, R1, R2>(src, y, z, j2, v);
+        } else {
+            const long row = AXIS == 1 ? (a * (long)N + ra % N) * S + ra / N : a * (long)S * S + ra;
+            const double2 *p = in + row * N + j2;
+#pragma unroll
+            for (int j = 0; j < R1; ++j) v[j] = p[R2 * j];
+        }
+        fft_reg<R1, N>(v, tw);
+#pragma unroll
+        for (int i = 0; i < R1; ++i) {
+            const int k1 = bitrev<R1>(i), e = j2 * k1; // e < N
+            double2 t = tw[e & (N / 2 - 1)];
+            if (e >= N / 2) t = double2{-t.x, -t.y};
+            s[(k1 * R2 + j2) * PITCH + la] = cmul(v[i], t);
+        }
+    }
+    __syncthreads();
+    if (rb < nlines) {
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const int k1 = kq + p * R2;
+            double2 u[R2];
+#pragma unroll
+            for (int j = 0; j < R2; ++j) u[j] = s[(k1 * R2 + j) * PITCH + lb];
+            fft_reg<R2, N>(u, tw);
+#pragma unroll
+            for (int i = 0; i < R2; ++i) {
+                const int k = k1 + R1 * bitrev<R2>(i);
+                const int m = k <= R ? k + R : k - N + R; // kept: 0 .. R and N - R .. N - 1
+                if (k > R && m < 0) continue;
+                long o;
+                if (AXIS == 0) o = ((a * (long)N + rb / N) * S + m) * N + rb % N;
+                else if (AXIS == 1) o = ((a * (long)S + rb / N) * S + m) * N + rb % N;
+                else o = (a * (long)S + m) * S * S + rb;
+                out[o] = u[i];
+            }
+        }
+    }
+}
+
+// Fixed-order sum over a workgroup (wavefront shuffles, then the waves in order).
+__device__ __forceinline__ double block_sum(double v, double *sh)
+{
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = 0.0;
+    for (int w = 0; w < TPB / 64; ++w) t += sh[w];
+    __syncthreads();
+    return t;
+}
+
+// Sums of shell b's modes in the plane mz (blockIdx = (mz + R, b)): thread my (and
+// my + 256, ...) runs over the mx of its ring, so a mode is visited once and the
+// order of every addition is fixed.  part[b][plane][row].
+__global__ void __launch_bounds__(TPB) k_bin_modes(const double2 *__restrict__ cube, int n, int nbins,
                                                    double *__restrict__ part)
 {
-    __shared__ int sbin[TPB];
-    __shared__ double sval[kRows][TPB];
-    const int tid = threadIdx.x;
-    const int R = nbins, S = 2 * R + 1;
+    __shared__ double sh[TPB / 64];
+    const int R = nbins, S = 2 * R + 1, b = blockIdx.y, mz = (int)blockIdx.x - R;
     const double N = (double)n * n * n, invN2 = 1.0 / (N * N), twopi = 6.283185307179586476925286766559;
-    double acc[kRows] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int c = 0; c < chunks; ++c) {
-        const long q = ((long)blockIdx.x * chunks + c) * TPB + tid;
-        int bin = -1;
-        double v[kRows] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        if (q < nmodes) {
-            const int mx = (int)(q % S) - R, my = (int)((q / S) % S) - R, mz = (int)(q / ((long)S * S)) - R;
-            const double mag = sqrt((double)(mx * mx + my * my + mz * mz));
-            bin = (int)floor(mag + 0.5) - 1;
-            if (bin >= 0 && bin < nbins) {
-                const long ip = ((long)wrapi(mz, n) * n + wrapi(my, n)) * n + wrapi(mx, n);
-                const long im = ((long)wrapi(-mz, n) * n + wrapi(-my, n)) * n + wrapi(-mx, n);
+    const double2 *z1 = cube, *z2 = cube + (long)S * S * S;
+    double v[kRows] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    double sx, sy, sz, cc;
+    sincospi(2.0 * mz / n, &sz, &cc);
+    for (int q = threadIdx.x; q < S; q += TPB) {
+        const int my = q - R;
+        // |m| in [b + 1/2, b + 3/2): |mx| between these, one to spare on either side
+        const double lo = (b + 0.5) * (b + 0.5) - (double)(mz * mz + my * my);
+        const double hi = (b + 1.5) * (b + 1.5) - (double)(mz * mz + my * my);
+        if (hi < 0.0) continue;
+        const int x0 = lo > 1.0 ? (int)sqrt(lo) - 1 : 0;
+        int x1 = (int)sqrt(hi) + 1;
+        x1 = x1 > R ? R : x1;
+        sincospi(2.0 * my / n, &sy, &cc);
+        for (int ax = x0; ax <= x1; ++ax)
+            for (int sg = 0; sg < (ax ? 2 : 1); ++sg) {
+                const int mx = sg ? -ax : ax;
+                const double mag = sqrt((double)(mx * mx + my * my + mz * mz));
+                if ((int)floor(mag + 0.5) - 1 != b) continue;
+                const long ip = ((long)(mz + R) * S + mx + R) * S + my + R;
+                const long im = ((long)(R - mz) * S + R - mx) * S + R - my;
                 const double2 ap = z1[ip], am = z1[im], bp = z2[ip], bm = z2[im];
                 // F[curl_x] = (ap + conj am) / 2, F[curl_y] = (ap - conj am) / (2i), likewise curl_z, div from z2
                 const double fxr = 0.5 * (ap.x + am.x), fxi = 0.5 * (ap.y - am.y);
@@ -217,45 +337,36 @@ __global__ void __launch_bounds__(TPB) k_bin_modes(const double2 *__restrict__ z
                 const double fdr = 0.5 * (bp.y + bm.y), fdi = -0.5 * (bp.x - bm.x);
                 const double pc = ((fxr * fxr + fxi * fxi) + (fyr * fyr + fyi * fyi) + (fzr * fzr + fzi * fzi)) * invN2;
                 const double pd = (fdr * fdr + fdi * fdi) * invN2;
-                double sx, sy, sz, cc;
                 sincospi(2.0 * mx / n, &sx, &cc);
-                sincospi(2.0 * my / n, &sy, &cc);
-                sincospi(2.0 * mz / n, &sz, &cc);
                 const double keff2 = (n * sx) * (n * sx) + (n * sy) * (n * sy) + (n * sz) * (n * sz);
-                v[0] = twopi * mag;
-                v[1] = 1.0;
-                v[2] = pc;
-                v[3] = pd;
-                v[4] = pc / keff2;
-                v[5] = pd / keff2;
-            } else {
-                bin = -1;
+                v[0] += twopi * mag;
+                v[1] += 1.0;
+                v[2] += pc;
+                v[3] += pd;
+                v[4] += pc / keff2;
+                v[5] += pd / keff2;
             }
-        }
-        sbin[tid] = bin;
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) sval[r][tid] = v[r];
-        __syncthreads();
-        if (tid < nbins)
-            for (int e = 0; e < TPB; ++e)
-                if (sbin[e] == tid)
-#pragma unroll
-                    for (int r = 0; r < kRows; ++r) acc[r] += sval[r][e];
-        __syncthreads();
     }
-    if (tid < nbins)
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) part[((long)blockIdx.x * kRows + r) * nbins + tid] = acc[r];
+    for (int r = 0; r < kRows; ++r) {
+        const double t = block_sum(v[r], sh);
+        if (threadIdx.x == 0) part[((long)b * S + blockIdx.x) * kRows + r] = t;
+    }
 }
 
-// out[row][bin] = sum over blocks, in block order
-__global__ void k_bin_reduce(const double *__restrict__ part, int nblk, int cells, double *__restrict__ out)
+// out[row][bin] = sum over the planes (thread t adds planes t, t + 256, ..., then
+// a fixed tree); one workgroup per bin
+__global__ void __launch_bounds__(TPB) k_bin_reduce(const double *__restrict__ part, int nbins, int S,
+                                                    double *__restrict__ out)
 {
-    const int q = blockIdx.x * TPB + threadIdx.x;
-    if (q >= cells) return;
-    double s = 0.0;
-    for (int b = 0; b < nblk; ++b) s += part[(long)b * cells + q];
-    out[q] = s;
+    __shared__ double sh[TPB / 64];
+    const int b = blockIdx.x;
+    for (int r = 0; r < kRows; ++r) {
+        double v = 0.0;
+        for (int p = threadIdx.x; p < S; p += TPB) v += part[((long)b * S + p) * kRows + r];
+        v = block_sum(v, sh);
+        if (threadIdx.x == 0) out[r * nbins + b] = v;
+    }
 }
 
 thread_local std::string s_err;
@@ -290,9 +401,7 @@ int ilog2(int v)
 
 struct gr_spectra_s {
     int n = 0, logn = 0, nbins = 0;
-    long nmodes = 0;
-    int chunks = 1, nblk = 0;
-    size_t off_z1 = 0, off_z2 = 0, off_tw = 0, off_part = 0, off_out = 0, bytes = 0;
+    size_t off_a = 0, off_b = 0, off_tw = 0, off_part = 0, off_out = 0, bytes = 0;
     char *ws = nullptr;
     hipStream_t stream = nullptr;
     bool bound = false;
@@ -313,6 +422,18 @@ int fft3(gr_spectra S, double2 *d)
     return GR_OK;
 }
 
+// the three pruned passes: fields -> a [2][z][S][y] -> b [2][S][S][z] -> a [2][S][S][S]
+template <int LOGN>
+void pruned_passes(hipStream_t st, const Fields &src, double2 *a, double2 *b, int R, const double2 *tw)
+{
+    constexpr int LINES = FftSplit<LOGN>::LINES;
+    const long n = 1 << LOGN, S = 2L * R + 1;
+    auto grid = [](long lines) { return (unsigned)(2 * ((lines + LINES - 1) / LINES)); };
+    k_fft_pruned<LOGN, 0><<<grid(n * n), TPB, 0, st>>>(src, nullptr, a, n * n, R, tw);
+    k_fft_pruned<LOGN, 1><<<grid(n * S), TPB, 0, st>>>(src, a, b, n * S, R, tw);
+    k_fft_pruned<LOGN, 2><<<grid(S * S), TPB, 0, st>>>(src, b, a, S * S, R, tw);
+}
+
 } // namespace
 
 extern "C" {
@@ -330,21 +451,16 @@ int gr_create_spectra(int n, int nbins, gr_spectra *out)
     S->n = n;
     S->logn = ilog2(n);
     S->nbins = nbins;
-    const long side = 2L * nbins + 1;
-    S->nmodes = side * side * side;
-    const long chunks_total = (S->nmodes + TPB - 1) / TPB;
-    S->chunks = (int)((chunks_total + kTargetBlocks - 1) / kTargetBlocks);
-    S->nblk = (int)((chunks_total + S->chunks - 1) / S->chunks);
-    const size_t N = (size_t)n * n * n;
+    const size_t side = 2 * (size_t)nbins + 1;
     size_t off = 0;
-    S->off_z1 = off;
-    off += al256(N * sizeof(double2));
-    S->off_z2 = off;
-    off += al256(N * sizeof(double2));
+    S->off_a = off; // x pass output, then the mode cube
+    off += al256(2 * (size_t)n * n * side * sizeof(double2));
+    S->off_b = off; // y pass output
+    off += al256(2 * (size_t)n * side * side * sizeof(double2));
     S->off_tw = off;
     off += al256((size_t)(n / 2) * sizeof(double2));
     S->off_part = off;
-    off += al256((size_t)S->nblk * kRows * nbins * sizeof(double));
+    off += al256(side * kRows * nbins * sizeof(double));
     S->off_out = off;
     off += al256((size_t)kRows * nbins * sizeof(double));
     S->bytes = off;
@@ -385,25 +501,26 @@ int gr_vector_spectra(gr_spectra S, const double *d_vx, const double *d_vy, cons
 {
     if (!S || !d_vx || !d_vy || !d_vz || !h_out) return sfail(GR_EINVAL, "null argument");
     if (!S->bound) return sfail(GR_ESTATE, "spectra handle not bound");
-    const int n = S->n, nb = S->nbins;
-    const long N = (long)n * n * n;
-    double2 *z1 = reinterpret_cast<double2 *>(S->ws + S->off_z1);
-    double2 *z2 = reinterpret_cast<double2 *>(S->ws + S->off_z2);
+    const int n = S->n, nb = S->nbins, side = 2 * nb + 1, cells = kRows * nb;
+    double2 *bufa = reinterpret_cast<double2 *>(S->ws + S->off_a);
+    double2 *bufb = reinterpret_cast<double2 *>(S->ws + S->off_b);
+    const double2 *tw = reinterpret_cast<const double2 *>(S->ws + S->off_tw);
     double *part = reinterpret_cast<double *>(S->ws + S->off_part);
     double *out = reinterpret_cast<double *>(S->ws + S->off_out);
-    if (n >= kCdx)
-        k_curl_div_march<<<(unsigned)((n / kCdx) * (n / kCdy) * (n / kCdz)), TPB, 0, S->stream>>>(d_vx, d_vy, d_vz, n,
-                                                                                                 z1, z2);
-    else
-        k_curl_div<<<(unsigned)((N + TPB - 1) / TPB), TPB, 0, S->stream>>>(d_vx, d_vy, d_vz, n, z1, z2);
+    const Fields src{d_vx, d_vy, d_vz};
+    switch (S->logn) {
+    case 3: pruned_passes<3>(S->stream, src, bufa, bufb, nb, tw); break;
+    case 4: pruned_passes<4>(S->stream, src, bufa, bufb, nb, tw); break;
+    case 5: pruned_passes<5>(S->stream, src, bufa, bufb, nb, tw); break;
+    case 6: pruned_passes<6>(S->stream, src, bufa, bufb, nb, tw); break;
+    case 7: pruned_passes<7>(S->stream, src, bufa, bufb, nb, tw); break;
+    case 8: pruned_passes<8>(S->stream, src, bufa, bufb, nb, tw); break;
+    case 9: pruned_passes<9>(S->stream, src, bufa, bufb, nb, tw); break;
+    default: pruned_passes<10>(S->stream, src, bufa, bufb, nb, tw); break;
+    }
     SLAUNCH();
-    int rc = fft3(S, z1);
-    if (rc != GR_OK) return rc;
-    rc = fft3(S, z2);
-    if (rc != GR_OK) return rc;
-    k_bin_modes<<<(unsigned)S->nblk, TPB, 0, S->stream>>>(z1, z2, n, nb, S->nmodes, S->chunks, part);
-    const int cells = kRows * nb;
-    k_bin_reduce<<<(unsigned)((cells + TPB - 1) / TPB), TPB, 0, S->stream>>>(part, S->nblk, cells, out);
+    k_bin_modes<<<dim3((unsigned)side, (unsigned)nb), TPB, 0, S->stream>>>(bufa, n, nb, part);
+    k_bin_reduce<<<(unsigned)nb, TPB, 0, S->stream>>>(part, nb, side, out);
     SLAUNCH();
     SHIP(hipMemcpyAsync(h_out, out, (size_t)cells * sizeof(double), hipMemcpyDeviceToHost, S->stream));
     SHIP(hipStreamSynchronize(S->stream));

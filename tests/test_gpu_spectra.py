@@ -124,3 +124,47 @@ def test_full_size_256_with_32_shells():
     got = S.vector(*[torch.from_numpy(a).cuda() for a in v])
     _compare(got, OS.vector_spectra(*v, nbins=32))
     S.close()
+
+
+def _low_modes(g, R):
+    """F[g](m) for |m_i| <= R, [mz][my][mx], by three dense FP64 products."""
+    n = g.shape[0]
+    m = torch.arange(-R, R + 1, device=g.device, dtype=torch.float64)
+    x = torch.arange(n, device=g.device, dtype=torch.float64)
+    ph = torch.remainder(x[:, None] * m[None, :], n) * (-2.0 * np.pi / n)
+    E = torch.complex(torch.cos(ph), torch.sin(ph))
+    S = 2 * R + 1
+    h = torch.complex(g.reshape(-1, n) @ E.real.contiguous(), g.reshape(-1, n) @ E.imag.contiguous())   # [z y][mx]
+    h = h.reshape(n, n, S).permute(0, 2, 1).reshape(-1, n) @ E                                          # [z mx][my]
+    h = h.reshape(n, S * S).t().contiguous() @ E                                                        # [mx my][mz]
+    return h.reshape(S, S, S).permute(2, 1, 0)
+
+
+@pytest.mark.parametrize("n,nbins", [(8, 1), (8, 2), (16, 3), (32, 5), (64, 16), (128, 7), (128, 32), (256, 19),
+                                     (512, 9), (1024, 3)])
+def test_pruned_transform_of_every_size(n, nbins):
+    """Every side the transform is written for, odd and largest shell counts:
+    the kept modes against dense products, binned here."""
+    print(f"[spectra] pruned n={n} nbins={nbins}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n + nbins)
+    v = [torch.randn((n, n, n), generator=gen, device="cuda", dtype=torch.float64) for _ in range(3)]
+    S = grmg.Spectra(n, nbins)
+    got = S.vector(*v)
+    S.close()
+    d = lambda f, dim: (torch.roll(f, -1, dim) - torch.roll(f, 1, dim)) * (0.5 * n)
+    x, y, z = v
+    N2 = float(n) ** 6
+    pc = sum(_low_modes(f(), nbins).abs() ** 2 for f in (lambda: d(z, 1) - d(y, 0), lambda: d(x, 0) - d(z, 2),
+                                                         lambda: d(y, 2) - d(x, 1))) / N2
+    pd = _low_modes(d(x, 2) + d(y, 1) + d(z, 0), nbins).abs() ** 2 / N2
+    m = torch.arange(-nbins, nbins + 1, device="cuda", dtype=torch.float64)
+    k2 = (n * torch.sin(2.0 * np.pi * m / n)) ** 2
+    keff2 = k2[:, None, None] + k2[None, :, None] + k2[None, None, :]
+    mag = torch.sqrt((m * m)[:, None, None] + (m * m)[None, :, None] + (m * m)[None, None, :])
+    shell = torch.floor(mag + 0.5).long() - 1
+    ref = np.zeros((6, nbins))
+    for b in range(nbins):
+        sel = shell == b
+        ref[:, b] = [2.0 * np.pi * mag[sel].mean().item(), sel.sum().item(), pc[sel].mean().item(),
+                     pd[sel].mean().item(), (pc / keff2)[sel].mean().item(), (pd / keff2)[sel].mean().item()]
+    _compare(got, ref)
