@@ -178,12 +178,16 @@ void launch_build_cmc(hipStream_t s, double *m2, double *f, const double *psi, c
                       const double *sm, const double *AA, long N, double a, double om, double c_tilde);
 void launch_shift_source(hipStream_t s, double *fB[3], const double *psi, const double *xi,
                          double *const A6[6], int n, double h, double a, double c_tilde);
-// ---- particles.hip launchers (fields: Phi, Psi and beta^i grids of side n) ----
-void launch_kick(hipStream_t s, int n, double a, double c, const double *Phi, const double *Psi,
-                 const double *const beta[3], const double *pos, double *u, long np, double dt, int order);
+// ---- particles.hip launchers ----
+// the metric packed for the particle gathers: pp = {Phi, Psi} and bxy = {beta^x,
+// beta^y} pairs (2 n^3 doubles each, 16-byte aligned), bz
+void launch_pack_metric(hipStream_t s, int n, double h, double a, double c, const double *psi, const double *xi,
+                        const double *const B[3], const double *b, double *pp, double *bxy, double *bz);
+void launch_kick(hipStream_t s, int n, double a, double c, const double *pp, const double *bxy, const double *bz,
+                 const double *pos, double *u, long np, double dt, int order);
+void launch_drift(hipStream_t s, int n, double a, double c, const double *pp, const double *bxy, const double *bz,
+                  double *pos, const double *u, long np, double dt);
 void launch_newton_kick(hipStream_t s, int n, const double *phiN, const double *pos, double *u, long np, double dt);
-void launch_drift(hipStream_t s, int n, double a, double c, const double *Phi, const double *Psi,
-                  const double *const beta[3], double *pos, const double *u, long np, double dt);
 void launch_derived(hipStream_t s, int which, double *out, const double *psi, const double *xi,
                     const double *Bcomp, const double *b, int n, double h, double a, double c_tilde);
 

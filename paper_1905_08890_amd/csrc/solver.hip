@@ -188,7 +188,10 @@ size_t layout(gr_grid g, char *base)
     if (!g->solver_only) {
         for (int f = 0; f < 10; ++f) g->field[f] = take(fb);
         for (int s = 0; s < 5; ++s) g->src[s] = take(fb);
-        for (int c = 0; c < 6; ++c) g->A6[c] = take(fb);
+        for (int c = 0; c < 6; c += 2) { // in pairs: the particle calls lay 2 n^3 doubles over (0, 1) and (2, 3)
+            g->A6[c] = take(2 * fb);
+            g->A6[c + 1] = g->A6[c] ? g->A6[c] + g->N() : nullptr;
+        }
         g->AA = take(fb);
         for (int c = 0; c < 3; ++c) g->fB[c] = take(fb);
         for (int f = 0; f < 10; ++f) g->alt[f] = take(fb);
@@ -1068,19 +1071,16 @@ int gr_deposit_sources(gr_grid g, const double *d_pos, const double *d_u, double
     return GR_OK;
 }
 
-// Phi (into the scratch A6[0]) and beta^i (A6[1..3]) from the held fields, for
-// the particle calls; A_ij is rebuilt by the next solve.
+// The packed metric of the held fields, for the particle calls: {Phi, Psi} pairs
+// over the scratch A6[0..1], {beta^x, beta^y} over A6[2..3], beta^z in A6[4];
+// A_ij is rebuilt by the next solve.
 namespace {
-int particle_metric(gr_grid g, const double **Phi, const double *beta[3])
+int particle_metric(gr_grid g)
 {
-    const double a = g->prm.a, c = g->prm.c_tilde;
-    launch_derived(g->stream, 0, g->A6[0], g->field[GR_PSI], g->field[GR_XI], nullptr, nullptr, g->n, g->h, a, c);
-    for (int d = 0; d < 3; ++d)
-        launch_derived(g->stream, 3 + d, g->A6[1 + d], g->field[GR_PSI], g->field[GR_XI], g->field[GR_BX + d],
-                       g->field[GR_BB], g->n, g->h, a, c);
+    const double *B[3] = {g->field[GR_BX], g->field[GR_BY], g->field[GR_BZ]};
+    launch_pack_metric(g->stream, g->n, g->h, g->prm.a, g->prm.c_tilde, g->field[GR_PSI], g->field[GR_XI], B,
+                       g->field[GR_BB], g->A6[0], g->A6[2], g->A6[4]);
     LAUNCHCHK();
-    *Phi = g->A6[0];
-    for (int d = 0; d < 3; ++d) beta[d] = g->A6[1 + d];
     return GR_OK;
 }
 
@@ -1098,9 +1098,8 @@ int gr_kick(gr_grid g, const double *d_pos, double *d_u, int64_t np, double dt, 
 {
     CHK(check_particles(g, d_pos, d_u, np, dt));
     if (order != GR_KICK_FORWARD && order != GR_KICK_REVERSE) return fail(GR_EINVAL, "bad kick order %d", order);
-    const double *Phi = nullptr, *beta[3];
-    CHK(particle_metric(g, &Phi, beta));
-    launch_kick(g->stream, g->n, g->prm.a, g->prm.c_tilde, Phi, g->field[GR_PSI], beta, d_pos, d_u, (long)np, dt,
+    CHK(particle_metric(g));
+    launch_kick(g->stream, g->n, g->prm.a, g->prm.c_tilde, g->A6[0], g->A6[2], g->A6[4], d_pos, d_u, (long)np, dt,
                 order);
     LAUNCHCHK();
     return GR_OK;
@@ -1109,9 +1108,8 @@ int gr_kick(gr_grid g, const double *d_pos, double *d_u, int64_t np, double dt, 
 int gr_drift(gr_grid g, double *d_pos, const double *d_u, int64_t np, double dt)
 {
     CHK(check_particles(g, d_pos, d_u, np, dt));
-    const double *Phi = nullptr, *beta[3];
-    CHK(particle_metric(g, &Phi, beta));
-    launch_drift(g->stream, g->n, g->prm.a, g->prm.c_tilde, Phi, g->field[GR_PSI], beta, d_pos, d_u, (long)np, dt);
+    CHK(particle_metric(g));
+    launch_drift(g->stream, g->n, g->prm.a, g->prm.c_tilde, g->A6[0], g->A6[2], g->A6[4], d_pos, d_u, (long)np, dt);
     LAUNCHCHK();
     return GR_OK;
 }

@@ -223,3 +223,27 @@ def test_newtonian_synchronisation_matches_oracle():
         assert np.abs(got - src_N[k]).max() <= 1e-12 * np.abs(src_N[k]).max(), name
     ud.copy_(u_save)
     assert torch.equal(ud, _dev(u))
+
+
+@pytest.mark.parametrize("n,npart", [(2, 4096), (6, 4096), (16, 1), (16, 255), (32, 257), (32, 32768)])
+def test_kick_and_drift_thread_orders(n, npart):
+    """Cubes of particles are taken in blocks, other counts in rows: each
+    against the oracle on the smallest grids, ragged counts and the wrap."""
+    print(f"[gpu] kick/drift n={n} particles={npart}", flush=True)
+    Psi, xi, B, b = _metric(n, 900 + n)
+    g = _grid_with(n, Psi, xi, B, b)
+    p = O.params(**PRM)
+    Phi, bx, by, bz = O.derived(Psi, xi, *B, b, prm=p)
+    pos, u = _particles(max(npart, 8), npart)
+    pos, u = pos[:npart].copy(), u[:npart].copy()
+    pd, ud = _dev(pos), _dev(u)
+    grmg.kick(g.handle, pd, ud, 0.05, grmg.KICK_FORWARD)
+    grmg.drift(g.handle, pd, _dev(u), 0.05)
+    torch.cuda.synchronize()
+    ref = O.kick(Phi, Psi, [bx, by, bz], pos, u, 0.05, grmg.KICK_FORWARD, prm=p)
+    eps = np.finfo(float).eps
+    du, dref = ud.cpu().numpy() - u, ref - u
+    assert np.abs(du - dref).max() <= 1e-12 * np.abs(dref).max() + 4 * eps * np.abs(ref).max()
+    d = (pd.cpu().numpy() - pos + 0.5) % 1.0 - 0.5
+    dr = (O.drift(Phi, Psi, [bx, by, bz], pos, u, 0.05, prm=p) - pos + 0.5) % 1.0 - 0.5
+    assert np.abs(d - dr).max() <= 1e-12 * np.abs(dr).max() + 4 * eps
