@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(TPB) kb_colour(BatchDev D, const int *__restri
     double J;
     const double Lv = op_point<KIND, double>(ph, nb_sum(phi, i, y, z, n), 1.0 / (L.h * L.h), load_c1<KIND>(L.coef, p),
                                              0.0, oc, Fb, J);
-    phi[p] = ph - (Lv - (L.f[p] - fs)) / J;
+    phi[p] = newton_update<KIND, double>(ph, Lv, L.f[p] - fs, J, poisson_inv_diag(1.0 / (L.h * L.h)));
 }
 
 // Fused red-black sweeps (rb_fused_tile) of the boxes whose level d takes
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(TPB) kb_restrict_coef(BatchDev D, const int *_
 
 // the rest of the V-cycle of each active box from its entry level, one workgroup per box
 template <int KIND>
-__global__ void __launch_bounds__(CTPB) kb_coarse_vcycle(BatchDev D, int fid, int nu1, int nu2, OpConst oc);
+__global__ void __launch_bounds__(kCoarseNT) kb_coarse_vcycle(BatchDev D, int fid, int nu1, int nu2, OpConst oc);
 
 // ------------------------------------------------------------- reductions
 
@@ -587,14 +587,15 @@ __global__ void __launch_bounds__(TPB) kb_fill_field(BatchDev D, const int *__re
 
 // ----------------------------------------------------- coarse cycle per box
 
-template <int KIND>
+template <int KIND, int NT>
 __device__ void cvb_sweep(double *__restrict__ phi, const double *__restrict__ f, const double *__restrict__ coef, int n,
                           double inv_h2, OpConst oc, double Fb, double fs)
 {
     const int half = n >> 1, tot = n * n * half;
     const SmallDiv dh(half), dn(n);
+    const double rJ = poisson_inv_diag(inv_h2);
     for (int colour = 0; colour < 2; ++colour) {
-        for (int t = threadIdx.x; t < tot; t += CTPB) {
+        for (int t = threadIdx.x; t < tot; t += NT) {
             const int r = dh.div(t), z = dn.div(r);
             const int x2 = t - r * half, y = r - z * n;
             const int i = 2 * x2 + ((y + z + colour) & 1);
@@ -603,32 +604,58 @@ __device__ void cvb_sweep(double *__restrict__ phi, const double *__restrict__ f
             double J;
             const double L = op_point<KIND, double>(ph, nb_sum(phi, i, y, z, n), inv_h2, load_c1<KIND>(coef, p), 0.0,
                                                     oc, Fb, J);
-            phi[p] = ph - (L - (f[p] - fs)) / J;
+            phi[p] = newton_update<KIND, double>(ph, L, f[p] - fs, J, rJ);
         }
         __syncthreads();
     }
 }
 
+template <int NT>
 __device__ double cvb_block_sum(double v)
 {
-    __shared__ double sh[CTPB / 64];
+    __shared__ double sh[NT / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
     if (lane == 0) sh[wave] = v;
     __syncthreads();
     double s = 0.0;
-    for (int w = 0; w < CTPB / 64; ++w) s += sh[w];
+    for (int w = 0; w < NT / 64; ++w) s += sh[w];
     __syncthreads();
     return s;
 }
 
-constexpr int kBoxCoarseLds = 1024; // doubles of LDS for the coarsest box level (8 KB)
+// the level table of a box's coarse cycle
+__device__ void box_coarse_levels(const BoxDev &X, int fid, CoarseLevelsT<double> &G)
+{
+    G.nl = X.nlev - X.centry;
+    for (int i = 0; i < G.nl; ++i) {
+        const int l = X.centry + i;
+        const BoxLev &V = X.lev[l];
+        G.n[i] = V.n;
+        G.inv_h2[i] = 1.0 / (V.h * V.h);
+        G.phi[i] = l == 0 ? X.field[fid] : V.phi;
+        G.f[i] = V.f;
+        G.c1[i] = V.coef;
+    }
+}
 
-template <int KIND>
-__device__ void coarse_vcycle_box(const BatchDev &D, int b, int fid, int nu1, int nu2, OpConst oc)
+// The rest of box b's V-cycle by NT threads with kCoarseLdsBytes of LDS at lds: every
+// level in LDS where they fit (all sides whose coarse entry is at most 16^3),
+// else from global memory.
+template <int KIND, int NT>
+__device__ void coarse_vcycle_box(double *lds, const BatchDev &D, int b, int fid, int nu1, int nu2, OpConst oc)
 {
     const BoxDev &X = D.box[b];
     const int l0 = X.centry, L = X.nlev;
+    if (coarse_lds_need<KIND, kPeriodic>(X.lev[l0].n, L - l0)) {
+        __shared__ CoarseLevelsT<double> G;
+        if (threadIdx.x == 0) box_coarse_levels(X, fid, G);
+        __syncthreads();
+        coarse_cycle_lds<KIND, kPeriodic, NT, double, double>(lds, G, nu1, nu2, oc,
+                                                              l0 == 0 ? D.scal[b * B_NSCAL + B_FBAR] : 0.0,
+                                                              l0 == 0 ? D.scal[b * B_NSCAL + B_FSHIFT] : 0.0);
+        return;
+    }
     auto PHI = [&](int i) { return i == 0 ? X.field[fid] : X.lev[i].phi; };
     const double Fb0 = l0 == 0 ? D.scal[b * B_NSCAL + B_FBAR] : 0.0;
     const double fs0 = l0 == 0 ? D.scal[b * B_NSCAL + B_FSHIFT] : 0.0;
@@ -638,9 +665,9 @@ __device__ void coarse_vcycle_box(const BatchDev &D, int b, int fid, int nu1, in
         double *phi = PHI(i);
         const double inv_h2 = 1.0 / (V.h * V.h);
         const double Fb = i == 0 ? Fb0 : 0.0, fs = i == 0 ? fs0 : 0.0;
-        for (int it = 0; it < nu1; ++it) cvb_sweep<KIND>(phi, V.f, V.coef, n, inv_h2, oc, Fb, fs);
+        for (int it = 0; it < nu1; ++it) cvb_sweep<KIND, NT>(phi, V.f, V.coef, n, inv_h2, oc, Fb, fs);
         const int M = m * m * m;
-        for (int q = threadIdx.x; q < M; q += CTPB) {
+        for (int q = threadIdx.x; q < M; q += NT) {
             const int Xc = q % m, Yc = (q / m) % m, Zc = q / (m * m);
             double sr = 0.0, sp = 0.0;
             for (int c = 0; c < 8; ++c) {
@@ -660,7 +687,7 @@ __device__ void coarse_vcycle_box(const BatchDev &D, int b, int fid, int nu1, in
         }
         __syncthreads();
         const double inv_H2 = 1.0 / (C.h * C.h);
-        for (int q = threadIdx.x; q < M; q += CTPB) {
+        for (int q = threadIdx.x; q < M; q += NT) {
             const int Xc = q % m, Yc = (q / m) % m, Zc = q / (m * m);
             double Jd;
             const double Lv = op_point<KIND, double>(C.phi[q], nb_sum(C.phi, Xc, Yc, Zc, m), inv_H2,
@@ -676,30 +703,13 @@ __device__ void coarse_vcycle_box(const BatchDev &D, int b, int fid, int nu1, in
         double *phi = PHI(i);
         const double inv_h2 = 1.0 / (V.h * V.h);
         const double Fb = i == 0 ? Fb0 : 0.0, fs = i == 0 ? fs0 : 0.0;
-        for (int q = threadIdx.x; q < N; q += CTPB) V.tmp[q] = phi[q];
+        for (int q = threadIdx.x; q < N; q += NT) V.tmp[q] = phi[q];
         __syncthreads();
-        // the 32 sweeps from LDS when the level, its source and coefficient fit
-        // (the coarsest box levels are 2^3 to 6^3), else from global memory
-        constexpr int NC = kNumCoef<KIND>();
-        __shared__ double lds[kBoxCoarseLds];
-        if ((2 + NC) * N <= kBoxCoarseLds) {
-            double *sphi = lds, *sf = lds + N, *sc = lds + 2 * N;
-            for (int q = threadIdx.x; q < N; q += CTPB) {
-                sphi[q] = phi[q];
-                sf[q] = V.f[q];
-                if (NC >= 1) sc[q] = V.coef[q];
-            }
-            __syncthreads();
-            for (int it = 0; it < kCoarseSweeps; ++it) cvb_sweep<KIND>(sphi, sf, sc, n, inv_h2, oc, Fb, fs);
-            for (int q = threadIdx.x; q < N; q += CTPB) phi[q] = sphi[q];
-            __syncthreads();
-        } else {
-            for (int it = 0; it < kCoarseSweeps; ++it) cvb_sweep<KIND>(phi, V.f, V.coef, n, inv_h2, oc, Fb, fs);
-        }
+        for (int it = 0; it < kCoarseSweeps; ++it) cvb_sweep<KIND, NT>(phi, V.f, V.coef, n, inv_h2, oc, Fb, fs);
         double dsum = 0.0;
-        for (int q = threadIdx.x; q < N; q += CTPB) dsum += phi[q] - V.tmp[q];
-        const double mean = cvb_block_sum(dsum) / (double)N;
-        for (int q = threadIdx.x; q < N; q += CTPB) phi[q] -= mean;
+        for (int q = threadIdx.x; q < N; q += NT) dsum += phi[q] - V.tmp[q];
+        const double mean = cvb_block_sum<NT>(dsum) / (double)N;
+        for (int q = threadIdx.x; q < N; q += NT) phi[q] -= mean;
         __syncthreads();
     }
     for (int i = L - 2; i >= l0; --i) {
@@ -708,7 +718,7 @@ __device__ void coarse_vcycle_box(const BatchDev &D, int b, int fid, int nu1, in
         double *phi = PHI(i);
         const double inv_h2 = 1.0 / (V.h * V.h);
         const double Fb = i == 0 ? Fb0 : 0.0, fs = i == 0 ? fs0 : 0.0;
-        for (int p = threadIdx.x; p < N; p += CTPB) {
+        for (int p = threadIdx.x; p < N; p += NT) {
             const int a = p % n, bb = (p / n) % n, dd = p / (n * n);
             const int I = a >> 1, J = bb >> 1, K = dd >> 1;
             const int Is[2] = {I, wrapi(I + ((a & 1) ? 1 : -1), m)};
@@ -724,15 +734,16 @@ __device__ void coarse_vcycle_box(const BatchDev &D, int b, int fid, int nu1, in
             phi[p] += v;
         }
         __syncthreads();
-        for (int it = 0; it < nu2; ++it) cvb_sweep<KIND>(phi, V.f, V.coef, n, inv_h2, oc, Fb, fs);
+        for (int it = 0; it < nu2; ++it) cvb_sweep<KIND, NT>(phi, V.f, V.coef, n, inv_h2, oc, Fb, fs);
     }
 }
 
 template <int KIND>
-__global__ void __launch_bounds__(CTPB) kb_coarse_vcycle(BatchDev D, int fid, int nu1, int nu2, OpConst oc)
+__global__ void __launch_bounds__(kCoarseNT) kb_coarse_vcycle(BatchDev D, int fid, int nu1, int nu2, OpConst oc)
 {
+    __shared__ double lds[kCoarseLdsBytes / sizeof(double)];
     if (!D.active[blockIdx.x]) return;
-    coarse_vcycle_box<KIND>(D, blockIdx.x, fid, nu1, nu2, oc);
+    coarse_vcycle_box<KIND, kCoarseNT>(lds, D, blockIdx.x, fid, nu1, nu2, oc);
 }
 
 // ------------------------------------------------ persistent task queue
@@ -772,11 +783,11 @@ __global__ void kb_queue_reset(int *__restrict__ ctl, int *__restrict__ done, in
 }
 
 template <int KIND>
-__device__ void q_run(const BatchDev &D, const QTask &q, int fid, int nu1, int nu2, OpConst oc)
+__device__ void q_run(double *lds, const BatchDev &D, const QTask &q, int fid, int nu1, int nu2, OpConst oc)
 {
     const int b = q.item, i = q.level;
     if (q.phase == Q_COARSE) {
-        coarse_vcycle_box<KIND>(D, b, fid, nu1, nu2, oc);
+        coarse_vcycle_box<KIND, CTPB>(lds, D, b, fid, nu1, nu2, oc);
         return;
     }
     const BoxDev &X = D.box[b];
@@ -796,7 +807,7 @@ __device__ void q_run(const BatchDev &D, const QTask &q, int fid, int nu1, int n
             double J;
             const double Lv = op_point<KIND, double>(ph, nb_sum(phi, ii, y, z, n), inv_h2, load_c1<KIND>(V.coef, p),
                                                      0.0, oc, Fb, J);
-            phi[p] = ph - (Lv - (V.f[p] - fs)) / J;
+            phi[p] = newton_update<KIND, double>(ph, Lv, V.f[p] - fs, J, poisson_inv_diag(inv_h2));
         }
         return;
     }
@@ -860,6 +871,7 @@ __global__ void __launch_bounds__(CTPB) kb_queue(BatchDev D, const QTask *__rest
                                                  int *__restrict__ ctl, int *__restrict__ done, int fid, int nu1,
                                                  int nu2, OpConst oc, long spin_limit)
 {
+    __shared__ double lds[kCoarseLdsBytes / sizeof(double)]; // of the coarse cycle tasks
     __shared__ int s_t, s_go;
     for (;;) {
         if (threadIdx.x == 0) {
@@ -889,7 +901,7 @@ __global__ void __launch_bounds__(CTPB) kb_queue(BatchDev D, const QTask *__rest
         if (t >= ntasks) return;
         if (go) { // thread 0's acquire, then the barrier, orders every thread's reads after the wait
             const QTask q = tasks[t];
-            q_run<KIND>(D, q, fid, nu1, nu2, oc);
+            q_run<KIND>(lds, D, q, fid, nu1, nu2, oc);
             __syncthreads(); // every thread's writes before thread 0's release
             if (threadIdx.x == 0) __hip_atomic_fetch_add(&done[q.item], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -1106,26 +1118,27 @@ __global__ void __launch_bounds__(TPB) kb32_prolong(BatchDev D, const int *__res
 // the correction cycle from the box's FP32 entry level down, one workgroup per
 // box, computed in FP64 in LDS
 template <int LKIND>
-__global__ void __launch_bounds__(kCoarseThreads) kb32_coarse(BatchDev D, int nu1, int nu2, OpConst oc)
+__global__ void __launch_bounds__(kCoarseNT) kb32_coarse(BatchDev D, int nu1, int nu2, OpConst oc)
 {
+    __shared__ double lds[kCoarseLdsBytes / sizeof(double)];
+    __shared__ CoarseLevelsT<float> G;
     const int b = blockIdx.x;
     if (!D.active[b]) return;
     const BoxDev &X = D.box[b];
-    CoarseLevelsT<float> G;
-    G.nl = X.nlev - X.centry32;
-    for (int i = 0; i < G.nl; ++i) {
-        const BoxLev &V = X.lev[X.centry32 + i];
-        G.n[i] = V.n;
-        G.inv_h2[i] = 1.0 / (V.h * V.h);
-        G.phi[i] = V.e;
-        G.phi0[i] = nullptr;
-        G.f[i] = V.b32;
-        G.c1[i] = V.c32;
-        G.c2[i] = V.a32;
-        G.tmp[i] = V.t32;
+    if (threadIdx.x == 0) {
+        G.nl = X.nlev - X.centry32;
+        for (int i = 0; i < G.nl; ++i) {
+            const BoxLev &V = X.lev[X.centry32 + i];
+            G.n[i] = V.n;
+            G.inv_h2[i] = 1.0 / (V.h * V.h);
+            G.phi[i] = V.e;
+            G.f[i] = V.b32;
+            G.c1[i] = V.c32;
+            G.c2[i] = V.a32;
+        }
     }
-    const double *zero = D.scal + b * B_NSCAL + B_ZERO;
-    coarse_cycle_lds<LKIND, float, double>(G, nu1, nu2, oc, zero, zero);
+    __syncthreads();
+    coarse_cycle_lds<LKIND, kPeriodic, kCoarseNT, float, double>(lds, G, nu1, nu2, oc, 0.0, 0.0);
 }
 
 // phi += e - <e> (mean in B_MEAN), FP64
@@ -1491,7 +1504,7 @@ __device__ void cvp_sweep(double *__restrict__ phi, const double *__restrict__ f
     const int N = n * n * n;
     const SmallDiv dn(n);
     for (int colour = 0; colour < 2; ++colour) {
-        for (int t = threadIdx.x; t < N; t += CTPB) {
+        for (int t = threadIdx.x; t < N; t += kCoarseNT) {
             const int r = dn.div(t), k = dn.div(r);
             const int i = t - r * n, j = r - k * n;
             if (((i + j + k) & 1) != colour) continue;
@@ -1504,22 +1517,39 @@ __device__ void cvp_sweep(double *__restrict__ phi, const double *__restrict__ f
     }
 }
 
-constexpr int kPatchCoarseLds = 4096; // doubles of LDS for the coarsest patch level (32 KB)
-
 template <int KIND>
-__global__ void __launch_bounds__(CTPB) kp_coarse_vcycle(BatchDev D, int fid, int nu1, int nu2, OpConst oc, int b0)
+__global__ void __launch_bounds__(kCoarseNT) kp_coarse_vcycle(BatchDev D, int fid, int nu1, int nu2, OpConst oc, int b0)
 {
+    __shared__ double lds[kCoarseLdsBytes / sizeof(double)];
+    __shared__ CoarseLevelsT<double> G;
     const int b = b0 + blockIdx.x;
     if (!D.active[b]) return;
     const BoxDev &X = D.box[b];
     const int l0 = X.centry, L = X.nlev;
+    // every level in LDS where they fit (all sides whose coarse entry is at most 16^3)
+    if (coarse_lds_need<KIND, kFaces>(X.lev[l0].n, L - l0)) {
+        if (threadIdx.x == 0) {
+            G.nl = L - l0;
+            for (int i = 0; i < G.nl; ++i) {
+                const BoxLev &V = X.lev[l0 + i];
+                G.n[i] = V.n;
+                G.inv_h2[i] = 1.0 / (V.h * V.h);
+                G.phi[i] = patch_phi(X, l0 + i, fid);
+                G.f[i] = V.f;
+                G.c1[i] = V.coef;
+            }
+        }
+        __syncthreads();
+        coarse_cycle_lds<KIND, kFaces, kCoarseNT, double, double>(lds, G, nu1, nu2, oc, 0.0, 0.0);
+        return;
+    }
     for (int i = l0; i < L - 1; ++i) {
         const BoxLev &V = X.lev[i], &C = X.lev[i + 1];
         const int n = V.n, m = C.n, M = m * m * m;
         double *phi = patch_phi(X, i, fid);
         const double inv_h2 = 1.0 / (V.h * V.h);
         for (int it = 0; it < nu1; ++it) cvp_sweep<KIND>(phi, V.f, V.coef, n, inv_h2, oc);
-        for (int q = threadIdx.x; q < M; q += CTPB) {
+        for (int q = threadIdx.x; q < M; q += kCoarseNT) {
             const int I = q % m, J = (q / m) % m, K = q / (m * m);
             double sr = 0.0, sp = 0.0;
             for (int c = 0; c < 8; ++c) {
@@ -1536,7 +1566,7 @@ __global__ void __launch_bounds__(CTPB) kp_coarse_vcycle(BatchDev D, int fid, in
         }
         __syncthreads();
         const double inv_H2 = 1.0 / (C.h * C.h);
-        for (int q = threadIdx.x; q < M; q += CTPB) {
+        for (int q = threadIdx.x; q < M; q += kCoarseNT) {
             const int I = q % m, J = (q / m) % m, K = q / (m * m);
             double Jd;
             C.f[q] = patch_op<KIND>(C.phi, I, J, K, m, inv_H2, load_c1<KIND>(C.coef, q), oc, Jd) - C.tmp[q];
@@ -1544,36 +1574,16 @@ __global__ void __launch_bounds__(CTPB) kp_coarse_vcycle(BatchDev D, int fid, in
         __syncthreads();
     }
     {
-        // coarsest level: its 32 sweeps from LDS when the padded iterate, the
-        // source and the coefficient fit (every patch side of the usual
-        // hierarchies ends at 3^3 to 10^3), else from global memory
         const BoxLev &V = X.lev[L - 1];
-        double *phi = patch_phi(X, L - 1, fid);
-        const double inv_h2 = 1.0 / (V.h * V.h);
-        const int n = V.n, P = (n + 2) * (n + 2) * (n + 2), N = n * n * n;
-        constexpr int NC = kNumCoef<KIND>();
-        __shared__ double lds[kPatchCoarseLds];
-        if (P + (1 + NC) * N <= kPatchCoarseLds) {
-            double *sphi = lds, *sf = lds + P, *sc = lds + P + N;
-            for (int q = threadIdx.x; q < P; q += CTPB) sphi[q] = phi[q];
-            for (int q = threadIdx.x; q < N; q += CTPB) {
-                sf[q] = V.f[q];
-                if (NC >= 1) sc[q] = V.coef[q];
-            }
-            __syncthreads();
-            for (int it = 0; it < kCoarseSweeps; ++it) cvp_sweep<KIND>(sphi, sf, sc, n, inv_h2, oc);
-            for (int q = threadIdx.x; q < P; q += CTPB) phi[q] = sphi[q];
-            __syncthreads();
-        } else {
-            for (int it = 0; it < kCoarseSweeps; ++it) cvp_sweep<KIND>(phi, V.f, V.coef, n, inv_h2, oc);
-        }
+        for (int it = 0; it < kCoarseSweeps; ++it)
+            cvp_sweep<KIND>(patch_phi(X, L - 1, fid), V.f, V.coef, V.n, 1.0 / (V.h * V.h), oc);
     }
     for (int i = L - 2; i >= l0; --i) {
         const BoxLev &V = X.lev[i], &C = X.lev[i + 1];
         const int n = V.n, m = C.n, N = n * n * n;
         double *phi = patch_phi(X, i, fid);
         const double inv_h2 = 1.0 / (V.h * V.h);
-        for (int p = threadIdx.x; p < N; p += CTPB) {
+        for (int p = threadIdx.x; p < N; p += kCoarseNT) {
             const int a = p % n, bb = (p / n) % n, dd = p / (n * n);
             const int I = a >> 1, J = bb >> 1, K = dd >> 1;
             const int Is[2] = {I, I + ((a & 1) ? 1 : -1)};
@@ -1979,7 +1989,7 @@ int batch_cycle(gr_batch B, int kind, int fid, const gr_solve_opts &o)
         KDISPATCH(kind, kb_queue, B->qworkers, CTPB, B->D, B->qtasks, B->qcount, B->qctl, B->qdone, fid, o.nu1, o.nu2,
                   oc, kQSpin);
     } else {
-        KDISPATCH(kind, kb_coarse_vcycle, B->nper, CTPB, B->D, fid, o.nu1, o.nu2, oc);
+        KDISPATCH(kind, kb_coarse_vcycle, B->nper, kCoarseNT, B->D, fid, o.nu1, o.nu2, oc);
     }
     for (int d = B->maxdepth - 1; d >= 0; --d) {
         const Tab &TC = B->colour[d], &TD = B->cdom[d];
@@ -2136,7 +2146,7 @@ int batch_cycle_mixed(gr_batch B, int kind, int fid, const gr_solve_opts &o)
         batch_smooth32(B, kind, d, o.nu1);
         LDISPATCH(kind, kb32_lin_rr, B->rr32[d].total(), TPB, B->D, B->rr32[d].dev, d, oc);
     }
-    LDISPATCH(kind, kb32_coarse, B->nper, kCoarseThreads, B->D, o.nu1, o.nu2, oc);
+    LDISPATCH(kind, kb32_coarse, B->nper, kCoarseNT, B->D, o.nu1, o.nu2, oc);
     for (int d = B->maxdepth32 - 1; d >= 0; --d) {
         const Tab &TC = B->colour32[d];
         if (TC.total() == 0) continue;
@@ -2236,7 +2246,7 @@ int patch_cycle(gr_batch B, hipStream_t s, int kind, int fid, const gr_solve_opt
         KDISPATCH(kind, kp_rr, TC.total(), TPB, B->Dp, TC.dev, d, fid, oc);
         KDISPATCH(kind, kp_coarse_rhs, TC.total(), TPB, B->Dp, TC.dev, d, oc);
     }
-    KDISPATCH(kind, kp_coarse_vcycle, B->npatch, CTPB, B->Dp, fid, o.nu1, o.nu2, oc, B->nper);
+    KDISPATCH(kind, kp_coarse_vcycle, B->npatch, kCoarseNT, B->Dp, fid, o.nu1, o.nu2, oc, B->nper);
     for (int d = B->pmaxdepth - 1; d >= 0; --d) {
         if (B->pcell[d].total() == 0) continue;
         kp_prolong<<<B->pcellf[d].total(), TPB, 0, s>>>(B->Dp, B->pcellf[d].dev, d, fid);

@@ -665,12 +665,13 @@ __global__ void __launch_bounds__(CTPB) k_coarse_vcycle(CoarseLevelsT<T> C, int 
     coarse_vcycle_body<KIND, T>(C, nu1, nu2, oc, T(*fbar0), T(*fshift0));
 }
 
-template <int KIND, typename TG, typename T>
-__global__ void __launch_bounds__(CTPB) k_coarse_vcycle_lds(CoarseLevelsT<TG> G, int nu1, int nu2, OpConst oc,
-                                                            const double *__restrict__ fbar0,
-                                                            const double *__restrict__ fshift0)
+template <int KIND, typename TG, int NT, size_t BYTES>
+__global__ void __launch_bounds__(NT) k_coarse_vcycle_lds(CoarseLevelsT<TG> G, int nu1, int nu2, OpConst oc,
+                                                          const double *__restrict__ fbar0,
+                                                          const double *__restrict__ fshift0)
 {
-    coarse_cycle_lds<KIND, TG, T>(G, nu1, nu2, oc, fbar0, fshift0);
+    __shared__ double s[BYTES / sizeof(double)];
+    coarse_cycle_lds<KIND, kPeriodic, NT, TG, double>(s, G, nu1, nu2, oc, *fbar0, *fshift0);
 }
 
 // ------------------------------------------------ mixed-precision outer steps
@@ -1057,18 +1058,6 @@ struct EwF64ToF32 {
         }                                                                                             \
     } while (0)
 
-#define GR_DISPATCH_K2T(kind, TG, T, KERNEL, GRID, BLOCK, ...)                                          \
-    do {                                                                                              \
-        switch (kind) {                                                                               \
-        case GR_KIND_POISSON: KERNEL<GR_KIND_POISSON, TG, T><<<GRID, BLOCK, 0, s>>>(__VA_ARGS__); break; \
-        case GR_KIND_HAMILTONIAN: KERNEL<GR_KIND_HAMILTONIAN, TG, T><<<GRID, BLOCK, 0, s>>>(__VA_ARGS__); break; \
-        case GR_KIND_CMC: KERNEL<GR_KIND_CMC, TG, T><<<GRID, BLOCK, 0, s>>>(__VA_ARGS__); break;      \
-        case K_LIN_POISSON: KERNEL<K_LIN_POISSON, TG, T><<<GRID, BLOCK, 0, s>>>(__VA_ARGS__); break;  \
-        case K_LIN_HAM: KERNEL<K_LIN_HAM, TG, T><<<GRID, BLOCK, 0, s>>>(__VA_ARGS__); break;          \
-        default: KERNEL<K_LIN_CMC, TG, T><<<GRID, BLOCK, 0, s>>>(__VA_ARGS__); break;                 \
-        }                                                                                             \
-    } while (0)
-
 template <typename T>
 void launch_rb_sweep_t(int kind, hipStream_t s, T *phi, const T *f, const T *c1, const T *c2, int n, double h,
                        OpConst oc, const double *fbar, const double *fshift)
@@ -1396,34 +1385,33 @@ void launch_restrict_f32(hipStream_t s, const float *fine, int n, float *coarse)
     k_restrict<float><<<G.grid, G.block, 0, s>>>(fine, n, coarse);
 }
 
-template <typename TG, typename T>
-static bool coarse_lds_fits(int kind, const CoarseLevelsT<TG> &C)
+// the cycle from LDS where its levels fit (GRMG_COARSE_LDS=0: never)
+template <int KIND, typename TG>
+static bool coarse_in_lds(hipStream_t s, const CoarseLevelsT<TG> &C, int nu1, int nu2, OpConst oc, const double *fbar0,
+                          const double *fshift0)
 {
     static const bool on = [] {
         const char *e = std::getenv("GRMG_COARSE_LDS");
         return !(e && std::atoi(e) == 0);
     }();
-    if (!on) return false;
-    size_t b = 0;
-    switch (kind) {
-    case GR_KIND_POISSON: b = coarse_lds_layout<GR_KIND_POISSON, TG, T>(C, nullptr, (T *)nullptr); break;
-    case GR_KIND_HAMILTONIAN: b = coarse_lds_layout<GR_KIND_HAMILTONIAN, TG, T>(C, nullptr, (T *)nullptr); break;
-    case GR_KIND_CMC: b = coarse_lds_layout<GR_KIND_CMC, TG, T>(C, nullptr, (T *)nullptr); break;
-    case K_LIN_POISSON: b = coarse_lds_layout<K_LIN_POISSON, TG, T>(C, nullptr, (T *)nullptr); break;
-    case K_LIN_HAM: b = coarse_lds_layout<K_LIN_HAM, TG, T>(C, nullptr, (T *)nullptr); break;
-    default: b = coarse_lds_layout<K_LIN_CMC, TG, T>(C, nullptr, (T *)nullptr); break;
-    }
-    return b <= kCoarseLdsBytes;
+    if (!on || !coarse_lds_need<KIND, kPeriodic>(C.n[0], C.nl)) return false;
+    if (C.n[0] <= 8)
+        k_coarse_vcycle_lds<KIND, TG, kCoarseNTSmall, kCoarseLdsSmall>
+            <<<1, kCoarseNTSmall, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0);
+    else
+        k_coarse_vcycle_lds<KIND, TG, kCoarseNT, kCoarseLdsBytes>
+            <<<1, kCoarseNT, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0);
+    return true;
 }
 
 void launch_coarse_vcycle(int kind, hipStream_t s, const CoarseLevelsT<double> &C, int nu1, int nu2, OpConst oc,
                           const double *fbar0, const double *fshift0)
 {
-    if (coarse_lds_fits<double, double>(kind, C)) {
-        GR_DISPATCH_K2T(kind, double, double, k_coarse_vcycle_lds, 1, CTPB, C, nu1, nu2, oc, fbar0, fshift0);
-        return;
-    }
-    GR_DISPATCH_KT(kind, double, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, fbar0, fshift0);
+    const bool done = kind == GR_KIND_POISSON ? coarse_in_lds<GR_KIND_POISSON>(s, C, nu1, nu2, oc, fbar0, fshift0)
+                      : kind == GR_KIND_HAMILTONIAN
+                          ? coarse_in_lds<GR_KIND_HAMILTONIAN>(s, C, nu1, nu2, oc, fbar0, fshift0)
+                          : coarse_in_lds<GR_KIND_CMC>(s, C, nu1, nu2, oc, fbar0, fshift0);
+    if (!done) GR_DISPATCH_KT(kind, double, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, fbar0, fshift0);
 }
 
 void launch_coarse_vcycle_f32(int kind, hipStream_t s, const CoarseLevelsT<float> &C, int nu1, int nu2, OpConst oc,
@@ -1431,11 +1419,10 @@ void launch_coarse_vcycle_f32(int kind, hipStream_t s, const CoarseLevelsT<float
 {
     // FP32 arrays, the cycle in FP64 in LDS (the global-memory fallback, for
     // thresholds whose levels do not fit, computes in FP32)
-    if (coarse_lds_fits<float, double>(kind, C)) {
-        GR_DISPATCH_K2T(kind, float, double, k_coarse_vcycle_lds, 1, CTPB, C, nu1, nu2, oc, zero, zero);
-        return;
-    }
-    GR_DISPATCH_KT(kind, float, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, zero, zero);
+    const bool done = kind == K_LIN_POISSON ? coarse_in_lds<K_LIN_POISSON>(s, C, nu1, nu2, oc, zero, zero)
+                      : kind == K_LIN_HAM ? coarse_in_lds<K_LIN_HAM>(s, C, nu1, nu2, oc, zero, zero)
+                                          : coarse_in_lds<K_LIN_CMC>(s, C, nu1, nu2, oc, zero, zero);
+    if (!done) GR_DISPATCH_KT(kind, float, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, zero, zero);
 }
 
 void launch_ir_residual(int kind, hipStream_t s, const double *phi, const double *f, const double *coef, int n,

@@ -64,17 +64,16 @@ __device__ __forceinline__ T op_point(T ph, T nbs, T inv_h2, T c1, T c2, OpConst
     }
 }
 
-// The point update ph - (L - fe) / J of every smoother.  The correction
-// equation of the Poisson kind (FP32 sweeps, FP64 coarse levels) has the constant
-// diagonal J = -6/h^2: there the update multiplies by its reciprocal rJ (formed
-// once per kernel from inv_h2), within an ulp of the division, which the
-// correction does not need.
+// The point update ph - (L - fe) / J of every smoother.  The Poisson kinds have
+// the constant diagonal J = -6/h^2: there the update multiplies by its
+// reciprocal rJ (formed once per kernel from inv_h2), within an ulp of the
+// division and a third of the point's instructions.
 template <typename T> __device__ __forceinline__ T poisson_inv_diag(T inv_h2) { return T(1) / (T(-6) * inv_h2); }
 
 template <int KIND, typename T>
 __device__ __forceinline__ T newton_update(T ph, T L, T fe, T J, T rJ)
 {
-    if constexpr (KIND == K_LIN_POISSON)
+    if constexpr (KIND == GR_KIND_POISSON || KIND == K_LIN_POISSON)
         return ph - (L - fe) * rJ;
     else
         return ph - (L - fe) / J;

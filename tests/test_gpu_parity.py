@@ -472,3 +472,21 @@ def test_invalid_arguments_are_rejected():
     small = torch.empty(1024, dtype=torch.uint8, device="cuda")
     with pytest.raises(grmg.GrError):
         grmg.bind(g.handle, small, 0)
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("n", [2, 4, 6, 8, 10, 14, 16, 20, 24, 28])
+def test_coarse_cycle_of_every_coarsest_side(kind, n):
+    """Coarsest levels of 2^3 (registers; the Poisson kind in closed form), 6^3
+    (one wavefront), 10^3 and 14^3 (the workgroup), alone and under one or two
+    levels: four cycles against the oracle, the whole-solve bar 1e-12."""
+    k = KINDS[kind]
+    f, coef, prm = _manufactured(k, n)
+    guess = 1e-3 * np.random.default_rng(n).standard_normal((n, n, n))
+    g = grid(n, prm)
+    g.set_field("rhs", f)
+    g.set_field("coef", coef)
+    g.set_field("U", guess)
+    g.solve_equation(k, "U", guess="current", rtol=0, max_cycles=4)
+    ref = O.solve_equation(k, guess, f, coef, prm=O.params(**prm), rtol=0, max_cycles=4)[0]
+    assert maxrel(g.get_field("U"), ref) < 1e-12

@@ -264,3 +264,26 @@ def test_patch_substep_keeps_the_coarse_fields():
             got = B.get_field(len(boxes) + j, k).cpu().numpy()
             assert maxrel(got, ref[j][0][k]) < 1e-12, (j, k)
 
+
+
+def test_every_coarsest_patch_side_matches_oracle():
+    """Sides whose coarsest level is swept in one wavefront (3, 4, 5, 6) or by
+    the workgroup (7, 9), odd and even, alone and below one or two levels, after
+    exactly 6 cycles per field: 1e-12, as the whole-solve test."""
+    K, box = 6, 24
+    sides = (3, 4, 6, 7, 9, 10, 12, 14)
+    patches = [(n, 1 / 48, 0, ((2 + j) / 24, 0.25, 0.5)) for j, n in enumerate(sides)]
+    print("[gpu] patch coarsest sides", flush=True)
+    box_src = synth._matter_sources(box, 310, 0.2)
+    patch_src = [synth._matter_sources(n, 500 + j, 0.1) for j, n in enumerate(sides)]
+    B = grmg.Batch([box], **PRM, patches=patches)
+    _load(B, [box], [box_src], patch_src)
+    assert B.solve(rtol=0.0, max_cycles=K)["status"] == grmg.OK
+    prm = O.params(a=PRM["a"], omega_m=PRM["omega_m"], c_tilde=PRM["c_tilde"])
+    F, st, cyc, rel, AA = O.solve_all(*box_src, prm=prm, max_cycles=K, rtol=0.0)
+    A6 = O.build_Aij(F["Vx"], F["Vy"], F["Vz"], F["U"])[0]
+    for j, (n, h, par, o) in enumerate(patches):
+        out, st, cyc, rel, AA = OD.solve_patch(F, A6, 1.0 / box, dict(zip(SRC, patch_src[j])), n, h, o, prm,
+                                               max_cycles=K, rtol=0.0)
+        for k in OD.FIELDS:
+            assert maxrel(B.get_field(1 + j, k).cpu().numpy(), OD.interior(out[k])) < 1e-12, (n, k)
