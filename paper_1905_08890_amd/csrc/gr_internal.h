@@ -24,6 +24,8 @@ enum Slot {
     S_RN = 5,        // sum eps^2   (pair with S_FN)
     S_FN = 6,        // sum (f - fshift)^2
     S_SCRATCH = 8,   // 8 general slots
+    S_CONTROL = 16,  // a SolveControl (3 slots)
+    S_COUNT = 20,    // arrival counter of SmallSum
     S_NUM = 32
 };
 
@@ -78,10 +80,58 @@ template <typename T> struct CoarseLevelsT {
     double inv_h2[kMaxLevels];
     T *phi[kMaxLevels], *phi0[kMaxLevels], *f[kMaxLevels], *c1[kMaxLevels], *c2[kMaxLevels], *tmp[kMaxLevels];
 };
+// stop (may be null): nonzero there, the launch does nothing (LDS form only)
 void launch_coarse_vcycle(int kind, hipStream_t s, const CoarseLevelsT<double> &C, int nu1, int nu2, OpConst oc,
-                          const double *fbar0, const double *fshift0);
+                          const double *fbar0, const double *fshift0, const int *stop = nullptr);
+bool coarse_cycle_in_lds(int kind, int n0, int nl); // whether launch_coarse_vcycle runs from LDS
 void launch_coarse_vcycle_f32(int kind, hipStream_t s, const CoarseLevelsT<float> &C, int nu1, int nu2, OpConst oc,
                               const double *zero);
+
+// ---- small_level.hip: a whole leg of the V-cycle on a small level in one launch ----
+// (nu = 1 or 2 sweeps, n even, 8 or at least 12, at most 64; in and out are different arrays, in may be null for a
+// zero iterate on the way down.)  down: sweeps, residual, restriction, coarse source
+// (phi_c, phi0_c, f_c from the coarse coefficient coef_c; correction kinds: f_c and
+// phi_c = 0).  up: prolongation of phi_c (FAS: phi_c - phi0_c), sweeps.
+// A sum over a grid finished by the workgroup that arrives last: partial sums
+// (kReduceBlocks per quantity), arrival counter (zero between uses), *out = scale * sum.
+struct SmallSum {
+    double *partials;
+    unsigned *count;
+    double *out;
+    double scale;
+};
+// Device-side control of a solve whose cycles are queued ahead of the stopping test
+struct SolveControl {
+    double rtol;
+    int max_cycles, cycle, stop;
+};
+template <typename T> struct SmallLeg {
+    const T *in;
+    T *out;
+    const T *f, *c1, *c2;
+    int n;
+    double h;
+    T *phi_c, *phi0_c, *f_c;
+    const T *coef_c;
+    const int *stop = nullptr;                           // nonzero there: the launch does nothing
+    SmallSum sum = {nullptr, nullptr, nullptr, 0.0};     // up: also the sum of the iterate, if partials
+};
+// solve start: control, arrival counter and the frozen scalars
+void launch_solve_begin(hipStream_t s, SolveControl *ctl, double rtol, int max_cycles, unsigned *count, double *fbar,
+                        double *fshift);
+// phi -= *mean and the next cycle's frozen mean (Hamiltonian <F>; CMC *add + <coef phi>) in *sum.out
+void launch_pin_frozen(int kind, hipStream_t s, double *phi, const double *f, const double *coef, long N, OpConst oc,
+                       const double *mean, const double *add, const SmallSum &sum, const int *stop);
+// stopping norms to sum.out[0..1], decision to ctl, both to the page-locked slot host[4 (cycle & 1)]
+void launch_norms_decide(int kind, hipStream_t s, const double *phi, const double *f, const double *coef, int n, double h,
+                         OpConst oc, const double *fbar, const double *fshift, const SmallSum &sum, SolveControl *ctl,
+                         double *host);
+void launch_small_down(int kind, hipStream_t s, const SmallLeg<double> &L, int nu, OpConst oc, const double *fbar,
+                       const double *fshift);
+void launch_small_up(int kind, hipStream_t s, const SmallLeg<double> &L, int nu, OpConst oc, const double *fbar,
+                     const double *fshift);
+void launch_small_down_f32(int kind, hipStream_t s, const SmallLeg<float> &L, int nu, OpConst oc, const double *zero);
+void launch_small_up_f32(int kind, hipStream_t s, const SmallLeg<float> &L, int nu, OpConst oc, const double *zero);
 
 // ---- FP32 correction-scheme kernels (mixed precision) ----
 void launch_rb_sweep_f32(int kind, hipStream_t s, float *e, const float *b, const float *c1, const float *c2, int n,

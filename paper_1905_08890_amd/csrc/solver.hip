@@ -97,6 +97,7 @@ struct gr_grid_s {
     int coarse_n32 = 8;    // the same for the FP32 correction cycles
     int coarse_np = 16;    // the same threshold for the Poisson kind (FP64 and correction cycles): its point
                            // update is cheap enough for one CU to take a 16^3 level faster than ~11 launches
+    int small_n = 64;      // levels with n <= small_n run each leg of their V-cycle in one launch
     int skew = 0;          // workspace array skew in bytes (see layout)
     double stall_ratio = 0.5; // mixed precision: a refinement step that keeps more than this
                               // fraction of the residual counts as stalled (two in a row: FP64)
@@ -112,6 +113,7 @@ struct gr_grid_s {
     // static grid)
     double *h_norms = nullptr, *d_norms = nullptr;
     hipEvent_t ev_norms = nullptr;
+    bool ahead = true; // queue a cycle before the norms of the one before it (h_norms[0..3], [4..7]: even, odd cycles)
     bool use_graph = true;
     struct GraphEntry {
         int prec, kind, nu1, nu2;
@@ -324,6 +326,8 @@ struct EqCtx {
     int kind;
     OpConst oc;
     int nu1, nu2;
+    const int *stop = nullptr; // cycles queued ahead of the stopping test (solve_one_ahead)
+    SmallSum sum = {nullptr, nullptr, nullptr, 0.0}; // the finest level's last launch also sums the iterate
 };
 
 const double *fbar_ptr(gr_grid g, int l) { return g->scal + (l == 0 ? S_FBAR : S_ZERO); }
@@ -421,6 +425,17 @@ int vcycle(gr_grid g, const EqCtx &E, int l)
     return st;
 }
 
+// Levels whose legs of the V-cycle run in one launch each (small_level.hip).  Its
+// sweeps are not the ones gr_sweep_timing counts, so a timed finest level keeps them.
+// Up to 64^3 by default: a 64^3 level's 26 launches of 3.3-5 us become two of 25 and
+// 19 us; at 96^3 the tiles queue 7 deep and the tiled sweeps are as fast.  The regions
+// wrap around at most once, which a last tile of a 10^3 level would exceed.
+bool use_small(gr_grid g, int l, int nu1, int nu2)
+{
+    const int n = g->lev[l].n;
+    return n <= g->small_n && n >= 8 && n != 10 && nu1 >= 1 && nu1 <= 2 && nu2 >= 1 && nu2 <= 2 && !(g->timing && l == 0);
+}
+
 int vcycle_body(gr_grid g, const EqCtx &E, int l)
 {
     Level &L = g->lev[l];
@@ -439,7 +454,7 @@ int vcycle_body(gr_grid g, const EqCtx &E, int l)
             C.c2[i] = nullptr;
             C.tmp[i] = V.tmp;
         }
-        launch_coarse_vcycle(E.kind, s, C, E.nu1, E.nu2, E.oc, fbar_ptr(g, l), fshift_ptr(g, l));
+        launch_coarse_vcycle(E.kind, s, C, E.nu1, E.nu2, E.oc, fbar_ptr(g, l), fshift_ptr(g, l), E.stop);
         LAUNCHCHK();
         return GR_OK;
     }
@@ -451,6 +466,21 @@ int vcycle_body(gr_grid g, const EqCtx &E, int l)
         CHK(reduce_mean(g, L.phi, L.tmp, L.N, g->scal + S_MEAN));
         launch_sub_scalar(s, L.phi, L.N, g->scal + S_MEAN);
         LAUNCHCHK();
+        return GR_OK;
+    }
+    if (use_small(g, l, E.nu1, E.nu2)) { // out of place both ways, so the iterate ends where it was
+        Level &C = g->lev[l + 1];
+        SmallLeg<double> P{L.phi, L.tmp, L.f, L.coef, nullptr, L.n, L.h, C.phi, C.phi0, C.f, C.coef, E.stop};
+        launch_small_down(E.kind, s, P, E.nu1, E.oc, fbar_ptr(g, l), fshift_ptr(g, l));
+        LAUNCHCHK();
+        std::swap(L.phi, L.tmp);
+        CHK(vcycle(g, E, l + 1));
+        P.in = L.phi;
+        P.out = L.tmp;
+        if (l == 0) P.sum = E.sum;
+        launch_small_up(E.kind, s, P, E.nu2, E.oc, fbar_ptr(g, l), fshift_ptr(g, l));
+        LAUNCHCHK();
+        std::swap(L.phi, L.tmp);
         return GR_OK;
     }
     CHK(smooth(g, E, l, E.nu1));
@@ -467,12 +497,109 @@ int vcycle_body(gr_grid g, const EqCtx &E, int l)
     return smooth(g, E, l, E.nu2);
 }
 
+// Whether every launch of this kind's V-cycle can be told to do nothing: each level
+// a small leg or the coarse cycle in LDS, and norms written to the host by the device.
+bool can_queue_ahead(gr_grid g, int kind, const gr_solve_opts &o)
+{
+    if (!g->d_norms || !g->ahead) return false;
+    for (int l = 0; l < g->nlev; ++l) {
+        if (g->lev[l].n <= (kind == GR_KIND_POISSON ? g->coarse_np : g->coarse_n))
+            return l > 0 && coarse_cycle_in_lds(kind, g->lev[l].n, g->nlev - l);
+        if (l == g->nlev - 1 || !use_small(g, l, o.nu1, o.nu2)) return false;
+    }
+    return false;
+}
+
+// Waits until the device has left the norms of cycle `cyc` in its page-locked slot.
+// The work behind it keeps the stream busy, so a stream that has run dry (or failed)
+// without the mark is an error, not a reason to wait on.
+int wait_norms(gr_grid g, int cyc)
+{
+    const volatile double *mark = g->h_norms + 4 * (cyc & 1) + 3;
+    for (unsigned spin = 1;; ++spin) {
+        if (*mark == (double)(cyc + 1)) return GR_OK;
+        if (spin % 4096 == 0) {
+            const hipError_t e = hipStreamQuery(g->stream);
+            if (e == hipErrorNotReady) continue;
+            if (e != hipSuccess) return fail(GR_EDEVICE, "norm read-back: %s", hipGetErrorString(e));
+            if (*mark != (double)(cyc + 1)) return fail(GR_EDEVICE, "norm read-back: the cycle left no norms");
+        }
+    }
+}
+
+// solve_one for such grids: a cycle is launched before the stopping norms of the one
+// before it are known, so the device does not wait for the host between cycles (~20 us
+// each); the launches of a cycle that turns out not to be needed find the device's own
+// stop flag set and do nothing.  Same cycles, same stopping test.  A 32^3 Hamiltonian
+// solve of ten cycles: 1.18 ms waiting, 1.07 with graphs started ahead, 0.88 with launches
+// ahead and the norms polled in page-locked memory.
+int solve_one_ahead(gr_grid g, int kind, double *phi, const gr_solve_opts &o, int *cycles_out, double *rel_out)
+{
+    const long N = g->N();
+    Level &F = g->lev[0];
+    F.phi = phi;
+    hipStream_t s = g->stream;
+    EqCtx E{kind, g->oc(), o.nu1, o.nu2};
+    SolveControl *ctl = reinterpret_cast<SolveControl *>(g->scal + S_CONTROL);
+    unsigned *count = reinterpret_cast<unsigned *>(g->scal + S_COUNT);
+    E.stop = &ctl->stop;
+    const double scale = 1.0 / (double)N;
+    if (kind != GR_KIND_POISSON)
+        for (int l = 1; l < g->nlev; ++l) launch_restrict(s, g->lev[l - 1].coef, g->lev[l - 1].n, g->lev[l].coef);
+    launch_solve_begin(s, ctl, o.rtol, o.max_cycles, count, g->scal + S_FBAR, g->scal + S_FSHIFT);
+    g->h_norms[3] = g->h_norms[7] = 0.0; // the marks; nothing queued writes them before this solve's first norms
+    if (kind == GR_KIND_CMC) CHK(reduce_mean(g, F.f, nullptr, N, g->scal + S_FMEAN));
+    LAUNCHCHK();
+    // the nonlinear kinds: pin (mean already in S_MEAN) and the next frozen mean, then the norms
+    auto measure = [&]() -> int {
+        if (kind != GR_KIND_POISSON)
+            launch_pin_frozen(kind, s, phi, F.f, F.coef, N, E.oc, g->scal + S_MEAN,
+                              kind == GR_KIND_CMC ? g->scal + S_FMEAN : nullptr,
+                              SmallSum{g->partials, count, g->scal + (kind == GR_KIND_CMC ? S_FSHIFT : S_FBAR), scale},
+                              E.stop);
+        launch_norms_decide(kind, s, phi, F.f, F.coef, F.n, F.h, E.oc, g->scal + S_FBAR, g->scal + S_FSHIFT,
+                            SmallSum{g->partials, count, g->scal + S_RN, scale}, ctl, g->d_norms);
+        LAUNCHCHK();
+        return GR_OK;
+    };
+    if (kind != GR_KIND_POISSON) E.sum = SmallSum{g->partials, count, g->scal + S_MEAN, scale};
+    auto cycle = [&]() -> int {
+        CHK(vcycle(g, E, 0));
+        return measure();
+    };
+    if (kind == GR_KIND_POISSON) CHK(pin_mean(g, phi, N));
+    else CHK(reduce_mean(g, phi, nullptr, N, g->scal + S_MEAN));
+    CHK(measure());
+    int cyc = 0;
+    double rel = 0.0;
+    int st = GR_OK;
+    for (;;) {
+        CHK(cycle()); // cycle cyc + 1, launch by launch: a graph's start leaves the device idle for ~13 us
+        CHK(wait_norms(g, cyc));
+        const volatile double *slot = g->h_norms + 4 * (cyc & 1);
+        const double rn = std::sqrt(slot[0]), fn = std::sqrt(slot[1]);
+        rel = rn / (fn > 0.0 ? fn : 1.0);
+        if (slot[2] != 0.0) { // the device's decision; the host only names it
+            if (!std::isfinite(rel)) st = fail(GR_ENAN, "non-finite residual (kind %d, cycle %d)", kind, cyc);
+            else if (o.rtol > 0.0 && !(rel <= o.rtol || rn == 0.0))
+                st = fail(GR_ENOTCONV, "kind %d: rel residual %.3e after %d cycles", kind, rel, cyc);
+            break;
+        }
+        ++cyc;
+    }
+    if (kind == GR_KIND_POISSON && cyc > 0) CHK(pin_mean(g, phi, N));
+    *cycles_out = cyc;
+    *rel_out = rel;
+    return st;
+}
+
 // Solve one equation for `phi` (fine), with fine source lev[0].f and fine
 // coefficient lev[0].coef already in place.  Follows the cycle definition:
 // pin the guess; per cycle: frozen means, residual norm, stopping test,
 // V-cycle, pin.
 int solve_one(gr_grid g, int kind, double *phi, const gr_solve_opts &o, int *cycles_out, double *rel_out)
 {
+    if (can_queue_ahead(g, kind, o)) return solve_one_ahead(g, kind, phi, o, cycles_out, rel_out);
     const long N = g->N();
     Level &F = g->lev[0];
     F.phi = phi;
@@ -617,6 +744,20 @@ int vcycle32_body(gr_grid g, int lkind, int l, int nu1, int nu2, OpConst oc, boo
         }
         launch_coarse_vcycle_f32(lkind, s, C, nu1, nu2, oc, g->scal + S_ZERO);
         LAUNCHCHK();
+        return GR_OK;
+    }
+    if (use_small(g, l, nu1, nu2)) {
+        Level32 &C = g->lev32[l + 1];
+        SmallLeg<float> P{e_unset ? nullptr : V.e, V.tmp, V.b, V.c, V.a, L.n, L.h, C.e, nullptr, C.b, nullptr};
+        launch_small_down_f32(lkind, s, P, nu1, oc, g->scal + S_ZERO);
+        LAUNCHCHK();
+        std::swap(V.e, V.tmp);
+        CHK(vcycle32(g, lkind, l + 1, nu1, nu2, oc, false));
+        P.in = V.e;
+        P.out = V.tmp;
+        launch_small_up_f32(lkind, s, P, nu2, oc, g->scal + S_ZERO);
+        LAUNCHCHK();
+        std::swap(V.e, V.tmp);
         return GR_OK;
     }
     CHK(smooth32(g, lkind, l, nu1, oc, e_unset));
@@ -934,11 +1075,14 @@ int gr_create_grid(const gr_grid_desc *desc, const gr_params *prm, gr_grid *out)
     // at or below this size run the rest of the V-cycle in one workgroup; 0: never;
     // GRMG_COARSE_N32 likewise for the FP32 correction cycles; GRMG_COARSE_NP the
     // same for the Poisson kind in both, 16 by default),
+    // GRMG_SMALL_N (largest level whose legs run in one launch each; 0: none),
+    // GRMG_AHEAD (0: wait for the stopping norms before the next cycle is launched),
     // GRMG_MIXED_STALL (mixed-precision stagnation ratio), GRMG_GRAPH (0: launch
     // every cycle's kernels one by one instead of replaying a captured graph)
     if (const char *e = std::getenv("GRMG_SMOOTHER")) {
         g->fused = std::strcmp(e, "split") != 0;
         if (std::strcmp(e, "fused") == 0) g->fcfg.min_n = 64;
+        g->small_n = 0; // the forced smoother on the small levels too
     }
     if (const char *e = std::getenv("GRMG_FUSED_MIN")) g->fcfg.min_n = std::atoi(e);
     if (const char *e = std::getenv("GRMG_FUSED_TILE")) g->fcfg.tile = std::min(3, std::max(0, std::atoi(e)));
@@ -948,6 +1092,8 @@ int gr_create_grid(const gr_grid_desc *desc, const gr_params *prm, gr_grid *out)
     if (const char *e = std::getenv("GRMG_COARSE_N")) g->coarse_n = std::atoi(e);
     if (const char *e = std::getenv("GRMG_COARSE_N32")) g->coarse_n32 = std::atoi(e);
     if (const char *e = std::getenv("GRMG_COARSE_NP")) g->coarse_np = std::atoi(e);
+    if (const char *e = std::getenv("GRMG_SMALL_N")) g->small_n = std::min(64, std::atoi(e));
+    if (const char *e = std::getenv("GRMG_AHEAD")) g->ahead = std::atoi(e) != 0;
     if (const char *e = std::getenv("GRMG_MIXED_STALL")) g->stall_ratio = std::atof(e);
     if (const char *e = std::getenv("GRMG_GRAPH")) g->use_graph = std::atoi(e) != 0;
     if (const char *e = std::getenv("GRMG_SKEW")) g->skew = std::max(0, std::atoi(e));
@@ -985,6 +1131,8 @@ int gr_create_grid(const gr_grid_desc *desc, const gr_params *prm, gr_grid *out)
             h->coarse_n = g->coarse_n;
             h->coarse_n32 = g->coarse_n32;
             h->coarse_np = g->coarse_np;
+            h->small_n = g->small_n;
+            h->ahead = g->ahead;
             h->stall_ratio = g->stall_ratio;
             h->use_graph = g->use_graph;
             h->skew = g->skew;
@@ -1019,7 +1167,7 @@ int gr_bind(gr_grid g, void *d_ws, size_t bytes, void *stream)
         HIPCHK(hipEventCreateWithFlags(&g->ev_in, hipEventDisableTiming));
         HIPCHK(hipEventCreateWithFlags(&g->ev_out, hipEventDisableTiming));
         HIPCHK(hipEventCreateWithFlags(&g->ev_norms, hipEventDisableTiming));
-        HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&g->h_norms), 2 * sizeof(double),
+        HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&g->h_norms), 8 * sizeof(double),
                              hipHostMallocMapped | hipHostMallocCoherent));
         HIPCHK(hipHostGetDevicePointer(reinterpret_cast<void **>(&g->d_norms), g->h_norms, 0));
     }
@@ -1031,7 +1179,7 @@ int gr_bind(gr_grid g, void *d_ws, size_t bytes, void *stream)
             HIPCHK(hipEventCreateWithFlags(&h->ev_in, hipEventDisableTiming));
             HIPCHK(hipEventCreateWithFlags(&h->ev_out, hipEventDisableTiming));
             HIPCHK(hipEventCreateWithFlags(&h->ev_norms, hipEventDisableTiming));
-            HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->h_norms), 2 * sizeof(double),
+            HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->h_norms), 8 * sizeof(double),
                                  hipHostMallocMapped | hipHostMallocCoherent));
             HIPCHK(hipHostGetDevicePointer(reinterpret_cast<void **>(&h->d_norms), h->h_norms, 0));
         }

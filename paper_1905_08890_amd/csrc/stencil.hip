@@ -668,9 +668,11 @@ __global__ void __launch_bounds__(CTPB) k_coarse_vcycle(CoarseLevelsT<T> C, int 
 template <int KIND, typename TG, int NT, size_t BYTES>
 __global__ void __launch_bounds__(NT) k_coarse_vcycle_lds(CoarseLevelsT<TG> G, int nu1, int nu2, OpConst oc,
                                                           const double *__restrict__ fbar0,
-                                                          const double *__restrict__ fshift0)
+                                                          const double *__restrict__ fshift0,
+                                                          const int *__restrict__ stop)
 {
     __shared__ double s[BYTES / sizeof(double)];
+    if (stop && *stop) return;
     coarse_cycle_lds<KIND, kPeriodic, NT, TG, double>(s, G, nu1, nu2, oc, *fbar0, *fshift0);
 }
 
@@ -1385,32 +1387,44 @@ void launch_restrict_f32(hipStream_t s, const float *fine, int n, float *coarse)
     k_restrict<float><<<G.grid, G.block, 0, s>>>(fine, n, coarse);
 }
 
-// the cycle from LDS where its levels fit (GRMG_COARSE_LDS=0: never)
-template <int KIND, typename TG>
-static bool coarse_in_lds(hipStream_t s, const CoarseLevelsT<TG> &C, int nu1, int nu2, OpConst oc, const double *fbar0,
-                          const double *fshift0)
+static bool coarse_lds_on()
 {
     static const bool on = [] {
         const char *e = std::getenv("GRMG_COARSE_LDS");
         return !(e && std::atoi(e) == 0);
     }();
-    if (!on || !coarse_lds_need<KIND, kPeriodic>(C.n[0], C.nl)) return false;
+    return on;
+}
+
+bool coarse_cycle_in_lds(int kind, int n0, int nl)
+{
+    if (!coarse_lds_on()) return false;
+    return kind == GR_KIND_POISSON ? coarse_lds_need<GR_KIND_POISSON, kPeriodic>(n0, nl) != 0
+                                   : coarse_lds_need<GR_KIND_HAMILTONIAN, kPeriodic>(n0, nl) != 0;
+}
+
+// the cycle from LDS where its levels fit (GRMG_COARSE_LDS=0: never)
+template <int KIND, typename TG>
+static bool coarse_in_lds(hipStream_t s, const CoarseLevelsT<TG> &C, int nu1, int nu2, OpConst oc, const double *fbar0,
+                          const double *fshift0, const int *stop)
+{
+    if (!coarse_lds_on() || !coarse_lds_need<KIND, kPeriodic>(C.n[0], C.nl)) return false;
     if (C.n[0] <= 8)
         k_coarse_vcycle_lds<KIND, TG, kCoarseNTSmall, kCoarseLdsSmall>
-            <<<1, kCoarseNTSmall, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0);
+            <<<1, kCoarseNTSmall, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0, stop);
     else
         k_coarse_vcycle_lds<KIND, TG, kCoarseNT, kCoarseLdsBytes>
-            <<<1, kCoarseNT, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0);
+            <<<1, kCoarseNT, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0, stop);
     return true;
 }
 
 void launch_coarse_vcycle(int kind, hipStream_t s, const CoarseLevelsT<double> &C, int nu1, int nu2, OpConst oc,
-                          const double *fbar0, const double *fshift0)
+                          const double *fbar0, const double *fshift0, const int *stop)
 {
-    const bool done = kind == GR_KIND_POISSON ? coarse_in_lds<GR_KIND_POISSON>(s, C, nu1, nu2, oc, fbar0, fshift0)
+    const bool done = kind == GR_KIND_POISSON ? coarse_in_lds<GR_KIND_POISSON>(s, C, nu1, nu2, oc, fbar0, fshift0, stop)
                       : kind == GR_KIND_HAMILTONIAN
-                          ? coarse_in_lds<GR_KIND_HAMILTONIAN>(s, C, nu1, nu2, oc, fbar0, fshift0)
-                          : coarse_in_lds<GR_KIND_CMC>(s, C, nu1, nu2, oc, fbar0, fshift0);
+                          ? coarse_in_lds<GR_KIND_HAMILTONIAN>(s, C, nu1, nu2, oc, fbar0, fshift0, stop)
+                          : coarse_in_lds<GR_KIND_CMC>(s, C, nu1, nu2, oc, fbar0, fshift0, stop);
     if (!done) GR_DISPATCH_KT(kind, double, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, fbar0, fshift0);
 }
 
@@ -1419,9 +1433,9 @@ void launch_coarse_vcycle_f32(int kind, hipStream_t s, const CoarseLevelsT<float
 {
     // FP32 arrays, the cycle in FP64 in LDS (the global-memory fallback, for
     // thresholds whose levels do not fit, computes in FP32)
-    const bool done = kind == K_LIN_POISSON ? coarse_in_lds<K_LIN_POISSON>(s, C, nu1, nu2, oc, zero, zero)
-                      : kind == K_LIN_HAM ? coarse_in_lds<K_LIN_HAM>(s, C, nu1, nu2, oc, zero, zero)
-                                          : coarse_in_lds<K_LIN_CMC>(s, C, nu1, nu2, oc, zero, zero);
+    const bool done = kind == K_LIN_POISSON ? coarse_in_lds<K_LIN_POISSON>(s, C, nu1, nu2, oc, zero, zero, nullptr)
+                      : kind == K_LIN_HAM ? coarse_in_lds<K_LIN_HAM>(s, C, nu1, nu2, oc, zero, zero, nullptr)
+                                          : coarse_in_lds<K_LIN_CMC>(s, C, nu1, nu2, oc, zero, zero, nullptr);
     if (!done) GR_DISPATCH_KT(kind, float, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, zero, zero);
 }
 
