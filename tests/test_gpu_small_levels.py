@@ -87,3 +87,24 @@ def test_cycles_queued_ahead_stop_alike(n, kind, monkeypatch):
     for g in (a, b):
         g.set_field("rhs", f)
         assert g.solve_equation(k, "Vx", allow=allow, rtol=1e-8)["status"] == grmg.ENAN
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n", [16, 24, 32])
+def test_concurrent_components_of_small_grids(n, precision, monkeypatch):
+    """The vector components on three streams equal the ones solved in turn, bit for bit."""
+    print(f"[gpu] concurrent components n={n} {precision}", flush=True)
+    monkeypatch.setenv("GRMG_CONCURRENT", "0")
+    a = grmg.Grid(n, **PRM)
+    monkeypatch.delenv("GRMG_CONCURRENT")
+    b = grmg.Grid(n, **PRM)
+    pos, u, mass = synth.zeldovich(n, 5, 0.5)
+    a.deposit_sources(pos, u, mass)
+    for name in ("s0", "sx", "sy", "sz", "sm"):
+        b.set_field(name, a.get_field(name))
+    for _ in range(2):
+        ra = a.solve_constraints(rtol=1e-9, precision=precision)
+        rb = b.solve_constraints(rtol=1e-9, precision=precision)
+        assert ra["cycles"] == rb["cycles"]
+        for f in range(10):
+            assert torch.equal(a.get_field(f), b.get_field(f)), f
