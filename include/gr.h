@@ -166,9 +166,9 @@ int gr_bind(gr_grid g, void *d_workspace, size_t bytes, void *hip_stream);
  * Psi currently held (the previous step's Psi^n, sec. 4.5), CIC-interpolated
  * to the particle.  Overwrites s0, s_i and the stress trace s_m
  * (s_m = gamma^ij s_ij += w m a^-2 chi^-4 u_i u_i/(W c h^3)).  Positions
- * outside [0,1) are wrapped.  Up to n^3 particles are deposited in cell order
- * (counting sort by cloud corner, then one sum per grid point, no
- * floating-point atomics); more particles fall back to an atomic scatter. */
+ * outside [0,1) are wrapped.  The particles are listed by the 8^3 tiles of
+ * points that their clouds reach and each tile is summed in LDS and stored
+ * once; the order of a point's terms is not fixed. */
 int gr_deposit_sources(gr_grid g, const double *d_pos, const double *d_u, double mass,
                        int64_t n_particles);
 

@@ -209,13 +209,10 @@ void launch_extrapolate(hipStream_t s, double *field, double *hist, double *alt,
 void launch_cubic_pass(hipStream_t s, const double *in, int nx, int ny, int nz, int dim, double *out);
 
 // ---- sources.hip launchers ----
-// cell-ordered deposit for up to `cap` particles; scratch of cic_sorted_bytes(N, cap)
-size_t cic_sorted_bytes(long N, long cap);
-void launch_cic_sorted(hipStream_t s, int n, double a, double c_tilde, const double *pos, const double *u,
-                       double mass, long np, const double *psi, void *scratch, double *s0, double *sx, double *sy,
-                       double *sz, double *sm);
+// CIC deposit of any number of particles; scratch of cic_bytes(n), 16-byte aligned
+size_t cic_bytes(int n);
 void launch_cic_deposit(hipStream_t s, int n, double a, double c_tilde, const double *pos, const double *u,
-                        double mass, long np, const double *psi, double *s0, double *sx, double *sy,
+                        double mass, long np, const double *psi, void *scratch, double *s0, double *sx, double *sy,
                         double *sz, double *sm);
 void launch_shift_scale(hipStream_t s, double *out, const double *in, long N, double scale,
                         const double *mean);

@@ -199,7 +199,7 @@ size_t layout(gr_grid g, char *base)
         for (int f = 0; f < 10; ++f) g->alt[f] = take(fb);
         for (int f = 0; f < 10; ++f) g->hist[f] = take(fb);
         g->gtmp = take(3 * fb / 4);
-        g->cic = take(cic_sorted_bytes(g->N(), g->N()));
+        g->cic = take(cic_bytes(g->n));
     }
     for (int l = 0; l < g->nlev; ++l) {
         Level &L = g->lev[l];
@@ -1208,15 +1208,8 @@ int gr_deposit_sources(gr_grid g, const double *d_pos, const double *d_u, double
     CHK(check_bound(g));
     if (np < 0 || (np > 0 && (!d_pos || !d_u))) return fail(GR_EINVAL, "bad particle arrays");
     if (!std::isfinite(mass)) return fail(GR_EINVAL, "mass not finite");
-    const long N = g->N();
-    if (np <= N) {
-        launch_cic_sorted(g->stream, g->n, g->prm.a, g->prm.c_tilde, d_pos, d_u, mass, (long)np, g->field[GR_PSI],
-                          g->cic, g->src[0], g->src[1], g->src[2], g->src[3], g->src[4]);
-    } else { // more particles than cells: scatter with floating-point atomics
-        for (int c = 0; c < 5; ++c) launch_fill(g->stream, g->src[c], N, 0.0);
-        launch_cic_deposit(g->stream, g->n, g->prm.a, g->prm.c_tilde, d_pos, d_u, mass, (long)np,
-                           g->field[GR_PSI], g->src[0], g->src[1], g->src[2], g->src[3], g->src[4]);
-    }
+    launch_cic_deposit(g->stream, g->n, g->prm.a, g->prm.c_tilde, d_pos, d_u, mass, (long)np, g->field[GR_PSI],
+                       g->cic, g->src[0], g->src[1], g->src[2], g->src[3], g->src[4]);
     LAUNCHCHK();
     return GR_OK;
 }

@@ -2,6 +2,8 @@
 // matter deposit, and the derived fields (paper sec. 4.1.2, 4.3, 4.5).
 #include "sources_ops.h"
 
+#include <algorithm>
+
 namespace grmg {
 
 namespace {
@@ -17,242 +19,291 @@ __device__ __forceinline__ int wrap_any(long i, int n)
 
 // ------------------------------------------------------------------- CIC
 
-// One thread per particle.  Cell-centred CIC: g = x/h - 1/2, i0 = floor(g),
-// t = g - i0, weights (1-t, t) on cells (i0, i0+1), periodic.  chi at the
-// particle from the CIC-interpolated Psi; W^2 = c^2 + a^-2 chi^-4 u.u.
-__global__ void __launch_bounds__(TPB) k_cic(int n, double a, double c, double kap, const double *__restrict__ pos,
-                                             const double *__restrict__ u, double mass, long np,
-                                             const double *__restrict__ psi, double *__restrict__ s0,
-                                             double *__restrict__ sx, double *__restrict__ sy,
-                                             double *__restrict__ sz, double *__restrict__ sm)
+// Cell-centred CIC: g = x/h - 1/2, i0 = floor(g), t = g - i0, weights (1-t, t) on cells
+// (i0, i0+1), periodic.  chi at the particle from the CIC-interpolated Psi;
+// W^2 = c^2 + a^-2 chi^-4 u.u.
+//
+// The grid points are cut into tiles of 8^3.  A particle is listed with every tile that
+// its cloud reaches (1.4 on average, at most 8): the entries are counted per tile, the
+// counts scanned, and the particles' numbers written to their tiles' lists.  A workgroup
+// then takes a tile, adds its particles' charges in LDS and stores every point once.  The
+// sums of a point are taken in no fixed order.
+//
+// Why: memory atomics run at about 26e9 a second on this card whatever they add (they
+// pass the eight L2s), so 40 a particle, or two a particle for a sort by cell, were what
+// the deposit cost; and a gather per point walks the lists of a dense lump alone.  LDS
+// takes both: the tile counters are first gathered per workgroup in LDS.  Against the
+// sort by cell and the gather per point, and above n^3 particles the scatter with memory
+// atomics (us): 128^3, 2.1e6 even particles 330 -> 170 (counting 25, lists 38, tiles 100);
+// 1.5e6, 40 % of them in lumps 500 -> 227; 256^3, 16.8e6 3210 -> 1280; 192^3, 8e6 12000
+// -> 750; 32^3, 3e4 60 -> 36.  Bound: the LDS adds, 17 clocks each with their conflicts.
+
+constexpr int DT = 8, DP = DT * DT * DT;         // tile side and points
+constexpr int DS = DT + 2;                       // Psi under the tile's clouds: one cell more on each side
+constexpr int BNT = 1024;                // threads of the binning kernels
+constexpr int BHASH = 8192, BPROBE = 32;         // hash table; entries that find no place count in memory
+
+__device__ __forceinline__ void cic_cells(const double *__restrict__ pos, long q, int n, int *i0, int *i1, double *t)
 {
-    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= np) return;
-    const double h = 1.0 / n;
-    int i0[3], i1[3];
-    double t[3];
     for (int d = 0; d < 3; ++d) {
         const double g = pos[3 * q + d] * n - 0.5;
         const double fl = floor(g);
         t[d] = g - fl;
-        // fl is finite for finite positions; wrap_any keeps any index in range
+        // any finite position wraps; the others count as cell 0
         const long il = isfinite(fl) ? (long)fl : 0;
-        i0[d] = wrap_any(il, n);
-        i1[d] = wrap_any(il + 1, n);
-    }
-    double psi_p = 0.0;
-    for (int cc = 0; cc < 8; ++cc) {
-        const int ox = cc & 1, oy = (cc >> 1) & 1, oz = cc >> 2;
-        const double w = (ox ? t[0] : 1.0 - t[0]) * (oy ? t[1] : 1.0 - t[1]) * (oz ? t[2] : 1.0 - t[2]);
-        psi_p += w * psi[lin(ox ? i1[0] : i0[0], oy ? i1[1] : i0[1], oz ? i1[2] : i0[2], n)];
-    }
-    const double chi = 1.0 - kap * psi_p;
-    const double chi2 = chi * chi;
-    const double ux = u[3 * q], uy = u[3 * q + 1], uz = u[3 * q + 2];
-    const double u2 = ux * ux + uy * uy + uz * uz;
-    const double g_uu = u2 / (a * a * chi2 * chi2); // gamma^ij u_i u_j
-    const double W = sqrt(c * c + g_uu);
-    const double vol = h * h * h;
-    const double q0 = mass * W / (c * vol);
-    const double qx = mass * ux / (c * vol);
-    const double qy = mass * uy / (c * vol);
-    const double qz = mass * uz / (c * vol);
-    const double qm = mass * g_uu / (W * c * vol); // stress trace gamma^ij s_ij
-    for (int cc = 0; cc < 8; ++cc) {
-        const int ox = cc & 1, oy = (cc >> 1) & 1, oz = cc >> 2;
-        const double w = (ox ? t[0] : 1.0 - t[0]) * (oy ? t[1] : 1.0 - t[1]) * (oz ? t[2] : 1.0 - t[2]);
-        const long p = lin(ox ? i1[0] : i0[0], oy ? i1[1] : i0[1], oz ? i1[2] : i0[2], n);
-        unsafeAtomicAdd(s0 + p, w * q0);
-        unsafeAtomicAdd(sx + p, w * qx);
-        unsafeAtomicAdd(sy + p, w * qy);
-        unsafeAtomicAdd(sz + p, w * qz);
-        unsafeAtomicAdd(sm + p, w * qm);
+        i0[d] = il >= 0 && il < n ? (int)il : wrap_any(il, n);
+        i1[d] = i0[d] + 1 == n ? 0 : i0[d] + 1;
     }
 }
 
-// Cell-ordered deposit (no floating-point atomics).  The lower-corner cell of
-// each particle's cloud is its key; particles are counted per key, the counts
-// are scanned into cell offsets, and each particle writes its weights and
-// charges (the per-particle part of the deposit above) to its cell's range.
-// Every grid point then sums, in a fixed loop order, the particles of the
-// 8 cells whose clouds reach it: the same sums as the scatter, one store per
-// point.
-
-struct CicItem {
-    double t[3];   // fractional offsets from the lower corner
-    double q[5];   // s0, sx, sy, sz, sm charges (before the cloud weights)
+// Tile coordinates of the lower and upper cells of a particle's cloud, 10 bits each
+// (n <= 1024); no particle: the lower ones are all ones.
+struct TileSpan {
+    unsigned lo, hi;
 };
-
-__device__ __forceinline__ int cic_key(const double *__restrict__ pos, long q, int n, int *i0, double *t)
+__device__ __forceinline__ TileSpan cic_span(const double *__restrict__ pos, long q, long np, int n)
 {
-    for (int d = 0; d < 3; ++d) {
-        const double g = pos[3 * q + d] * n - 0.5;
-        const double fl = floor(g);
-        t[d] = g - fl;
-        const long il = isfinite(fl) ? (long)fl : 0;
-        i0[d] = wrap_any(il, n);
-    }
-    return (int)lin(i0[0], i0[1], i0[2], n);
-}
-
-__global__ void __launch_bounds__(TPB) k_cic_count(int n, const double *__restrict__ pos, long np,
-                                                   int *__restrict__ key, int *__restrict__ cnt)
-{
-    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= np) return;
-    int i0[3];
-    double t[3];
-    const int k = cic_key(pos, q, n, i0, t);
-    key[q] = k;
-    atomicAdd(cnt + k, 1);
-}
-
-// Exclusive scan of cnt[0..N) into start[0..N], start[N] = total.  Three
-// passes: per-block scan of 2048 items (8 per thread), a one-block scan of
-// the block totals, and the block offsets added.
-constexpr int kScanItems = 8;
-constexpr int kScanTile = TPB * kScanItems;
-
-__device__ __forceinline__ int block_excl_scan(int v, int *total)
-{
-    __shared__ int wsum[TPB / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int x = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    int before = 0, all = 0;
-    for (int i = 0; i < TPB / 64; ++i) {
-        if (i < w) before += wsum[i];
-        all += wsum[i];
-    }
-    __syncthreads();
-    *total = all;
-    return before + x - v;
-}
-
-__global__ void __launch_bounds__(TPB) k_scan_tiles(const int *__restrict__ cnt, long N, int *__restrict__ start,
-                                                    int *__restrict__ tile_sum)
-{
-    const long base = (long)blockIdx.x * kScanTile + (long)threadIdx.x * kScanItems;
-    int v[kScanItems], sum = 0;
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-        v[i] = base + i < N ? cnt[base + i] : 0;
-        sum += v[i];
-    }
-    int total;
-    int run = block_excl_scan(sum, &total);
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-        if (base + i < N) start[base + i] = run;
-        run += v[i];
-    }
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
-}
-
-__global__ void __launch_bounds__(TPB) k_scan_tile_sums(int *__restrict__ tile_sum, int ntiles,
-                                                        int *__restrict__ start_end)
-{
-    int carry = 0;
-    for (int b0 = 0; b0 < ntiles; b0 += TPB) {
-        const int i = b0 + threadIdx.x;
-        const int v = i < ntiles ? tile_sum[i] : 0;
-        int total;
-        const int ex = block_excl_scan(v, &total);
-        if (i < ntiles) tile_sum[i] = carry + ex;
-        carry += total;
-    }
-    if (threadIdx.x == 0) *start_end = carry;
-}
-
-__global__ void __launch_bounds__(TPB) k_scan_add(int *__restrict__ start, long N, const int *__restrict__ tile_sum,
-                                                  int *__restrict__ cur)
-{
-    const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= N) return;
-    start[p] += tile_sum[p / kScanTile];
-    cur[p] = 0;
-}
-
-__global__ void __launch_bounds__(TPB) k_cic_place(int n, double a, double c, double kap,
-                                                   const double *__restrict__ pos, const double *__restrict__ u,
-                                                   double mass, long np, const double *__restrict__ psi,
-                                                   const int *__restrict__ key, const int *__restrict__ start,
-                                                   int *__restrict__ cur, CicItem *__restrict__ items)
-{
-    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= np) return;
-    const double h = 1.0 / n;
+    if (q >= np) return {~0u, ~0u};
     int i0[3], i1[3];
     double t[3];
-    cic_key(pos, q, n, i0, t);
-    for (int d = 0; d < 3; ++d) i1[d] = i0[d] + 1 == n ? 0 : i0[d] + 1;
-    double psi_p = 0.0;
-    for (int cc = 0; cc < 8; ++cc) {
-        const int ox = cc & 1, oy = (cc >> 1) & 1, oz = cc >> 2;
-        const double w = (ox ? t[0] : 1.0 - t[0]) * (oy ? t[1] : 1.0 - t[1]) * (oz ? t[2] : 1.0 - t[2]);
-        psi_p += w * psi[lin(ox ? i1[0] : i0[0], oy ? i1[1] : i0[1], oz ? i1[2] : i0[2], n)];
+    cic_cells(pos, q, n, i0, i1, t);
+    return {(unsigned)(i0[0] / DT) | (unsigned)(i0[1] / DT) << 10 | (unsigned)(i0[2] / DT) << 20,
+            (unsigned)(i1[0] / DT) | (unsigned)(i1[1] / DT) << 10 | (unsigned)(i1[2] / DT) << 20};
+}
+// f(tile) for every tile of the span, once
+template <typename F> __device__ __forceinline__ void for_tiles(const TileSpan s, int nt, F f)
+{
+    if (s.lo == ~0u) return;
+    const unsigned diff = s.lo ^ s.hi;
+    const int nx = diff & 1023u ? 2 : 1, ny = (diff >> 10) & 1023u ? 2 : 1, nz = diff >> 20 ? 2 : 1;
+    for (int c = 0; c < nx * ny * nz; ++c) {
+        const int cx = nx == 2 ? c & 1 : 0, r = nx == 2 ? c >> 1 : c, cy = ny == 2 ? r & 1 : 0, cz = ny == 2 ? r >> 1 : r;
+        const int x = (cx ? s.hi : s.lo) & 1023u, y = ((cy ? s.hi : s.lo) >> 10) & 1023u, z = (cz ? s.hi : s.lo) >> 20;
+        f((z * nt + y) * nt + x);
     }
-    const double chi = 1.0 - kap * psi_p;
-    const double chi2 = chi * chi;
-    const double ux = u[3 * q], uy = u[3 * q + 1], uz = u[3 * q + 2];
-    const double g_uu = (ux * ux + uy * uy + uz * uz) / (a * a * chi2 * chi2);
-    const double W = sqrt(c * c + g_uu);
-    const double vol = h * h * h;
-    const int k = key[q];
-    CicItem it;
-    it.t[0] = t[0];
-    it.t[1] = t[1];
-    it.t[2] = t[2];
-    it.q[0] = mass * W / (c * vol);
-    it.q[1] = mass * ux / (c * vol);
-    it.q[2] = mass * uy / (c * vol);
-    it.q[3] = mass * uz / (c * vol);
-    it.q[4] = mass * g_uu / (W * c * vol);
-    items[start[k] + atomicAdd(cur + k, 1)] = it;
 }
 
-// One thread per grid point (x fastest); the cells whose clouds reach point
-// (i, j, k) are (i - dx, j - dy, k - dz), d in {0, 1}; the point is the upper
-// corner (weight t) along a dimension where d = 1, the lower (1 - t) else.
-__global__ void __launch_bounds__(TPB) k_cic_gather(int n, const int *__restrict__ start,
-                                                    const CicItem *__restrict__ items, double *__restrict__ s0,
-                                                    double *__restrict__ sx, double *__restrict__ sy,
-                                                    double *__restrict__ sz, double *__restrict__ sm)
+// The slot of `key` in the workgroup's hash table, -1 if none is near; INSERT: taken if free.
+template <bool INSERT> __device__ __forceinline__ int table_slot(int *keys, int key)
 {
-    const long N = (long)n * n * n;
-    const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= N) return;
-    const int i = (int)(p % n), j = (int)((p / n) % n), k = (int)(p / ((long)n * n));
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int cc = 0; cc < 8; ++cc) {
-        const int dx = cc & 1, dy = (cc >> 1) & 1, dz = cc >> 2;
-        const long c = lin(dx ? (i == 0 ? n - 1 : i - 1) : i, dy ? (j == 0 ? n - 1 : j - 1) : j,
-                           dz ? (k == 0 ? n - 1 : k - 1) : k, n);
-        const int b = start[c], e = start[c + 1];
-        for (int s = b; s < e; ++s) {
-            const CicItem it = items[s];
-            const double w = (dx ? it.t[0] : 1.0 - it.t[0]) * (dy ? it.t[1] : 1.0 - it.t[1]) *
-                             (dz ? it.t[2] : 1.0 - it.t[2]);
+    unsigned s = ((unsigned)key * 2654435769u) >> 19; // 13 bits: BHASH
+    for (int p = 0; p < BPROBE; ++p, s = (s + 1) & (BHASH - 1)) {
+        int k = __hip_atomic_load(keys + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (INSERT && k == -1) k = atomicCAS(keys + s, -1, key) == -1 ? key : keys[s];
+        if (k == key) return (int)s;
+        if (!INSERT && k == -1) return -1;
+    }
+    return -1;
+}
+
+// Entries per tile (PLACE = false, at = counts) or the entries themselves (at = the
+// tiles' next free places): each tile that a workgroup's particles reach costs one
+// memory atomic, not each particle.  HASH = false: at most BSLOT tiles, a counter each.
+template <bool PLACE, bool HASH, int BSLOT, int BPT>
+__global__ void __launch_bounds__(BNT) k_cic_bin(int n, int nt, const double *__restrict__ pos, long np,
+                                                 unsigned *__restrict__ at, unsigned *__restrict__ list)
+{
+    __shared__ int keys[HASH ? BSLOT : 1];
+    __shared__ unsigned cnt[BSLOT];
+    const int slots = HASH ? BSLOT : nt * nt * nt;
+    const long q0 = (long)blockIdx.x * (BNT * BPT) + threadIdx.x;
+    TileSpan span[BPT];
 #pragma unroll
-            for (int f = 0; f < 5; ++f) acc[f] += w * it.q[f];
+    for (int i = 0; i < BPT; ++i) span[i] = cic_span(pos, q0 + i * BNT, np, n);
+    for (int i = threadIdx.x; i < slots; i += BNT) {
+        if (HASH) keys[i] = -1;
+        cnt[i] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < BPT; ++i)
+        for_tiles(span[i], nt, [&](int k) {
+            const int s = HASH ? table_slot<true>(keys, k) : k;
+            if (s >= 0) atomicAdd(cnt + s, 1u);
+            else if (!PLACE) atomicAdd(at + k, 1u);
+        });
+    __syncthreads();
+    for (int i = threadIdx.x; i < slots; i += BNT)
+        if (cnt[i]) {
+            const unsigned b = atomicAdd(at + (HASH ? keys[i] : i), cnt[i]);
+            if (PLACE) cnt[i] = b;
+        }
+    if constexpr (PLACE) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < BPT; ++i)
+            for_tiles(span[i], nt, [&](int k) {
+                const int s = HASH ? table_slot<false>(keys, k) : k;
+                list[s >= 0 ? atomicAdd(cnt + s, 1u) : atomicAdd(at + k, 1u)] = (unsigned)(q0 + i * BNT);
+            });
+    }
+}
+
+// Exclusive scan of cnt[0..nt3) into start[0..nt3] and next[0..nt3), one workgroup; and the
+// tiles with long lists, up to `room` of them (heavy[0]: how many), cnt: whether listed.
+// The arrays are 16-byte aligned.
+constexpr int SCNT = 1024, SCPT = 8;
+constexpr int DNT = 512;
+constexpr unsigned DLONG = 2 * DNT;
+__global__ void __launch_bounds__(SCNT) k_cic_scan(unsigned *__restrict__ cnt, int nt3, unsigned *__restrict__ start,
+                                                   unsigned *__restrict__ next, unsigned *__restrict__ heavy,
+                                                   unsigned room)
+{
+    __shared__ unsigned wsum[SCNT / 64];
+    __shared__ unsigned nheavy;
+    if (threadIdx.x == 0) nheavy = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    unsigned carry = 0;
+    for (int b0 = 0; b0 < nt3; b0 += SCNT * SCPT) {
+        const int base = b0 + threadIdx.x * SCPT;
+        const bool full = base + SCPT <= nt3;
+        unsigned v[SCPT], sum = 0;
+        if (full) {
+#pragma unroll
+            for (int i = 0; i < SCPT; i += 4) *reinterpret_cast<uint4 *>(v + i) = *reinterpret_cast<const uint4 *>(cnt + base + i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < SCPT; ++i) v[i] = base + i < nt3 ? cnt[base + i] : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < SCPT; ++i) sum += v[i];
+        unsigned x = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wsum[w] = x;
+        __syncthreads();
+        unsigned run = carry + x - sum, all = 0;
+        for (int i = 0; i < SCNT / 64; ++i) {
+            if (i < w) run += wsum[i];
+            all += wsum[i];
+        }
+        carry += all;
+        unsigned out[SCPT], mark[SCPT];
+#pragma unroll
+        for (int i = 0; i < SCPT; ++i) {
+            unsigned at = room;
+            if (v[i] > DLONG) at = atomicAdd(&nheavy, 1u);
+            if (at < room) heavy[1 + at] = (unsigned)(base + i);
+            mark[i] = at < room;
+            out[i] = run;
+            run += v[i];
+        }
+        if (full) {
+#pragma unroll
+            for (int i = 0; i < SCPT; i += 4) {
+                *reinterpret_cast<uint4 *>(start + base + i) = *reinterpret_cast<const uint4 *>(out + i);
+                *reinterpret_cast<uint4 *>(next + base + i) = *reinterpret_cast<const uint4 *>(out + i);
+                *reinterpret_cast<uint4 *>(cnt + base + i) = *reinterpret_cast<const uint4 *>(mark + i);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < SCPT; ++i)
+                if (base + i < nt3) {
+                    start[base + i] = next[base + i] = out[i];
+                    cnt[base + i] = mark[i];
+                }
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        start[nt3] = carry;
+        heavy[0] = nheavy < room ? nheavy : room;
+    }
+}
+
+// One tile: the sources of its points from the particles of its list (added to what is
+// there: ADD).  Bound by the LDS adds (40 a particle); the first `room` workgroups take
+// the dense lumps, which would otherwise be the tail.
+template <bool ADD>
+__global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, double c, double kap,
+                                                  const double *__restrict__ pos, const double *__restrict__ u,
+                                                  double mass, const double *__restrict__ psi,
+                                                  const unsigned *__restrict__ start, const unsigned *__restrict__ list,
+                                                  const unsigned *__restrict__ listed,
+                                                  const unsigned *__restrict__ heavy, int room, double *__restrict__ s0, double *__restrict__ sx,
+                                                  double *__restrict__ sy, double *__restrict__ sz,
+                                                  double *__restrict__ sm)
+{
+    __shared__ double acc[5][DP];
+    __shared__ double ps[DS * DS * DS];
+    int b = blockIdx.x;
+    if (b < room) {
+        if ((unsigned)b >= heavy[0]) return;
+        b = (int)heavy[1 + b];
+    } else {
+        const int G = gridDim.x - room;
+        b -= room;
+        if ((G & 7) == 0) b = (b & 7) * (G >> 3) + (b >> 3); // runs of tiles per XCD: neighbours share particles
+        if (listed[b]) return;
+    }
+    const int T[3] = {b % nt, (b / nt) % nt, b / (nt * nt)};
+    const unsigned first = start[b], last = start[b + 1];
+    for (int i = threadIdx.x; i < 5 * DP; i += DNT) (&acc[0][0])[i] = 0.0;
+    for (int i = threadIdx.x; i < DS * DS * DS; i += DNT) {
+        int x[3] = {i % DS, (i / DS) % DS, i / (DS * DS)};
+        for (int d = 0; d < 3; ++d) {
+            x[d] += DT * T[d] - 1;
+            if (x[d] < 0) x[d] += n;
+            else if (x[d] >= n) x[d] %= n;
+        }
+        ps[i] = psi[lin(x[0], x[1], x[2], n)];
+    }
+    __syncthreads();
+    const double h = 1.0 / n, vol = h * h * h, qs = mass / (c * vol);
+    for (unsigned e = first + threadIdx.x; e < last; e += DNT) {
+        const long q = list[e];
+        int i0[3], i1[3], at[3];
+        double t[3];
+        cic_cells(pos, q, n, i0, i1, t);
+        const double ux = u[3 * q], uy = u[3 * q + 1], uz = u[3 * q + 2];
+        bool in[3][2];
+        int p[3][2];
+        for (int d = 0; d < 3; ++d) {
+            in[d][0] = i0[d] / DT == T[d];
+            in[d][1] = i1[d] / DT == T[d];
+            p[d][0] = i0[d] % DT;
+            p[d][1] = i1[d] % DT;
+            at[d] = in[d][0] ? p[d][0] + 1 : 0;
+        }
+        double psi_p = 0.0;
+        for (int cc = 0; cc < 8; ++cc) {
+            const int ox = cc & 1, oy = (cc >> 1) & 1, oz = cc >> 2;
+            const double w = (ox ? t[0] : 1.0 - t[0]) * (oy ? t[1] : 1.0 - t[1]) * (oz ? t[2] : 1.0 - t[2]);
+            psi_p += w * ps[((at[2] + oz) * DS + at[1] + oy) * DS + at[0] + ox];
+        }
+        const double chi = 1.0 - kap * psi_p;
+        const double chi2 = chi * chi;
+        const double g_uu = (ux * ux + uy * uy + uz * uz) / (a * a * chi2 * chi2); // gamma^ij u_i u_j
+        const double W = sqrt(c * c + g_uu);
+        const double Q[5] = {qs * W, qs * ux, qs * uy, qs * uz, qs * (g_uu / W)}; // the last: stress trace gamma^ij s_ij
+#pragma unroll
+        for (int cc = 0; cc < 8; ++cc) {
+            const int ox = cc & 1, oy = (cc >> 1) & 1, oz = cc >> 2;
+            if (!(in[0][ox] && in[1][oy] && in[2][oz])) continue;
+            const double w = (ox ? t[0] : 1.0 - t[0]) * (oy ? t[1] : 1.0 - t[1]) * (oz ? t[2] : 1.0 - t[2]);
+            const int r = (p[2][oz] * DT + p[1][oy]) * DT + p[0][ox];
+#pragma unroll
+            for (int f = 0; f < 5; ++f) unsafeAtomicAdd(&acc[f][r], w * Q[f]);
         }
     }
-    s0[p] = acc[0];
-    sx[p] = acc[1];
-    sy[p] = acc[2];
-    sz[p] = acc[3];
-    sm[p] = acc[4];
+    __syncthreads();
+    double *const out[5] = {s0, sx, sy, sz, sm};
+    for (int r = threadIdx.x; r < DP; r += DNT) {
+        const int x = DT * T[0] + r % DT, y = DT * T[1] + (r / DT) % DT, z = DT * T[2] + r / (DT * DT);
+        if (x >= n || y >= n || z >= n) continue;
+        const long g = lin(x, y, z, n);
+#pragma unroll
+        for (int f = 0; f < 5; ++f) out[f][g] = ADD ? out[f][g] + acc[f][r] : acc[f][r];
+    }
 }
 
-__global__ void k_fill_i32(int *__restrict__ x, long N, int v)
+__global__ void k_fill_u32(unsigned *__restrict__ x, long N)
 {
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < N) x[p] = v;
+    if (p < N) x[p] = 0;
 }
 
 // ----------------------------------------------------------------- builders
@@ -353,48 +404,64 @@ inline unsigned blocks_for(long count) { return (unsigned)((count + TPB - 1) / T
 
 } // namespace
 
+// Particles that one pass takes: as many as the lists hold in the worst case (every cloud
+// over eight tiles).  Twice the cells, so that a usual run needs one pass.
+static long cic_pass(long N) { return std::min(std::max(2 * N, 1L << 16), 1L << 28); }
+static long cic_tiles(int n)
+{
+    const long nt = (n + DT - 1) / DT;
+    return nt * nt * nt;
+}
+// tiles with long lists that are taken first
+static unsigned cic_room(long nt3) { return (unsigned)std::min(1 + nt3 / 8, 4096L); }
+
+size_t cic_bytes(int n)
+{
+    return sizeof(unsigned) * (size_t)(8 * cic_pass((long)n * n * n) + 3 * (cic_tiles(n) + 4) + 1 + cic_room(cic_tiles(n)));
+}
+
+// A table with a counter per tile up to 32768 of them (256^3, 128 KB of LDS), a hash table
+// beyond.  8192 particles a workgroup from 2^20 on, so that few workgroups count into the
+// same tile, 2048 below, so that the chip has enough workgroups.
+template <bool PLACE>
+static void cic_bin(hipStream_t s, int n, int nt, const double *pos, long np, unsigned *at, unsigned *list)
+{
+    if (np <= 0) return;
+    const long nt3 = cic_tiles(n);
+    auto run = [&](auto k, int per_thread) {
+        k<<<(unsigned)((np + BNT * per_thread - 1) / (BNT * per_thread)), BNT, 0, s>>>(n, nt, pos, np, at, list);
+    };
+    if (nt3 <= 8192 && np < (1L << 20)) run(k_cic_bin<PLACE, false, 8192, 2>, 2);
+    else if (nt3 <= 8192) run(k_cic_bin<PLACE, false, 8192, 8>, 8);
+    else if (nt3 <= 32768) run(k_cic_bin<PLACE, false, 32768, 8>, 8);
+    else run(k_cic_bin<PLACE, true, BHASH, 8>, 8);
+}
+
 void launch_cic_deposit(hipStream_t s, int n, double a, double c_tilde, const double *pos, const double *u,
-                        double mass, long np, const double *psi, double *s0, double *sx, double *sy, double *sz,
-                        double *sm)
+                        double mass, long np, const double *psi, void *scratch, double *s0, double *sx, double *sy,
+                        double *sz, double *sm)
 {
     const double kap = 1.0 / (2.0 * a * a * c_tilde * c_tilde);
-    if (np > 0)
-        k_cic<<<blocks_for(np), TPB, 0, s>>>(n, a, c_tilde, kap, pos, u, mass, np, psi, s0, sx, sy, sz, sm);
-}
-
-size_t cic_sorted_bytes(long N, long cap)
-{
-    const long ntiles = (N + kScanTile - 1) / kScanTile;
-    return sizeof(int) * (size_t)(2 * N + 1 + cap + ntiles) + sizeof(CicItem) * (size_t)cap + 8 * 256;
-}
-
-void launch_cic_sorted(hipStream_t s, int n, double a, double c_tilde, const double *pos, const double *u,
-                       double mass, long np, const double *psi, void *scratch, double *s0, double *sx, double *sy,
-                       double *sz, double *sm)
-{
-    const double kap = 1.0 / (2.0 * a * a * c_tilde * c_tilde);
-    const long N = (long)n * n * n;
-    const long ntiles = (N + kScanTile - 1) / kScanTile;
-    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    char *b = static_cast<char *>(scratch);
-    CicItem *items = reinterpret_cast<CicItem *>(b);
-    b += up(sizeof(CicItem) * (size_t)(np > 0 ? np : 1));
-    int *start = reinterpret_cast<int *>(b); // N + 1
-    b += up(sizeof(int) * (size_t)(N + 1));
-    int *cnt = reinterpret_cast<int *>(b); // N, reused as the per-cell cursor
-    b += up(sizeof(int) * (size_t)N);
-    int *key = reinterpret_cast<int *>(b); // np
-    b += up(sizeof(int) * (size_t)(np > 0 ? np : 1));
-    int *tsum = reinterpret_cast<int *>(b); // ntiles
-    k_fill_i32<<<blocks_for(N), TPB, 0, s>>>(cnt, N, 0);
-    if (np > 0) k_cic_count<<<blocks_for(np), TPB, 0, s>>>(n, pos, np, key, cnt);
-    k_scan_tiles<<<(unsigned)ntiles, TPB, 0, s>>>(cnt, N, start, tsum);
-    k_scan_tile_sums<<<1, TPB, 0, s>>>(tsum, (int)ntiles, start + N);
-    k_scan_add<<<blocks_for(N), TPB, 0, s>>>(start, N, tsum, cnt);
-    if (np > 0)
-        k_cic_place<<<blocks_for(np), TPB, 0, s>>>(n, a, c_tilde, kap, pos, u, mass, np, psi, key, start, cnt,
-                                                    items);
-    k_cic_gather<<<blocks_for(N), TPB, 0, s>>>(n, start, items, s0, sx, sy, sz, sm);
+    const int nt = (n + DT - 1) / DT;
+    const long nt3 = cic_tiles(n), pass = cic_pass((long)n * n * n);
+    const long row = (nt3 + 4) / 4 * 4; // nt3 + 1 at least
+    const unsigned room = cic_room(nt3);
+    unsigned *list = static_cast<unsigned *>(scratch), *cnt = list + 8 * pass, *next = cnt + row, *start = next + row,
+             *heavy = start + row;
+    for (long q = 0; q == 0 || q < np; q += pass) {
+        const long m = std::min(pass, np - q);
+        const double *x = m > 0 ? pos + 3 * q : nullptr, *v = m > 0 ? u + 3 * q : nullptr;
+        k_fill_u32<<<blocks_for(nt3), TPB, 0, s>>>(cnt, nt3);
+        cic_bin<false>(s, n, nt, x, m, cnt, nullptr);
+        k_cic_scan<<<1, SCNT, 0, s>>>(cnt, (int)nt3, start, next, heavy, room);
+        cic_bin<true>(s, n, nt, x, m, next, list);
+        if (q == 0)
+            k_cic_tile<false><<<(unsigned)nt3 + room, DNT, 0, s>>>(n, nt, a, c_tilde, kap, x, v, mass, psi, start, list, cnt, heavy, (int)room, s0, sx,
+                                                            sy, sz, sm);
+        else
+            k_cic_tile<true><<<(unsigned)nt3 + room, DNT, 0, s>>>(n, nt, a, c_tilde, kap, x, v, mass, psi, start, list, cnt, heavy, (int)room, s0, sx,
+                                                           sy, sz, sm);
+    }
 }
 
 void launch_shift_scale(hipStream_t s, double *out, const double *in, long N, double scale, const double *mean)

@@ -1,0 +1,56 @@
+"""CIC deposit by tiles of 8^3 points: ragged and tiny grids, clouds over tile edges and
+corners, the workgroup tables' overflow, and counts of more than one pass, against the
+oracle (relative to the largest value; sums of at most a few thousand terms: 1e-12)."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1905_08890_amd import grmg, synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+PRM = dict(a=0.7, omega_m=synth.OMEGA_M, c_tilde=synth.C_TILDE)
+
+
+def _check(n, pos, seed):
+    rng = np.random.default_rng(seed)
+    u = 1e-2 * rng.standard_normal(pos.shape)
+    psi = 10.0 * rng.standard_normal((n, n, n))
+    mass = 1.0 / max(1, len(pos))
+    g = grmg.Grid(n, **PRM)
+    g.set_field("Psi", psi)
+    ref = O.cic_deposit(n, pos, u, mass, psi=psi, prm=O.params(**PRM))
+    for _ in range(2):
+        g.deposit_sources(pos, u, mass)
+        for name, r in zip(("s0", "sx", "sy", "sz", "sm"), ref):
+            d = np.abs(g.get_field(name).cpu().numpy() - r).max()
+            assert d <= 1e-12 * np.abs(r).max(), (name, d)
+
+
+@pytest.mark.parametrize("n,count", [(2, 700), (4, 3), (8, 1), (8, 600), (10, 999), (12, 5000), (20, 4097), (24, 30000),
+                                     (16, 150000), (2, 70000)])
+def test_counts_and_sides(n, count):
+    """Sides that 8 divides and does not; the last two counts need several passes."""
+    print(f"[gpu] deposit n={n} count={count}", flush=True)
+    _check(n, np.random.default_rng(n + count).uniform(-0.5, 1.5, (count, 3)), n)
+
+
+@pytest.mark.parametrize("n", [8, 16, 40, 160])
+def test_clouds_over_tile_corners(n):
+    """Every cloud over eight tiles where the grid has them; at 160^3 (8000 tiles, corners in
+    random order) a workgroup reaches more tiles than its table holds."""
+    print(f"[gpu] deposit corners n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    corner = 8 * rng.integers(0, n // 8, (20000, 3))
+    _check(n, (corner + rng.uniform(-0.45, 0.45, corner.shape)) / n, n)
+
+
+def test_one_dense_lump():
+    """Most particles in one tile."""
+    n = 32
+    print("[gpu] deposit lump", flush=True)
+    rng = np.random.default_rng(3)
+    pos = rng.uniform(0, 1, (8000, 3))
+    pos[:6000] = 0.3 + 0.01 * rng.standard_normal((6000, 3))
+    _check(n, pos, 3)
