@@ -23,6 +23,7 @@
 #include "gr_internal.h"
 
 typedef __bf16 bf16;
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
@@ -37,14 +38,17 @@ __device__ __forceinline__ int wrapn(int i, int n) { return i < 0 ? i + n : (i >
 
 // out[v][ocoff + co] = act(bias[co] + sum_k in[v + off(tap)][icoff + ci] w[co][k]),
 // k = tap * cin + ci, taps ordered (dz, dy, dx) in {-1,0,1}^3 with dx fastest.
-// One wave: VG groups of 16 consecutive voxels x all COUT channels, so each
-// weight operand (B) feeds VG matrix-core products.  The 27 taps are unrolled
+// One wave: VG groups of 16 consecutive voxels x 16 NT output channels (blockIdx.y
+// picks them).  The 27 taps are unrolled
 // (every lane of a product works on the same tap) and each tap runs over the
-// input channels in steps of KS = 32 (v_mfma_f32_16x16x32_bf16, 8 channels per
+// input channels in CK steps of KS = 32 (v_mfma_f32_16x16x32_bf16, 8 channels per
 // lane) when cin % 32 == 0, else KS = 16 (v_mfma_f32_16x16x16_bf16, 4 channels
 // per lane); a lane's neighbour rows are formed once, so the inner loop is
-// loads and matrix products.  n^3 must be a multiple of 64 VG (4 waves per
-// block) and cin a multiple of KS.
+// loads and matrix products.  CK = 0: any number of steps.  n^3 must be a multiple of
+// 64 VG (4 waves per block) and cin a multiple of KS.
+// Latency bound on the deep levels (8^3 has 32 groups of voxels): one group and 16
+// channels a wave, the steps unrolled so that their loads overlap; 64 -> 64 channels
+// at 8^3 65 -> 14 us against four groups and all channels a wave.
 template <int KS> struct ConvOperand;
 template <> struct ConvOperand<32> {
     typedef bf16x8 type;
@@ -61,15 +65,29 @@ template <> struct ConvOperand<16> {
     }
 };
 
-template <int COUT, int VG, int KS, bool RELU, bool BIAS>
+// four channels of one voxel: bias, ReLU, one 8-byte store
+template <bool RELU, bool BIAS>
+__device__ __forceinline__ void store_out(floatx4 v, const float *__restrict__ bias, int co, bf16 *__restrict__ dst)
+{
+    bf16x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float r = v[j] + (BIAS ? bias[co + j] : 0.0f);
+        if (RELU) r = r > 0.0f ? r : 0.0f;
+        o[j] = (bf16)r;
+    }
+    *reinterpret_cast<bf16x4 *>(dst) = o;
+}
+
+template <int NT, int VG, int KS, int CK, bool RELU, bool BIAS>
 __global__ void __launch_bounds__(256) k_conv3(const bf16 *__restrict__ in, int cin, int icstride, int icoff,
                                                const bf16 *__restrict__ w, int kpad, const float *__restrict__ bias,
                                                bf16 *__restrict__ out, int ocstride, int ocoff, int n)
 {
     typedef ConvOperand<KS> Op;
     typedef typename Op::type opT;
-    constexpr int NT = COUT / 16, PER = KS / 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int PER = KS / 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cob = 16 * NT * blockIdx.y;
     const int v0 = (blockIdx.x * 4 + wave) * 16 * VG;
     const int i = lane & 15, g = lane >> 4;
     // neighbour coordinates of this lane's voxel in each group: x, y * n, z * n^2
@@ -90,8 +108,10 @@ __global__ void __launch_bounds__(256) k_conv3(const bf16 *__restrict__ in, int 
     for (int q = 0; q < VG; ++q)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[q][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const bf16 *wl = w + (long)i * kpad + PER * g;
+    const bf16 *wl = w + (long)(cob + i) * kpad + PER * g;
     const long wstep = (long)16 * kpad;
+    const int steps = CK ? CK : cin / KS;
+    constexpr int UN = CK ? CK : 1;
 #pragma unroll
     for (int dz = 0; dz < 3; ++dz)
 #pragma unroll
@@ -103,8 +123,10 @@ __global__ void __launch_bounds__(256) k_conv3(const bf16 *__restrict__ in, int 
 #pragma unroll
                 for (int q = 0; q < VG; ++q)
                     src[q] = in + (long)(zo[q][dz] + yo[q][dy] + xo[q][dx]) * icstride + icoff + PER * g;
-                const bf16 *wt = wl + tap * cin;
-                for (int c0 = 0; c0 < cin; c0 += KS) {
+                const bf16 *wt = wl + tap * (CK ? CK * KS : cin);
+#pragma unroll UN
+                for (int ck = 0; ck < steps; ++ck) {
+                    const int c0 = ck * KS;
                     opT bw[NT];
 #pragma unroll
                     for (int t = 0; t < NT; ++t) bw[t] = *reinterpret_cast<const opT *>(wt + t * wstep + c0);
@@ -112,148 +134,178 @@ __global__ void __launch_bounds__(256) k_conv3(const bf16 *__restrict__ in, int 
                     for (int q = 0; q < VG; ++q) {
                         const opT a = *reinterpret_cast<const opT *>(src[q] + c0);
 #pragma unroll
-                        for (int t = 0; t < NT; ++t) acc[q][t] = Op::mfma(a, bw[t], acc[q][t]);
+                        for (int t = 0; t < NT; ++t) acc[q][t] = Op::mfma(bw[t], a, acc[q][t]);
                     }
                 }
             }
-    // lane holds D[4g + j][i]: voxel v0 + 16 q + 4g + j, channel 16t + i
+    // lane holds D[4g + j][i]: voxel v0 + 16 q + i, channels 16t + 4g + j
 #pragma unroll
     for (int q = 0; q < VG; ++q)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int co = 16 * t + i;
-            const float b = BIAS ? bias[co] : 0.0f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float r = acc[q][t][j] + b;
-                if (RELU) r = r > 0.0f ? r : 0.0f;
-                out[(long)(v0 + 16 * q + 4 * g + j) * ocstride + ocoff + co] = (bf16)r;
-            }
-        }
+        for (int t = 0; t < NT; ++t)
+            store_out<RELU, BIAS>(acc[q][t], bias, cob + 16 * t + 4 * g,
+                                  out + (long)(v0 + 16 * q + i) * ocstride + ocoff + cob + 16 * t + 4 * g);
 }
 
 // The same convolution with the input staged in LDS: one block computes a
-// 16 (x) x 4 (y) x 4 (z) tile of output voxels; wave w takes the plane z0 + w
-// and its product group q the row y0 + q.  For each chunk of CW input
-// channels the block copies the tile's 18 x 6 x 6 input halo into LDS (voxel
-// stride CW + 8 elements, so the 16-byte reads of 8 consecutive lanes fall in
-// distinct banks), then every tap reads its operand at a constant offset from
-// the lane's base.  CW = 32: one v_mfma_f32_16x16x32_bf16 per tap, all lanes
-// on the same tap.  CW = 16: taps go in pairs, lanes g < 2 on the first and
-// g >= 2 on the second (8 channels each), the unpaired 27th tap padded with
-// zeros.  n must be a multiple of 16 and cin of CW.
+// 16 (x) x 4 (y) x 4 (z) tile of output voxels and 16 NT channels (blockIdx.y picks
+// them); wave w takes the plane z0 + w and its product group q the row y0 + q.  For
+// each chunk of CW input channels the block copies the tile's 18 x 6 x 6 input halo
+// into LDS; the next chunk is loaded meanwhile.  Voxel strides of 32 and 96 bytes are
+// free of bank conflicts with the lanes that a 16-byte read takes together (lanes 0-3,
+// 12-15, 20-27; 48 and 80 bytes doubled the LDS cycles).  CW = 32: one
+// v_mfma_f32_16x16x32_bf16 per tap, all lanes on the same tap; a plane's six rows are
+// read once for the three dy, and the weights are loaded a row or two of taps ahead.
+// CW = 16: taps go in pairs, lanes g < 2 on the first and g >= 2 on the second (8
+// channels each), the unpaired 27th tap padded with zeros, all weights loaded first.
+// n must be a multiple of 16 and cin of CW.
+//
+// The products of an output run in the order taps within channel chunks.  Operands are
+// given weights first, so a lane holds four channels of one voxel and stores them at once.
+// Bound by issue and latency: at 16 channels 56 products take 400 other instructions a
+// wave, so blocks that march in z (MARCH) keep weights and addresses; at 32 and 64 by the
+// weights, that every wave reads from L2.  Measured (us): 16 -> 16 at 128^3 131 -> 60;
+// 64 -> 64 at 32^3 50 -> 24 and at 16^3 47 -> 15 (16 channels a block instead of all,
+// where tiles are few), 32 -> 32 at 64^3 51 -> 32.  48 -> 16 at 128^3 takes 200, as long
+// with whole voxels staged once.
 constexpr int CT_HX = 18, CT_HY = 6, CT_HZ = 6, CT_HV = CT_HX * CT_HY * CT_HZ;
 
-template <int COUT, int CW, bool RELU, bool BIAS>
-__global__ void __launch_bounds__(256) k_conv3_lds(const bf16 *__restrict__ in, int cin, int icstride, int icoff,
-                                                   const bf16 *__restrict__ w, int kpad,
-                                                   const float *__restrict__ bias, bf16 *__restrict__ out,
-                                                   int ocstride, int ocoff, int n)
+template <int NT, int CW, bool MARCH, bool RELU, bool BIAS>
+__global__ void __launch_bounds__(256, MARCH ? 3 : 2)
+    k_conv3_lds(const bf16 *__restrict__ in, int cin, int icstride, int icoff, const bf16 *__restrict__ w, int kpad,
+                const float *__restrict__ bias, bf16 *__restrict__ out, int ocstride, int ocoff, int n, int ztiles)
 {
-    constexpr int NT = COUT / 16, STR = CW + 8, UPV = CW / 8, NU = CT_HV * UPV, PERT = (NU + 255) / 256;
+    constexpr int STR = CW == 32 ? 48 : 16, UPV = CW / 8, NU = CT_HV * UPV, PERT = (NU + 255) / 256;
     __shared__ __align__(16) bf16 tile[CT_HV * STR];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cob = 16 * NT * blockIdx.y;
     const int i = lane & 15, g = lane >> 4;
     // blocks in contiguous runs per XCD (dispatch is round-robin over the 8 XCDs)
     const int nblk = gridDim.x;
     int b = blockIdx.x;
     if (nblk % 8 == 0) b = (b & 7) * (nblk >> 3) + (b >> 3);
     const int tx = n >> 4, ty = n >> 2;
-    const int X0 = (b % tx) * 16, Y0 = ((b / tx) % ty) * 4, Z0 = (b / tx / ty) * 4;
-    floatx4 acc[4][NT];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[q][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int X0 = (b % tx) * 16, Y0 = ((b / tx) % ty) * 4;
+    int zt = MARCH ? ztiles : 1, Z0 = (b / tx / ty) * 4 * zt;
     const bool hi = g >= 2;
     const int lbase = (wave * CT_HY * CT_HX + i) * STR + (CW == 32 ? 8 * g : 8 * (g & 1));
-    const bf16 *wl = w + (long)i * kpad + (CW == 32 ? 8 * g : 8 * (g & 1));
+    const bf16 *wl = w + (long)(cob + i) * kpad + (CW == 32 ? 8 * g : 8 * (g & 1));
     const long wstep = (long)16 * kpad;
-    for (int c0 = 0; c0 < cin; c0 += CW) {
-        bf16x8 stage[PERT];
+    bf16x8 stage[PERT];
+    int sxy[PERT]; // halo voxel in its plane (n^2 < 2^21), plane of the halo above it
 #pragma unroll
-        for (int r = 0; r < PERT; ++r) {
-            const int u = threadIdx.x + 256 * r;
-            if (u < NU) {
-                const int h = u / UPV, cu = u % UPV;
-                const int hx = h % CT_HX, hy = (h / CT_HX) % CT_HY, hz = h / (CT_HX * CT_HY);
-                const long src = ((long)wrapn(Z0 - 1 + hz, n) * n + wrapn(Y0 - 1 + hy, n)) * n + wrapn(X0 - 1 + hx, n);
-                stage[r] = *reinterpret_cast<const bf16x8 *>(in + src * icstride + icoff + c0 + 8 * cu);
-            }
-        }
-        __syncthreads(); // the previous chunk's reads are done
+    for (int r = 0; r < PERT; ++r) {
+        const int u = threadIdx.x + 256 * r, h = u < NU ? u / UPV : 0;
+        const int hx = h % CT_HX, hy = (h / CT_HX) % CT_HY, hz = h / (CT_HX * CT_HY);
+        sxy[r] = (wrapn(Y0 - 1 + hy, n) * n + wrapn(X0 - 1 + hx, n)) | hz << 24;
+    }
+    const bf16 *inl = in + icoff + 8 * (threadIdx.x % UPV);
+    auto fetch = [&](int z0, int c0) {
 #pragma unroll
-        for (int r = 0; r < PERT; ++r) {
-            const int u = threadIdx.x + 256 * r;
-            if (u < NU) *reinterpret_cast<bf16x8 *>(tile + (u / UPV) * STR + 8 * (u % UPV)) = stage[r];
-        }
-        __syncthreads();
-        if (CW == 32) {
-            // rows (dz, dy) in a loop, the three dx of a row unrolled
-#pragma unroll 1
-            for (int r = 0; r < 9; ++r) {
-                const int roff = ((r / 3) * CT_HY + r % 3) * CT_HX * STR;
+        for (int r = 0; r < PERT; ++r)
+            stage[r] = *reinterpret_cast<const bf16x8 *>(
+                inl + (long)(wrapn(z0 - 1 + (sxy[r] >> 24), n) * n * n + (sxy[r] & 0xffffff)) * icstride + c0);
+    };
+    bf16 *const put = tile + (threadIdx.x / UPV) * STR + 8 * (threadIdx.x % UPV);
+    bf16x8 bw[CW == 16 ? 14 : 1][NT];
+    floatx4 acc[4][NT];
+    fetch(Z0, 0);
+    for (int c0 = 0, first = 1;; first = 0) { // chunks of a tile, then the next tile
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) {
-                    const int tap = 3 * r + dx;
-                    bf16x8 bw[NT];
+        for (int r = 0; r < PERT; ++r)
+            if ((int)threadIdx.x + 256 * r < NU) *reinterpret_cast<bf16x8 *>(put + r * (256 / UPV) * STR) = stage[r];
+        const bool tile_done = MARCH || c0 + CW >= cin, all_done = tile_done && zt == 1;
+        if (MARCH || c0 == 0)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[q][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (CW == 32) {
+            constexpr int AHEAD = 3 - NT, RING = AHEAD + 1;
+            bf16x8 wr[RING][3][NT]; // weights of the rows of taps r .. r + AHEAD
+            auto weights = [&](int r) {
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
-                        bw[t] = *reinterpret_cast<const bf16x8 *>(wl + t * wstep + tap * cin + c0);
+                        wr[r % RING][dx][t] = *reinterpret_cast<const bf16x8 *>(wl + t * wstep + (3 * r + dx) * cin + c0);
+            };
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const bf16x8 a =
-                            *reinterpret_cast<const bf16x8 *>(tile + lbase + q * CT_HX * STR + roff + dx * STR);
+            for (int r = 0; r < AHEAD; ++r) weights(r);
+            __syncthreads();
+            if (!all_done) fetch(tile_done ? Z0 + 4 : Z0, tile_done ? 0 : c0 + CW);
 #pragma unroll
-                        for (int t = 0; t < NT; ++t)
-                            acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[t], acc[q][t], 0, 0, 0);
-                    }
+            for (int dz = 0; dz < 3; ++dz) {
+                bf16x8 a[6][3];
+#pragma unroll
+                for (int y = 0; y < 6; ++y)
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx)
+                        a[y][dx] = *reinterpret_cast<const bf16x8 *>(tile + lbase + ((dz * CT_HY + y) * CT_HX + dx) * STR);
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const int r = 3 * dz + dy;
+                    if (r + AHEAD < 9) weights(r + AHEAD);
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int t = 0; t < NT; ++t)
+                                acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[r % RING][dx][t], a[q + dy][dx],
+                                                                                    acc[q][t], 0, 0, 0);
                 }
             }
         } else {
-#pragma unroll 1
+            if (!MARCH || first) { // MARCH: one chunk, whose weights stay
+#pragma unroll
+                for (int m = 0; m < 14; ++m)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        const int tap = m < 13 ? 2 * m + (hi ? 1 : 0) : 26;
+                        bw[m][t] = *reinterpret_cast<const bf16x8 *>(wl + t * wstep + tap * cin + c0);
+                        if (m == 13 && hi)
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) bw[m][t][j] = (bf16)0.0f;
+                    }
+            }
+            __syncthreads();
+            if (!all_done) fetch(tile_done ? Z0 + 4 : Z0, tile_done ? 0 : c0 + CW);
+#pragma unroll
             for (int m = 0; m < 14; ++m) {
-                const int tap = 2 * m + (hi ? 1 : 0);
-                const bool valid = tap < 27;
-                const int toff = (((tap / 9) * CT_HY + (tap / 3) % 3) * CT_HX + tap % 3) * STR;
-                const int wk = tap * cin + c0;
-                bf16x8 bw[NT];
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    if (valid) bw[t] = *reinterpret_cast<const bf16x8 *>(wl + t * wstep + wk);
-                    else
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) bw[t][j] = (bf16)0.0f;
-                }
+                const int t0 = 2 * m, t1 = m < 13 ? 2 * m + 1 : 26; // lanes g < 2 and g >= 2
+                const int o0 = (((t0 / 9) * CT_HY + (t0 / 3) % 3) * CT_HX + t0 % 3) * STR;
+                const int o1 = (((t1 / 9) * CT_HY + (t1 / 3) % 3) * CT_HX + t1 % 3) * STR;
+                const bf16 *at = tile + lbase + (hi ? o1 : o0);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    bf16x8 a;
-                    if (valid) a = *reinterpret_cast<const bf16x8 *>(tile + lbase + q * CT_HX * STR + toff);
-                    else
+                    bf16x8 a = *reinterpret_cast<const bf16x8 *>(at + q * CT_HX * STR);
+                    if (m == 13 && hi)
 #pragma unroll
                         for (int j = 0; j < 8; ++j) a[j] = (bf16)0.0f;
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
-                        acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[t], acc[q][t], 0, 0, 0);
+                        acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[m][t], a, acc[q][t], 0, 0, 0);
                 }
             }
         }
-    }
-    // lane holds D[4g + j][i]: voxel (X0 + 4g + j, Y0 + q, Z0 + wave), channel 16t + i
+        if (tile_done) {
+            // lane holds D[4g + j][i]: voxel (X0 + i, Y0 + q, Z0 + wave), channels 16t + 4g + j
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const long vrow = ((long)(Z0 + wave) * n + (Y0 + q)) * n + X0 + 4 * g;
+            for (int q = 0; q < 4; ++q) {
+                const long v = ((long)(Z0 + wave) * n + (Y0 + q)) * n + X0 + i;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int co = 16 * t + i;
-            const float bb = BIAS ? bias[co] : 0.0f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float r = acc[q][t][j] + bb;
-                if (RELU) r = r > 0.0f ? r : 0.0f;
-                out[(vrow + j) * ocstride + ocoff + co] = (bf16)r;
+                for (int t = 0; t < NT; ++t)
+                    store_out<RELU, BIAS>(acc[q][t], bias, cob + 16 * t + 4 * g,
+                                          out + v * ocstride + ocoff + cob + 16 * t + 4 * g);
             }
+            if (all_done) return;
+            --zt;
+            Z0 += 4;
+            c0 = 0;
+        } else {
+            c0 += CW;
         }
+        __syncthreads(); // this chunk's reads are done
     }
 }
 
@@ -382,21 +434,28 @@ __global__ void k_pack_input(const float *__restrict__ src, int cin, bf16 *__res
     d[1] = hi;
 }
 
-// 2x2x2 average of channels [coff, coff + c) -> [m^3][c]
+// 2x2x2 average of channels [coff, coff + c) -> [m^3][c]; one thread per voxel and
+// group of 8 channels (c, coff and cstride are multiples of 8)
 __global__ void k_pool(const bf16 *__restrict__ in, int cstride, int coff, int c, bf16 *__restrict__ out, int n)
 {
-    const int m = n / 2;
+    const int m = n / 2, gc = c / 8;
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (long)m * m * m * c) return;
-    const int ch = (int)(q % c);
-    const long V = q / c;
-    const int X = (int)(V % m), Y = (int)((V / m) % m), Z = (int)(V / ((long)m * m));
-    float s = 0.0f;
+    if (q >= (long)m * m * m * gc) return;
+    const int ch = (int)(q % gc) * 8;
+    const int V = (int)(q / gc);
+    const int X = V % m, Y = (V / m) % m, Z = V / (m * m);
+    float s[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
     for (int k = 0; k < 8; ++k) {
         const long v = ((long)(2 * Z + (k >> 2)) * n + 2 * Y + ((k >> 1) & 1)) * n + 2 * X + (k & 1);
-        s += (float)in[v * cstride + coff + ch];
+        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(in + v * cstride + coff + ch);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] += (float)a[j];
     }
-    out[V * c + ch] = (bf16)(0.125f * s);
+    bf16x8 o;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] = (bf16)(0.125f * s[j]);
+    *reinterpret_cast<bf16x8 *>(out + (long)V * c + ch) = o;
 }
 
 // gradient of the pooling, added to channels [coff, coff + c) of gin
@@ -458,27 +517,24 @@ __global__ void k_relu_bwd(bf16 *__restrict__ g, int gcstride, int gcoff, const 
     if (!((float)a[v * acstride + acoff + ch] > 0.0f)) g[v * gcstride + gcoff + ch] = (bf16)0.0f;
 }
 
-// 1x1 head: y[o][v] = b[o] + sum_c w[o][c] h[v][c]   (FP32 planar output)
-__global__ void k_head(const bf16 *__restrict__ h, int c, const float *__restrict__ w, const float *__restrict__ b,
-                       float *__restrict__ y, int cout, long N)
+// 1x1 head: y[o][v] = b[o] + sum_c w[o][c] h[v][c]   (FP32 planar output, 16 channels)
+__global__ void __launch_bounds__(TPB) k_head(const bf16 *__restrict__ h, const float *__restrict__ w,
+                                              const float *__restrict__ b, float *__restrict__ y, int cout, long N)
 {
     const long v = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= N) return;
+    const bf16x8 *hp = reinterpret_cast<const bf16x8 *>(h + v * 16);
+    const bf16x8 lo = hp[0], hi = hp[1];
     float hv[16];
-    if (c == 16) { // two 16-byte loads
-        const bf16x8 *hp = reinterpret_cast<const bf16x8 *>(h + v * 16);
-        const bf16x8 lo = hp[0], hi = hp[1];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            hv[k] = (float)lo[k];
-            hv[k + 8] = (float)hi[k];
-        }
-    } else {
-        for (int k = 0; k < c; ++k) hv[k] = (float)h[v * c + k];
+    for (int k = 0; k < 8; ++k) {
+        hv[k] = (float)lo[k];
+        hv[k + 8] = (float)hi[k];
     }
     for (int o = 0; o < cout; ++o) {
         float s = b[o];
-        for (int k = 0; k < c; ++k) s += w[o * c + k] * hv[k];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) s += w[o * 16 + k] * hv[k];
         y[o * N + v] = s;
     }
 }
@@ -755,14 +811,19 @@ int pad32(int k) { return (k + 31) / 32 * 32; }
 
 constexpr int kWgradBlocks = 64; // voxel-chunk blocks per tap of the weight gradient
 
-template <int COUT, int VG, bool RELU, bool BIAS>
-void launch_conv_ks(hipStream_t s, unsigned grid, const bf16 *in, int cin, int ics, int icoff, const bf16 *w, int kpad,
-                    const float *bias, bf16 *out, int ocs, int ocoff, int n)
+// k_conv3 with the channel steps unrolled for the counts that networks have
+template <int NT, int VG, bool RELU, bool BIAS, typename... A>
+void launch_conv_ks(hipStream_t s, dim3 grid, int cin, const bf16 *in, A... a)
 {
-    if (cin % 32 == 0)
-        k_conv3<COUT, VG, 32, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, ics, icoff, w, kpad, bias, out, ocs, ocoff, n);
-    else
-        k_conv3<COUT, VG, 16, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, ics, icoff, w, kpad, bias, out, ocs, ocoff, n);
+    switch (cin) {
+    case 16: k_conv3<NT, VG, 16, 1, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, a...); return;
+    case 32: k_conv3<NT, VG, 32, 1, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, a...); return;
+    case 48: k_conv3<NT, VG, 16, 3, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, a...); return;
+    case 64: k_conv3<NT, VG, 32, 2, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, a...); return;
+    case 96: k_conv3<NT, VG, 32, 3, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, a...); return;
+    case 128: k_conv3<NT, VG, 32, 4, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, a...); return;
+    default: k_conv3<NT, VG, 16, 0, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, a...);
+    }
 }
 
 template <bool RELU, bool BIAS>
@@ -771,45 +832,38 @@ bool launch_conv_t(hipStream_t s, int cout, const bf16 *in, int cin, int ics, in
 {
     const long N = (long)n * n * n;
     if (cin % 16 || N % 64 || N >= (1L << 31)) return false;
+    if (cout != 16 && cout != 32 && cout != 48 && cout != 64 && cout != 96 && cout != 128) return false;
     if (n % 16 == 0) {
+        // 32 channels a block balance LDS reads and products; 16 where the chip would
+        // have fewer than four blocks a CU otherwise
         const unsigned gl = (unsigned)((n / 16) * (n / 4) * (n / 4));
-#define CONV_LDS(C)                                                                                           \
-    case C:                                                                                                   \
-        if (cin % 32 == 0)                                                                                    \
-            k_conv3_lds<C, 32, RELU, BIAS><<<gl, 256, 0, s>>>(in, cin, ics, icoff, w, kpad, bias, out, ocs, ocoff, n); \
-        else                                                                                                  \
-            k_conv3_lds<C, 16, RELU, BIAS><<<gl, 256, 0, s>>>(in, cin, ics, icoff, w, kpad, bias, out, ocs, ocoff, n); \
-        return true;
-        switch (cout) {
-            CONV_LDS(16)
-            CONV_LDS(32)
-            CONV_LDS(48)
-            CONV_LDS(64)
-            CONV_LDS(96)
-            CONV_LDS(128)
-        default: return false;
+        const bool two = cout % 32 == 0 && gl * (cout / 32) >= 1024;
+        // 16 -> 16 channels: blocks march over up to four tiles in z while the chip keeps
+        // eight a CU; the weights and staging addresses are formed once
+        int zt = 1;
+        if (cin == 16 && cout == 16)
+            while (zt < 4 && n / 4 % (2 * zt) == 0 && gl / (2 * zt) >= 2048) zt *= 2;
+        const dim3 grid(gl / zt, cout / (two ? 32 : 16));
+#define CONV_LDS(NT, CW, MARCH)                                                                                    \
+    k_conv3_lds<NT, CW, MARCH, RELU, BIAS><<<grid, 256, 0, s>>>(in, cin, ics, icoff, w, kpad, bias, out, ocs, ocoff, n, zt)
+        if (cin % 32 == 0) {
+            if (two) CONV_LDS(2, 32, false);
+            else CONV_LDS(1, 32, false);
+        } else {
+            if (two) CONV_LDS(2, 16, false);
+            else if (zt > 1) CONV_LDS(1, 16, true);
+            else CONV_LDS(1, 16, false);
         }
 #undef CONV_LDS
+        return true;
     }
-    // four voxel groups per wave where the grid allows it (two for the widest outputs), else one
-    const int vg = (N % 256 == 0) ? (cout >= 96 ? 2 : 4) : 1;
-    const unsigned grid = (unsigned)(N / (64 * vg));
-#define CONV_CASE(C)                                                                                          \
-    case C:                                                                                                   \
-        if (vg == 4) launch_conv_ks<C, 4, RELU, BIAS>(s, grid, in, cin, ics, icoff, w, kpad, bias, out, ocs, ocoff, n); \
-        else if (vg == 2) launch_conv_ks<C, 2, RELU, BIAS>(s, grid, in, cin, ics, icoff, w, kpad, bias, out, ocs, ocoff, n); \
-        else launch_conv_ks<C, 1, RELU, BIAS>(s, grid, in, cin, ics, icoff, w, kpad, bias, out, ocs, ocoff, n); \
-        break;
-    switch (cout) {
-        CONV_CASE(16)
-        CONV_CASE(32)
-        CONV_CASE(48)
-        CONV_CASE(64)
-        CONV_CASE(96)
-        CONV_CASE(128)
-    default: return false;
-    }
-#undef CONV_CASE
+    // two groups of voxels and 32 channels a wave where that leaves two blocks a CU
+    if (cout % 32 == 0 && N % 128 == 0 && N / 128 * (cout / 32) >= 512)
+        launch_conv_ks<2, 2, RELU, BIAS>(s, dim3((unsigned)(N / 128), cout / 32), cin, in, ics, icoff, w, kpad, bias, out,
+                                         ocs, ocoff, n);
+    else
+        launch_conv_ks<1, 1, RELU, BIAS>(s, dim3((unsigned)(N / 64), cout / 16), cin, in, ics, icoff, w, kpad, bias, out,
+                                         ocs, ocoff, n);
     return true;
 }
 
@@ -987,7 +1041,7 @@ int forward(gr_unet U, int n, const float *d_in)
     for (int k = 0; k < 3; ++k) {
         const int nk = n >> k, nk1 = nk >> 1;
         // pool the skip channels of cat[k]
-        k_pool<<<nb((long)nk1 * nk1 * nk1 * c[k]), TPB, 0, s>>>(U->cat[k].p, c[k + 1] + c[k], c[k + 1], c[k], U->p[k].p, nk);
+        k_pool<<<nb((long)nk1 * nk1 * nk1 * (c[k] / 8)), TPB, 0, s>>>(U->cat[k].p, c[k + 1] + c[k], c[k + 1], c[k], U->p[k].p, nk);
         ULAUNCH();
         const int la = E1A + 2 * k, lb = E1B + 2 * k;
         UCHK(conv_fwd(U, la, U->p[k].p, c[k], 0, U->ea[k + 1].p, c[k + 1], 0, nk1));
@@ -1005,7 +1059,7 @@ int forward(gr_unet U, int n, const float *d_in)
         UCHK(conv_fwd(U, la, U->cat[k].p, c[k + 1] + c[k], 0, U->da[k].p, c[k], 0, nk));
         UCHK(conv_fwd(U, lb, U->da[k].p, c[k], 0, U->db[k].p, c[k], 0, nk));
     }
-    k_head<<<nb(N), TPB, 0, s>>>(U->db[0].p, c[0], U->param + U->head_w, U->param + U->head_b, U->y, U->d.out_ch, N);
+    k_head<<<nb(N), TPB, 0, s>>>(U->db[0].p, U->param + U->head_w, U->param + U->head_b, U->y, U->d.out_ch, N);
     ULAUNCH();
     return GR_OK;
 }
