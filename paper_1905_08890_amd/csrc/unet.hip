@@ -312,107 +312,182 @@ __global__ void __launch_bounds__(256, MARCH ? 3 : 2)
 // Weight gradient of a 3^3 convolution on the BF16 matrix cores:
 //   dW[co][tap*cin + ci] = sum_v g[v][gcoff + co] in[v + off(tap)][icoff + ci],
 //   db[co] = sum_v g[v][gcoff + co].
-// Per tap this is a GEMM with M = cout, N = cin and K = the voxels.  A block
-// owns one tap and every WB-th chunk of 64 consecutive voxels; each chunk's
-// output gradient and shifted input are staged in LDS transposed (channel
-// rows of 64 voxels), so an MFMA operand (8 consecutive voxels of one channel)
-// is one 16-byte LDS read.  Each wave accumulates its 16 x 16 (co, ci) tiles
-// over the block's chunks in FP32; the block writes its partial sums, and
-// k_wgrad_reduce adds the WB partials in a fixed order (deterministic).
-constexpr int WG_CHUNK = 64;              // voxels per staged chunk (two K steps)
-constexpr int WG_ROW = WG_CHUNK + 8;      // LDS row pitch in bf16 (144 bytes)
+// Per tap this is a GEMM with M = cout, N = cin and K = the voxels.  A block takes
+// tiles of TX x 4 x 4 voxels (TX = 16, 8 or 4) and CO x CI channels for all 27 taps:
+// the output gradient and the input with its halo are staged in LDS once, channels
+// last, and the operands (8 voxels of one channel a lane) come from transposing LDS
+// reads (ds_read_b64_tr_b16: 16 lanes read 4 voxels x 16 channels, lane i gets the 4
+// voxels of channel i), so a tap is an offset.  Wave w accumulates the taps w, w + 4,
+// ... in FP32 over the block's tiles (blockIdx.x, + gridDim.x, ...); the block writes
+// its partial sums, and k_wgrad_reduce adds the partials in a fixed order.  db comes
+// from products with ones in the waves that have one tap less.
+// A block a tap, staged 27 times and transposed by 2-byte stores, took 73 us a layer
+// (64^3 network, 14 layers); this 8-18 us (48 -> 16 at 64^3: 40), bound by latency and, at 16
+// channels, by the LDS reads.
 constexpr int WG_MAXC = 128;              // largest channel count of either side
-constexpr int WG_MAXT = 8;                // 16 x 16 tiles per wave (cout/16 * cin/16 <= 32)
+typedef __attribute__((address_space(3))) shortx4 *lds_s4;
+union WgOperand {
+    shortx4 h[2];
+    bf16x8 v;
+};
+// 8 voxels (two runs of 4) x this lane's channel
+__device__ __forceinline__ bf16x8 wg_operand(const bf16 *p0, const bf16 *p1)
+{
+    WgOperand o;
+    o.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(__attribute__((address_space(3))) short *)(short *)p0);
+    o.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(__attribute__((address_space(3))) short *)(short *)p1);
+    return o.v;
+}
+template <int TX, int CO, int CI>
 __global__ void __launch_bounds__(TPB) k_conv3_wgrad(const bf16 *__restrict__ g, int cout, int gcstride, int gcoff,
                                                      const bf16 *__restrict__ in, int cin, int icstride, int icoff,
                                                      float *__restrict__ part, float *__restrict__ bpart, int n)
 {
-    __shared__ __attribute__((aligned(16))) bf16 sg[64 * WG_ROW];
-    __shared__ __attribute__((aligned(16))) bf16 si[WG_MAXC * WG_ROW];
-    const int tap = blockIdx.y;
-    const int dx = tap % 3 - 1, dy = (tap / 3) % 3 - 1, dz = tap / 9 - 1;
-    const long N = (long)n * n * n;
-    const long nchunk = N / WG_CHUNK;
+    constexpr int HX = TX + 2, HV = HX * 36, TV = TX * 16; // halo and tile voxels
+    constexpr int SG = CO + 8, SI = CI + 8;                // LDS strides of a voxel
+    constexpr int UG = CO / 8, UI = CI / 8, PG = (TV * UG + TPB - 1) / TPB, PI = (HV * UI + TPB - 1) / TPB;
+    constexpr int NT = 7, MT = CO / 16, KT = CI / 16, STEPS = TV / 32;
+    __shared__ __align__(16) bf16 sg[TV * SG];
+    __shared__ __align__(16) bf16 si[HV * SI];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, gq = lane >> 4;
-    const int tco = cout / 16, tci = cin / 16, ntile = tco * tci;
-    floatx4 acc[WG_MAXT];
+    const int co0 = CO * (blockIdx.y % (cout / CO)), ci0 = CI * (blockIdx.y / (cout / CO));
+    const int tx = n / TX, ty = n / 4, tiles = tx * ty * ty;
+    floatx4 acc[NT][MT][KT], bacc[MT];
 #pragma unroll
-    for (int t = 0; t < WG_MAXT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float bacc = 0.0f;
-    const int gvec = cout / 8, ivec = cin / 8;
-    for (long ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
-        const long v0 = ch * WG_CHUNK;
-        // stage: g rows [co][voxel], input rows [ci][voxel] at the tap's shifted voxels
-        for (int e = threadIdx.x; e < WG_CHUNK * gvec; e += TPB) {
-            const int r = e / gvec, q = e % gvec;
-            const bf16x8 val = *reinterpret_cast<const bf16x8 *>(g + (v0 + r) * gcstride + gcoff + 8 * q);
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) sg[(8 * q + j) * WG_ROW + r] = val[j];
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int k = 0; k < KT; ++k) acc[t][m][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < MT; ++m) bacc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 ones;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ones[j] = (bf16)1.0f;
+    // this lane's place in the LDS reads: voxel i / 4 of a run of 4, channels 4 (i % 4) ..
+    const bf16 *const lg = sg + (i >> 2) * SG + 4 * (i & 3), *const li = si + (i >> 2) * SI + 4 * (i & 3);
+    // voxel 8 gq (+ 4) of K step 0: run of 4 in x, rows of TX in y, then z
+    const int r0 = 2 * gq, r1 = 2 * gq + 1; // runs of 4 voxels
+    constexpr int RX = TX / 4;              // runs per row
+    auto run_halo = [](int r) { return ((r / (4 * RX)) * 6 + (r / RX) % 4) * HX + 4 * (r % RX); };
+    const int hr0 = run_halo(r0) * SI, hr1 = run_halo(r1) * SI;
+    bf16x8 pg[PG], pi[PI];
+    auto fetch = [&](int tile) {
+        const int X0 = (tile % tx) * TX, Y0 = ((tile / tx) % ty) * 4, Z0 = (tile / tx / ty) * 4;
+#pragma unroll
+        for (int r = 0; r < PG; ++r) {
+            const int u = threadIdx.x + TPB * r, v = u < TV * UG ? u / UG : 0;
+            const long src = ((long)(Z0 + v / (4 * TX)) * n + Y0 + (v / TX) % 4) * n + X0 + v % TX;
+            pg[r] = *reinterpret_cast<const bf16x8 *>(g + src * gcstride + gcoff + co0 + 8 * (u % UG));
         }
-        for (int e = threadIdx.x; e < WG_CHUNK * ivec; e += TPB) {
-            const int r = e / ivec, q = e % ivec;
-            const long v = v0 + r;
-            const int x = (int)(v % n), y = (int)((v / n) % n), z = (int)(v / ((long)n * n));
-            const long src = ((long)wrapn(z + dz, n) * n + wrapn(y + dy, n)) * n + wrapn(x + dx, n);
-            const bf16x8 val = *reinterpret_cast<const bf16x8 *>(in + src * icstride + icoff + 8 * q);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) si[(8 * q + j) * WG_ROW + r] = val[j];
+        for (int r = 0; r < PI; ++r) {
+            const int u = threadIdx.x + TPB * r, h = u < HV * UI ? u / UI : 0;
+            const long src = ((long)wrapn(Z0 - 1 + h / (6 * HX), n) * n + wrapn(Y0 - 1 + (h / HX) % 6, n)) * n +
+                             wrapn(X0 - 1 + h % HX, n);
+            pi[r] = *reinterpret_cast<const bf16x8 *>(in + src * icstride + icoff + ci0 + 8 * (u % UI));
+        }
+    };
+    fetch(blockIdx.x);
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+#pragma unroll
+        for (int r = 0; r < PG; ++r) {
+            const int u = threadIdx.x + TPB * r;
+            if (u < TV * UG) *reinterpret_cast<bf16x8 *>(sg + (u / UG) * SG + 8 * (u % UG)) = pg[r];
+        }
+#pragma unroll
+        for (int r = 0; r < PI; ++r) {
+            const int u = threadIdx.x + TPB * r;
+            if (u < HV * UI) *reinterpret_cast<bf16x8 *>(si + (u / UI) * SI + 8 * (u % UI)) = pi[r];
         }
         __syncthreads();
+        if (tile + (int)gridDim.x < tiles) fetch(tile + gridDim.x);
+#pragma unroll 1
+        for (int s = 0; s < STEPS; ++s) { // 32 voxels: 8 runs
+            bf16x8 a[MT];
 #pragma unroll
-        for (int t = 0; t < WG_MAXT; ++t) {
-            const int tile = wave + 4 * t;
-            if (tile < ntile) {
-                const int cot = tile / tci, cit = tile % tci;
+            for (int m = 0; m < MT; ++m)
+                a[m] = wg_operand(lg + (32 * s + 8 * gq) * SG + 16 * m, lg + (32 * s + 8 * gq + 4) * SG + 16 * m);
+            const int hs = run_halo(8 * s) * SI;
 #pragma unroll
-                for (int ks = 0; ks < WG_CHUNK / 32; ++ks) {
-                    const int k = 32 * ks + 8 * gq;
-                    const bf16x8 a = *reinterpret_cast<const bf16x8 *>(sg + (16 * cot + i) * WG_ROW + k);
-                    const bf16x8 b = *reinterpret_cast<const bf16x8 *>(si + (16 * cit + i) * WG_ROW + k);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[t], 0, 0, 0);
+            for (int t = 0; t < NT; ++t) {
+                const int tap = wave + 4 * t;
+                if (tap < 27) { // uniform in the wave
+                    const int to = (((tap / 9) * 6 + (tap / 3) % 3) * HX + tap % 3) * SI + hs;
+#pragma unroll
+                    for (int k = 0; k < KT; ++k) {
+                        const bf16x8 b = wg_operand(li + hr0 + to + 16 * k, li + hr1 + to + 16 * k);
+#pragma unroll
+                        for (int m = 0; m < MT; ++m)
+                            acc[t][m][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[t][m][k], 0, 0, 0);
+                    }
+                } else if (ci0 == 0) { // wave 3: the bias gradient
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+                        bacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], ones, bacc[m], 0, 0, 0);
                 }
             }
-        }
-        if (tap == 13 && (int)threadIdx.x < cout) {
-            float s = 0.0f;
-            for (int r = 0; r < WG_CHUNK; ++r) s += (float)sg[threadIdx.x * WG_ROW + r];
-            bacc += s;
         }
         __syncthreads();
     }
     // partial of this block: part[blockIdx.x][tap][co][ci]; lane holds D[4gq + j][i]
-    float *dst = part + ((long)blockIdx.x * 27 + tap) * cout * cin;
 #pragma unroll
-    for (int t = 0; t < WG_MAXT; ++t) {
-        const int tile = wave + 4 * t;
-        if (tile < ntile) {
-            const int cot = tile / tci, cit = tile % tci;
+    for (int t = 0; t < NT; ++t) {
+        const int tap = wave + 4 * t;
+        if (tap >= 27) continue;
+        float *dst = part + ((long)blockIdx.x * 27 + tap) * cout * cin;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) dst[(long)(16 * cot + 4 * gq + j) * cin + 16 * cit + i] = acc[t][j];
-        }
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int k = 0; k < KT; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    dst[(long)(co0 + 16 * m + 4 * gq + j) * cin + ci0 + 16 * k + i] = acc[t][m][k][j];
     }
-    if (tap == 13 && (int)threadIdx.x < cout) bpart[(long)blockIdx.x * cout + threadIdx.x] = bacc;
+    if (wave == 3 && ci0 == 0 && i == 0)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bpart[(long)blockIdx.x * cout + co0 + 16 * m + 4 * gq + j] = bacc[m][j];
 }
 
-// dw[co][tap*cin + ci] += sum over the nb block partials (in order); db likewise
-__global__ void k_wgrad_reduce(const float *__restrict__ part, const float *__restrict__ bpart, int nbk, int cout,
-                               int cin, float *__restrict__ dw, float *__restrict__ db)
+// dw[co][tap*cin + ci] += sum over the nbk block partials, db likewise, in a fixed order.
+// Four consecutive values a thread; the 8 groups of 32 threads of a block take every
+// eighth partial and are added in order.  The last block takes db, 4 groups of 64.
+__global__ void __launch_bounds__(TPB) k_wgrad_reduce(const float *__restrict__ part, const float *__restrict__ bpart,
+                                                      int nbk, int cout, int cin, float *__restrict__ dw,
+                                                      float *__restrict__ db)
 {
-    const long per = 27L * cout * cin;
-    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < per) {
+    __shared__ floatx4 sh[8][32];
+    __shared__ float shb[4][64];
+    if (blockIdx.x == gridDim.x - 1) {
+        const int c = threadIdx.x & 63, w = threadIdx.x >> 6;
+        float t = 0.0f;
+        if (c < cout)
+#pragma unroll 8
+            for (int b = w; b < nbk; b += 4) t += bpart[(long)b * cout + c];
+        shb[w][c] = t;
+        __syncthreads();
+        if (w == 0 && c < cout) db[c] += ((t + shb[1][c]) + shb[2][c]) + shb[3][c];
+        return;
+    }
+    const long per = 27L * cout * cin; // a multiple of 128
+    const int c = threadIdx.x & 31, w = threadIdx.x >> 5;
+    const long q = (long)blockIdx.x * 128 + 4 * c;
+    floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int b = w; b < nbk; b += 8) s += *reinterpret_cast<const floatx4 *>(part + (long)b * per + q);
+    sh[w][c] = s;
+    __syncthreads();
+    if (w == 0) {
+        for (int k = 1; k < 8; ++k) s += sh[k][c];
         const int tap = (int)(q / ((long)cout * cin));
         const int rem = (int)(q % ((long)cout * cin));
         const int co = rem / cin, ci = rem % cin;
-        float s = 0.0f;
-        for (int b = 0; b < nbk; ++b) s += part[(long)b * per + q];
-        dw[(long)co * 27 * cin + tap * cin + ci] += s;
-    }
-    if (db && q < cout) {
-        float s = 0.0f;
-        for (int b = 0; b < nbk; ++b) s += bpart[(long)b * cout + q];
-        db[q] += s;
+        float *d = dw + (long)co * 27 * cin + tap * cin + ci; // parameters start at any multiple of 4 bytes
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[j] += s[j];
     }
 }
 
@@ -506,15 +581,22 @@ __global__ void k_upsample_bwd(const bf16 *__restrict__ gout, int cstride, int c
     gin[V * c + ch] = (bf16)s;
 }
 
-// g = g * (a > 0) on channels [coff, coff + c) of both (ReLU gradient)
+// g = g * (a > 0) on channels [coff, coff + c) of both (ReLU gradient); one thread per
+// voxel and group of 8 channels (all counts and offsets are multiples of 8)
 __global__ void k_relu_bwd(bf16 *__restrict__ g, int gcstride, int gcoff, const bf16 *__restrict__ a, int acstride,
                            int acoff, int c, long N)
 {
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N * c) return;
-    const int ch = (int)(q % c);
-    const long v = q / c;
-    if (!((float)a[v * acstride + acoff + ch] > 0.0f)) g[v * gcstride + gcoff + ch] = (bf16)0.0f;
+    const int gc = c / 8;
+    if (q >= N * gc) return;
+    const int v = (int)(q / gc), ch = (int)(q - (long)v * gc) * 8;
+    bf16x8 *gp = reinterpret_cast<bf16x8 *>(g + (long)v * gcstride + gcoff + ch);
+    const bf16x8 av = *reinterpret_cast<const bf16x8 *>(a + (long)v * acstride + acoff + ch);
+    bf16x8 gv = *gp;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (!((float)av[j] > 0.0f)) gv[j] = (bf16)0.0f;
+    *gp = gv;
 }
 
 // 1x1 head: y[o][v] = b[o] + sum_c w[o][c] h[v][c]   (FP32 planar output, 16 channels)
@@ -809,7 +891,9 @@ int ufail(int code, const char *fmt, ...)
 
 int pad32(int k) { return (k + 31) / 32 * 32; }
 
-constexpr int kWgradBlocks = 64; // voxel-chunk blocks per tap of the weight gradient
+constexpr int kWgradBlocks = 64; // most partial sums of a weight gradient of 128 x 64 channels
+
+constexpr int kWgradRows = 512;  // most partial sums of any
 
 // k_conv3 with the channel steps unrolled for the counts that networks have
 template <int NT, int VG, bool RELU, bool BIAS, typename... A>
@@ -935,7 +1019,7 @@ size_t unet_layout(gr_unet U, char *base)
     // taps x cout x cin) or the head's (one block per 256 voxels x its parameters)
     const size_t head_part = (size_t)((N + TPB - 1) / TPB) * (size_t)(U->d.out_ch * U->c[0] + U->d.out_ch);
     U->wg_part = takeF(std::max((size_t)kWgradBlocks * 27 * WG_MAXC * 64, head_part));
-    U->wg_bpart = takeF((size_t)kWgradBlocks * 64);
+    U->wg_bpart = takeF((size_t)kWgradRows * 64);
     U->y = takeF((size_t)U->d.out_ch * N);
     U->gy = takeF((size_t)U->d.out_ch * N);
     U->lq = takeF((size_t)U->d.out_ch * N);
@@ -989,15 +1073,34 @@ int conv_wgrad(gr_unet U, int li, const bf16 *gout, int gcs, int gcoff, const bf
 {
     const ConvLayer &L = U->conv[li];
     const long N = (long)n * n * n;
-    if (N % WG_CHUNK || L.cout % 16 || L.cin % 16 || L.cout > 64 || L.cin > WG_MAXC ||
-        (L.cout / 16) * (L.cin / 16) > 4 * WG_MAXT)
+    if (N % 64 || n % 4 || L.cout % 16 || L.cin % 16 || L.cout > 64 || L.cin > WG_MAXC)
         return ufail(GR_EINVAL, "weight gradient: unsupported shape (n %d, cin %d, cout %d)", n, L.cin, L.cout);
-    const int nbk = (int)std::min<long>(kWgradBlocks, N / WG_CHUNK);
-    k_conv3_wgrad<<<dim3((unsigned)nbk, 27), TPB, 0, U->stream>>>(gout, L.cout, gcs, gcoff, in, L.cin, ics, icoff,
-                                                                 U->wg_part, U->wg_bpart, n);
+    // a tile of 16 x 4 x 4 voxels where the side has them; 32 channels of a side where they
+    // divide it; as many partial sums as give the chip two blocks a CU, but no more than
+    // there is room for (kWgradBlocks x 128 x 64) or tiles
+    const int tw = n % 16 == 0 ? 16 : n % 8 == 0 ? 8 : 4;
+    const int co = L.cout % 32 ? 16 : 32, ci = L.cin % 32 ? 16 : 32, cb = L.cout / co * (L.cin / ci);
+    const long room = (long)kWgradBlocks * WG_MAXC * 64 / ((long)L.cout * L.cin);
+    const int nbk = (int)std::min({(long)(512 + cb - 1) / cb, N / (16 * tw), room, (long)kWgradRows});
+    const dim3 grid((unsigned)nbk, (unsigned)cb);
+#define WGRAD(TX, CO, CI)                                                                                        \
+    k_conv3_wgrad<TX, CO, CI><<<grid, TPB, 0, U->stream>>>(gout, L.cout, gcs, gcoff, in, L.cin, ics, icoff,     \
+                                                           U->wg_part, U->wg_bpart, n)
+#define WGRAD_X(CO, CI)                                                                                          \
+    do {                                                                                                        \
+        if (tw == 16) WGRAD(16, CO, CI);                                                                         \
+        else if (tw == 8) WGRAD(8, CO, CI);                                                                      \
+        else WGRAD(4, CO, CI);                                                                                   \
+    } while (0)
+    if (co == 32 && ci == 32) WGRAD_X(32, 32);
+    else if (co == 32) WGRAD_X(32, 16);
+    else if (ci == 32) WGRAD_X(16, 32);
+    else WGRAD_X(16, 16);
+#undef WGRAD_X
+#undef WGRAD
     const long per = 27L * L.cout * L.cin;
-    k_wgrad_reduce<<<nb(per), TPB, 0, U->stream>>>(U->wg_part, U->wg_bpart, nbk, L.cout, L.cin, U->grad + L.w_off,
-                                                   U->grad + L.b_off);
+    k_wgrad_reduce<<<(unsigned)(per / 128) + 1, TPB, 0, U->stream>>>(U->wg_part, U->wg_bpart, nbk, L.cout, L.cin,
+                                                                 U->grad + L.w_off, U->grad + L.b_off);
     ULAUNCH();
     return GR_OK;
 }
@@ -1005,7 +1108,7 @@ int conv_wgrad(gr_unet U, int li, const bf16 *gout, int gcs, int gcoff, const bf
 int relu_bwd(gr_unet U, bf16 *g, int gcs, int gcoff, const bf16 *a, int acs, int acoff, int c, int n)
 {
     const long N = (long)n * n * n;
-    k_relu_bwd<<<nb(N * c), TPB, 0, U->stream>>>(g, gcs, gcoff, a, acs, acoff, c, N);
+    k_relu_bwd<<<nb(N * (c / 8)), TPB, 0, U->stream>>>(g, gcs, gcoff, a, acs, acoff, c, N);
     ULAUNCH();
     return GR_OK;
 }
