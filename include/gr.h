@@ -481,8 +481,8 @@ const char *gr_unet_last_error(void);
  * and the means of P_curl, P_div, P_vector, P_scalar over its modes.  nbins =
  * n / 8 reaches a quarter of the Nyquist wave number pi n.
  * Handle: n a power of two in [8, 1024], 1 <= nbins <= n / 4; the workspace
- * (2 n S (n + S) complex values, S = 2 nbins + 1, plus small tables,
- * gr_spectra_workspace_bytes, 256-byte aligned) is the caller's.  gr_vector_spectra runs on the bound
+ * (two complex n^3 arrays plus small tables, gr_spectra_workspace_bytes,
+ * 256-byte aligned) is the caller's.  gr_vector_spectra runs on the bound
  * stream and synchronises it before returning; the results are deterministic
  * (fixed summation order).  gr_spectra_fft: in-place forward 3-D FFT of an
  * n^3 complex array (interleaved re, im doubles) with the same kernels.

@@ -1107,9 +1107,10 @@ int gr_create_grid(const gr_grid_desc *desc, const gr_params *prm, gr_grid *out)
         g->lev[l].N = (long)g->lev[l].n * g->lev[l].n * g->lev[l].n;
     }
     // GRMG_CONCURRENT=0: solve the components of vector equations one after another
-    // (from 16^3: the three components of a 48^3 vector equation in 3.0 instead of 5.7 ms,
-    // of a 16^3 one in about the time of one; below, the grid is one launch a cycle)
-    bool conc = n >= 16;
+    // Above 32^3: the three components of a 48^3 vector equation take 3.0 instead of 5.7 ms.
+    // On smaller grids, where a solve is ~1 ms, the helpers' arrays would add a quarter to
+    // the workspace.
+    bool conc = n > 32;
     if (const char *e = std::getenv("GRMG_CONCURRENT")) conc = conc && std::atoi(e) != 0;
     if (conc)
         for (auto &h : g->sub) {

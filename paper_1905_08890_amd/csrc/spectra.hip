@@ -18,6 +18,7 @@
 //      over the planes).
 // gr_spectra_fft, the whole transform of a caller's array, moves line bundles
 // through LDS with radix-2 stages.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -457,6 +458,7 @@ int gr_create_spectra(int n, int nbins, gr_spectra *out)
     off += al256(2 * (size_t)n * n * side * sizeof(double2));
     S->off_b = off; // y pass output
     off += al256(2 * (size_t)n * side * side * sizeof(double2));
+    off = std::max(off, 2 * al256((size_t)n * n * n * sizeof(double2))); // the size callers have always been told
     S->off_tw = off;
     off += al256((size_t)(n / 2) * sizeof(double2));
     S->off_part = off;

@@ -90,7 +90,7 @@ def test_cycles_queued_ahead_stop_alike(n, kind, monkeypatch):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
-@pytest.mark.parametrize("n", [16, 24, 32])
+@pytest.mark.parametrize("n", [32, 36, 40, 48])
 def test_concurrent_components_of_small_grids(n, precision, monkeypatch):
     """The vector components on three streams equal the ones solved in turn, bit for bit."""
     print(f"[gpu] concurrent components n={n} {precision}", flush=True)
