@@ -533,19 +533,32 @@ __global__ void k_pool(const bf16 *__restrict__ in, int cstride, int coff, int c
     *reinterpret_cast<bf16x8 *>(out + (long)V * c + ch) = o;
 }
 
-// gradient of the pooling, added to channels [coff, coff + c) of gin
+// voxel v < 2^31 of an n^3 grid
+__device__ __forceinline__ void voxel_at(int v, int n, int &x, int &y, int &z)
+{
+    const unsigned r = (unsigned)v / n;
+    x = (int)((unsigned)v - r * n);
+    z = (int)(r / n);
+    y = (int)(r - z * n);
+}
+
+// gradient of the pooling, added to channels [coff, coff + c) of gin; one thread per
+// voxel and group of 8 channels (c, coff and cstride are multiples of 8)
 __global__ void k_pool_bwd_add(const bf16 *__restrict__ gout, int c, bf16 *__restrict__ gin, int cstride, int coff,
                                int n)
 {
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (long)n * n * n * c) return;
-    const int ch = (int)(q % c);
-    const long v = q / c;
-    const int x = (int)(v % n), y = (int)((v / n) % n), z = (int)(v / ((long)n * n));
-    const int m = n / 2;
-    const long V = ((long)(z / 2) * m + y / 2) * m + x / 2;
-    const long d = v * cstride + coff + ch;
-    gin[d] = (bf16)((float)gin[d] + 0.125f * (float)gout[V * c + ch]);
+    const int gc = c / 8;
+    if (q >= (long)n * n * n * gc) return;
+    const int v = (int)(q / gc), ch = (int)(q - (long)v * gc) * 8, m = n / 2;
+    int x, y, z;
+    voxel_at(v, n, x, y, z);
+    const bf16x8 o = *reinterpret_cast<const bf16x8 *>(gout + (((long)(z / 2) * m + y / 2) * m + x / 2) * c + ch);
+    bf16x8 *gp = reinterpret_cast<bf16x8 *>(gin + (long)v * cstride + coff + ch);
+    bf16x8 gv = *gp;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) gv[j] = (bf16)((float)gv[j] + 0.125f * (float)o[j]);
+    *gp = gv;
 }
 
 // nearest upsampling of [m^3][c] into channels [0, c) of out [n^3][cstride]
@@ -556,11 +569,10 @@ __global__ void k_upsample(const bf16 *__restrict__ in, int c, bf16 *__restrict_
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const int cg = c >> 3;
     if (q >= (long)n * n * n * cg) return;
-    const int ch = (int)(q % cg) * 8;
-    const long v = q / cg;
-    const int x = (int)(v % n), y = (int)((v / n) % n), z = (int)(v / ((long)n * n));
-    const int m = n / 2;
-    *reinterpret_cast<bf16x8 *>(out + v * cstride + ch) =
+    const int v = (int)(q / cg), ch = (int)(q - (long)v * cg) * 8, m = n / 2;
+    int x, y, z;
+    voxel_at(v, n, x, y, z);
+    *reinterpret_cast<bf16x8 *>(out + (long)v * cstride + ch) =
         *reinterpret_cast<const bf16x8 *>(in + (((long)(z / 2) * m + y / 2) * m + x / 2) * c + ch);
 }
 
@@ -676,7 +688,8 @@ __global__ void k_lap_loss1(const float *__restrict__ y, const float *__restrict
     float s = 0.0f;
     for (long p = (long)blockIdx.x * TPB + threadIdx.x; p < total; p += (long)gridDim.x * TPB) {
         const long ch = p / N, v = p - ch * N;
-        const int x = (int)(v % n), yy = (int)((v / n) % n), z = (int)(v / ((long)n * n));
+        const unsigned r = (unsigned)v / n; // below 2^31 voxels
+        const int x = (int)((unsigned)v - r * n), z = (int)(r / n), yy = (int)(r - z * n);
         const float l = lap_at<true>(y, t, ch * N, x, yy, z, n);
         q[p] = l;
         s += l * l;
@@ -695,7 +708,8 @@ __global__ void k_lap_loss2(const float *__restrict__ q, float *__restrict__ gy,
     const long N = (long)n * n * n;
     for (long p = (long)blockIdx.x * TPB + threadIdx.x; p < total; p += (long)gridDim.x * TPB) {
         const long ch = p / N, v = p - ch * N;
-        const int x = (int)(v % n), yy = (int)((v / n) % n), z = (int)(v / ((long)n * n));
+        const unsigned r = (unsigned)v / n; // below 2^31 voxels
+        const int x = (int)((unsigned)v - r * n), z = (int)(r / n), yy = (int)(r - z * n);
         gy[p] += 2.0f * lam * lap_at<false>(q, nullptr, ch * N, x, yy, z, n) / (float)total;
     }
 }
@@ -704,39 +718,60 @@ __global__ void k_lap_loss2(const float *__restrict__ q, float *__restrict__ gy,
 // dW[o][c] = sum_v gy[o][v] h[v][c] and db[o] = sum_v gy[o][v] over its 256
 // voxels, one parameter per thread in voxel order, to part[block][cout*c + cout]
 // (k_head_reduce adds the blocks in order: deterministic).
-__global__ void __launch_bounds__(TPB) k_head_bwd(const float *__restrict__ gy, const bf16 *__restrict__ h, int c,
+// 16 channels; the output gradients of a voxel are read once.
+__global__ void __launch_bounds__(TPB) k_head_bwd(const float *__restrict__ gy, const bf16 *__restrict__ h,
                                                   const float *__restrict__ w, int cout, bf16 *__restrict__ gh,
                                                   float *__restrict__ part, long N)
 {
+    constexpr int C = 16;
     __shared__ float sgy[16][TPB];
-    __shared__ float sh[TPB][17];
-    const long v0 = (long)blockIdx.x * TPB;
-    const long v = v0 + threadIdx.x;
+    __shared__ float sh[TPB][C + 1];
+    const long v = (long)blockIdx.x * TPB + threadIdx.x;
+    float hv[C], g[C], gv[16];
+#pragma unroll
+    for (int k = 0; k < C; ++k) hv[k] = g[k] = 0.0f;
+#pragma unroll
+    for (int o = 0; o < 16; ++o) gv[o] = v < N && o < cout ? gy[o * N + v] : 0.0f;
     if (v < N) {
-        float hv[16];
-        for (int k = 0; k < c; ++k) {
-            hv[k] = (float)h[v * c + k];
-            sh[threadIdx.x][k] = hv[k];
+        const bf16x8 *hp = reinterpret_cast<const bf16x8 *>(h + v * C);
+        const bf16x8 lo = hp[0], hi = hp[1];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            hv[k] = (float)lo[k];
+            hv[k + 8] = (float)hi[k];
         }
-        for (int o = 0; o < cout; ++o) sgy[o][threadIdx.x] = gy[o * N + v];
-        for (int k = 0; k < c; ++k) {
-            float s = 0.0f;
-            for (int o = 0; o < cout; ++o) s += w[o * c + k] * gy[o * N + v];
-            gh[v * c + k] = (bf16)s;
+    }
+#pragma unroll
+    for (int o = 0; o < 16; ++o) {
+        if (o >= cout) break;
+#pragma unroll
+        for (int k = 0; k < C; ++k) g[k] += w[o * C + k] * gv[o];
+        sgy[o][threadIdx.x] = gv[o];
+    }
+#pragma unroll
+    for (int k = 0; k < C; ++k) sh[threadIdx.x][k] = hv[k];
+    if (v < N) {
+        bf16x8 lo, hi;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            lo[k] = (bf16)g[k];
+            hi[k] = (bf16)g[k + 8];
         }
-    } else {
-        for (int k = 0; k < c; ++k) sh[threadIdx.x][k] = 0.0f;
-        for (int o = 0; o < cout; ++o) sgy[o][threadIdx.x] = 0.0f;
+        bf16x8 *gp = reinterpret_cast<bf16x8 *>(gh + v * C);
+        gp[0] = lo;
+        gp[1] = hi;
     }
     __syncthreads();
-    const int npar = cout * c + cout;
+    const int npar = cout * C + cout;
     for (int q = threadIdx.x; q < npar; q += TPB) {
         float s = 0.0f;
-        if (q < cout * c) {
-            const int o = q / c, k = q % c;
+        if (q < cout * C) {
+            const int o = q / C, k = q % C;
+#pragma unroll 8
             for (int r = 0; r < TPB; ++r) s += sgy[o][r] * sh[r][k];
         } else {
-            const int o = q - cout * c;
+            const int o = q - cout * C;
+#pragma unroll 8
             for (int r = 0; r < TPB; ++r) s += sgy[o][r];
         }
         part[(long)blockIdx.x * npar + q] = s;
@@ -1176,7 +1211,7 @@ int backward(gr_unet U, int n)
     {
         const int nw = U->d.out_ch * c[0], npar = nw + U->d.out_ch;
         const unsigned nblk = nb(N);
-        k_head_bwd<<<nblk, TPB, 0, s>>>(U->gy, U->db[0].p, c[0], U->param + U->head_w, U->d.out_ch, U->g_db[0].p,
+        k_head_bwd<<<nblk, TPB, 0, s>>>(U->gy, U->db[0].p, U->param + U->head_w, U->d.out_ch, U->g_db[0].p,
                                         U->wg_part, N);
         k_head_reduce<<<(unsigned)npar, TPB, 0, s>>>(U->wg_part, (int)nblk, npar, nw, U->grad + U->head_w,
                                                      U->grad + U->head_b);
@@ -1213,7 +1248,7 @@ int backward(gr_unet U, int n)
     for (int k = 2; k >= 0; --k) {
         const int nk = n >> k;
         const int C = c[k + 1] + c[k];
-        k_pool_bwd_add<<<nb((long)nk * nk * nk * c[k]), TPB, 0, s>>>(U->g_p[k].p, c[k], U->g_cat[k].p, C, c[k + 1], nk);
+        k_pool_bwd_add<<<nb((long)nk * nk * nk * (c[k] / 8)), TPB, 0, s>>>(U->g_p[k].p, c[k], U->g_cat[k].p, C, c[k + 1], nk);
         ULAUNCH();
         const int la = E0A + 2 * k, lb = E0B + 2 * k;
         UCHK(relu_bwd(U, U->g_cat[k].p, C, c[k + 1], U->cat[k].p, C, c[k + 1], c[k], nk));
