@@ -155,7 +155,8 @@ __global__ void __launch_bounds__(256) k_conv3(const bf16 *__restrict__ in, int 
 // free of bank conflicts with the lanes that a 16-byte read takes together (lanes 0-3,
 // 12-15, 20-27; 48 and 80 bytes doubled the LDS cycles).  CW = 32: one
 // v_mfma_f32_16x16x32_bf16 per tap, all lanes on the same tap; a plane's six rows are
-// read once for the three dy, and the weights are loaded a row or two of taps ahead.
+// read once for the three dy, and the weights are loaded
+// a row of taps ahead (NT = 2) or all at once (NT = 1: 17 -> 12 us a layer of the 64^3 network).
 // CW = 16: taps go in pairs, lanes g < 2 on the first and g >= 2 on the second (8
 // channels each), the unpaired 27th tap padded with zeros, all weights loaded first.
 // n must be a multiple of 16 and cin of CW.
@@ -165,7 +166,7 @@ __global__ void __launch_bounds__(256) k_conv3(const bf16 *__restrict__ in, int 
 // Bound by issue and latency: at 16 channels 56 products take 400 other instructions a
 // wave, so blocks that march in z (MARCH) keep weights and addresses; at 32 and 64 by the
 // weights, that every wave reads from L2.  Measured (us): 16 -> 16 at 128^3 131 -> 60;
-// 64 -> 64 at 32^3 50 -> 24 and at 16^3 47 -> 15 (16 channels a block instead of all,
+// 64 -> 64 at 32^3 50 -> 19 and at 16^3 47 -> 12 (16 channels a block instead of all,
 // where tiles are few), 32 -> 32 at 64^3 51 -> 32.  48 -> 16 at 128^3 takes 200, as long
 // with whole voxels staged once.
 constexpr int CT_HX = 18, CT_HY = 6, CT_HZ = 6, CT_HV = CT_HX * CT_HY * CT_HZ;
@@ -220,7 +221,7 @@ __global__ void __launch_bounds__(256, MARCH ? 3 : 2)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) acc[q][t] = floatx4{0.f, 0.f, 0.f, 0.f};
         if constexpr (CW == 32) {
-            constexpr int AHEAD = 3 - NT, RING = AHEAD + 1;
+            constexpr int AHEAD = NT == 1 ? 8 : 1, RING = AHEAD + 1; // NT = 1: all before the staging barrier
             bf16x8 wr[RING][3][NT]; // weights of the rows of taps r .. r + AHEAD
             auto weights = [&](int r) {
 #pragma unroll
