@@ -592,7 +592,7 @@ __device__ void cvb_sweep(double *__restrict__ phi, const double *__restrict__ f
                           double inv_h2, OpConst oc, double Fb, double fs)
 {
     const int half = n >> 1, tot = n * n * half;
-    const SmallDiv dh(half), dn(n);
+    const SmallDiv dh(half, tot), dn(n);
     const double rJ = poisson_inv_diag(inv_h2);
     for (int colour = 0; colour < 2; ++colour) {
         for (int t = threadIdx.x; t < tot; t += NT) {

@@ -22,7 +22,7 @@ __device__ void cv_sweep(T *__restrict__ phi, const T *__restrict__ f, const T *
                          const T *__restrict__ c2, int n, T inv_h2, OpConst oc, T Fb, T fs)
 {
     const int half = n >> 1, tot = n * n * half;
-    const SmallDiv dh(half), dn(n);
+    const SmallDiv dh(half, tot), dn(n);
     const T rJ = poisson_inv_diag(inv_h2);
     for (int colour = 0; colour < 2; ++colour) {
         for (int t = threadIdx.x; t < tot; t += kCoarseThreads) {

@@ -79,16 +79,20 @@ __device__ __forceinline__ T newton_update(T ph, T L, T fe, T J, T rJ)
         return ph - (L - fe) / J;
 }
 
-// t / d for 0 <= t < 2^24: for 1 < d < 2^8 a multiply-high with m = ceil(2^32 / d)
-// (the error term t (m d - 2^32) < 2^24 2^8 keeps the quotient exact), else a division.
+// t / d for 0 <= t < count: for 1 < d < 2^8 and count up to 2^24 a multiply-high with
+// m = ceil(2^32 / d) (the error term t (m d - 2^32) < 2^24 2^8 keeps the quotient exact),
+// else a division.  The x-pairs of a level of side 2 d pass 2^24 from side 323 on.
 struct SmallDiv {
     unsigned m;
     int d;
-    __device__ __forceinline__ explicit SmallDiv(int d_)
-        : m(d_ > 1 && d_ < 256 ? 0xffffffffu / (unsigned)d_ + 1u : 0u), d(d_)
+    __host__ __device__ __forceinline__ explicit SmallDiv(int d_, long count = 1L << 24)
+        : m(d_ > 1 && d_ < 256 && count <= (1L << 24) ? 0xffffffffu / (unsigned)d_ + 1u : 0u), d(d_)
     {
     }
-    __device__ __forceinline__ int div(int t) const { return m ? (int)__umulhi((unsigned)t, m) : t / d; }
+    __host__ __device__ __forceinline__ int div(int t) const
+    {
+        return m ? (int)(((unsigned long long)(unsigned)t * m) >> 32) : t / d;
+    }
 };
 
 template <int KIND, typename T>
