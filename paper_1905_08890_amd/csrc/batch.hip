@@ -1116,7 +1116,8 @@ __global__ void __launch_bounds__(TPB) kb32_prolong(BatchDev D, const int *__res
 }
 
 // the correction cycle from the box's FP32 entry level down, one workgroup per
-// box, computed in FP64 in LDS
+// box, computed in FP64 in LDS; a coarsest level too wide for that (sides 18, 22, ...: such
+// a box enters there) by coarsest_wide, from 30^3 on with the iterate in the level's FP64 scratch
 template <int LKIND>
 __global__ void __launch_bounds__(kCoarseNT) kb32_coarse(BatchDev D, int nu1, int nu2, OpConst oc)
 {
@@ -1125,6 +1126,15 @@ __global__ void __launch_bounds__(kCoarseNT) kb32_coarse(BatchDev D, int nu1, in
     const int b = blockIdx.x;
     if (!D.active[b]) return;
     const BoxDev &X = D.box[b];
+    if (!coarse_lds_need<LKIND, kPeriodic>(X.lev[X.centry32].n, X.nlev - X.centry32)) {
+        const BoxLev &V = X.lev[X.centry32];
+        const double inv_h2 = 1.0 / (V.h * V.h);
+        if (sizeof(double) * V.n * V.n * V.n <= kCoarseLdsBytes)
+            coarsest_wide<LKIND>(lds, V.n, inv_h2, oc, V.b32, V.c32, V.a32, V.e);
+        else
+            coarsest_wide<LKIND>(V.tmp, V.n, inv_h2, oc, V.b32, V.c32, V.a32, V.e);
+        return;
+    }
     if (threadIdx.x == 0) {
         G.nl = X.nlev - X.centry32;
         for (int i = 0; i < G.nl; ++i) {

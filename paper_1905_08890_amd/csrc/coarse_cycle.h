@@ -681,7 +681,9 @@ __device__ void coarse_cycle_body(T *s, const CoarseLevelsT<TG> &G, int nu1, int
     }
 }
 
-// s: the workgroup's LDS, at least coarse_lds_bytes; called by NT threads
+// s: the workgroup's LDS, at least coarse_lds_bytes; called by NT threads.  Only for
+// levels that coarse_lds_need accepts: a larger first level has more pairs than the threads
+// take and runs past the LDS.
 template <int KIND, int BC, int NT, typename TG, typename T>
 __device__ void coarse_cycle_lds(T *s, const CoarseLevelsT<TG> &G, int nu1, int nu2, OpConst oc, T Fb0, T fs0)
 {
@@ -705,6 +707,38 @@ __device__ void coarse_cycle_lds(T *s, const CoarseLevelsT<TG> &G, int nu1, int 
     coarse_cycle_body<KIND, BC, NT, TG, T>(s, G, nu1, nu2, oc, Fb0, fs0);
     const int W0 = G.n[0] + 2 * BC, P0 = W0 * W0 * W0;
     for (int q = threadIdx.x; q < P0; q += NT) G.phi[0][q] = TG(s[q]);
+}
+
+// The coarsest correction level alone, of any side: for levels that the cycle above does
+// not take (a coarsest side above 16 is twice an odd number: 18, 22, 26, ...).  The same 32
+// sweeps and mean, computed in FP64, cells strided over the NT = kCoarseThreads threads.
+// x: N values for the iterate, LDS (sides up to 26) or global memory; e: the correction.
+template <int KIND, typename TG>
+__device__ __forceinline__ void coarsest_wide(double *x, int n, double inv_h2, OpConst oc, const TG *__restrict__ f,
+                                              const TG *__restrict__ c1, const TG *__restrict__ c2, TG *__restrict__ e)
+{
+    const int N = n * n * n, half = n >> 1, tot = n * n * half;
+    const SmallDiv dh(half, tot), dn(n);
+    const double rJ = poisson_inv_diag(inv_h2);
+    for (int q = threadIdx.x; q < N; q += kCoarseThreads) x[q] = (double)e[q];
+    __syncthreads();
+    for (int h = 0; h < 2 * kCoarseSweeps; ++h) {
+        for (int t = threadIdx.x; t < tot; t += kCoarseThreads) {
+            const int r = dh.div(t), z = dn.div(r), y = r - z * n;
+            const int i = 2 * (t - r * half) + ((y + z + h) & 1);
+            const long p = lin(i, y, z, n);
+            const double ph = x[p];
+            double J;
+            const double L = op_point<KIND, double>(ph, nb_sum(x, i, y, z, n), inv_h2, (double)load_c1<KIND>(c1, p),
+                                                    (double)load_c2<KIND>(c2, p), oc, 0.0, J);
+            x[p] = newton_update<KIND, double>(ph, L, (double)f[p], J, rJ);
+        }
+        __syncthreads();
+    }
+    double d = 0.0;
+    for (int q = threadIdx.x; q < N; q += kCoarseThreads) d += x[q] - (double)e[q];
+    const double mean = cv_block_sum(d) / (double)N;
+    for (int q = threadIdx.x; q < N; q += kCoarseThreads) e[q] = TG(x[q] - mean);
 }
 
 } // namespace detail

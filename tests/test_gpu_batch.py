@@ -348,3 +348,38 @@ def test_batch_queue_with_tuned_forms(precision, monkeypatch):
             assert maxrel(Q.get_field(0, name), fields[name]) < 1e-12, name
         st = Q.solve(allow=(grmg.OK, grmg.EINVAL), rtol=1e-10, nu1=9, nu2=2)
         assert st["status"] == grmg.EINVAL
+
+
+def test_batch_mixed_with_wide_coarsest_levels():
+    """Boxes whose coarsest level is 18^3 or wider (sides that are 2^k times an odd
+    number from 9 on): every cell of that level takes part in the correction.  The bars
+    of the usual sides: refined to 1e-12 within 1e-9 of the FP64 solution, and at 1e-10
+    within two steps of the FP64 cycles without the FP64 fallback; 30^3 and 60^3
+    have their coarsest iterate outside the LDS."""
+    sides = [18, 36, 44, 72, 30, 60, 32]
+    print(f"[gpu] batch mixed, wide coarsest levels {sides}", flush=True)
+    A = grmg.Batch(sides, **PRM)
+    M = grmg.Batch(sides, **PRM)
+    for i, n in enumerate(sides):
+        for name, v in zip(("s0", "sx", "sy", "sz", "sm"), synth._matter_sources(n, 820 + i, 0.4)):
+            A.set_field(i, name, v)
+            M.set_field(i, name, v)
+    ra = A.solve(rtol=1e-13, max_cycles=200, allow=(grmg.OK, grmg.ENOTCONV))
+    rm = M.solve(rtol=1e-12, max_cycles=200, precision="mixed")
+    assert rm["status"] == grmg.OK
+    for i in range(len(sides)):
+        assert max(ra["rel_res"][i]) <= 1e-12, i
+        for f in range(10):
+            ref, got = A.get_field(i, f), M.get_field(i, f)
+            assert float((got - ref).abs().max()) <= 1e-9 * float(ref.abs().max()), (i, f)
+    r64 = A.solve(rtol=1e-10, max_cycles=200)
+    r32 = M.solve(rtol=1e-10, max_cycles=200, precision="mixed")
+    assert r64["status"] == r32["status"] == grmg.OK
+    for i, n in enumerate(sides):
+        # a refinement step that keeps more than half of the residual twice in a row goes to FP64 by rule:
+        # the 32 red-black sweeps of a coarsest side m keep this much of its longest wave
+        m = n // (n & -n) * 2
+        if ((2.0 + np.cos(2.0 * np.pi / m)) / 3.0) ** 64 < 0.5:   # up to m = 22
+            assert not any(r32["fallback"][i]), (i, r32["fallback"][i], r32["cycles"][i])
+        for f in range(10):
+            assert abs(r32["cycles"][i][f] - r64["cycles"][i][f]) <= 2, (i, f, r32["cycles"][i], r64["cycles"][i])
