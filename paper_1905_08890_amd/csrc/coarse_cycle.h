@@ -205,7 +205,11 @@ constexpr int kPeriodic = 0, kFaces = 1;
 constexpr size_t kCoarseLdsBytes = 150 * 1024;
 constexpr size_t kCoarseLdsSmall = 20 * 1024; // enough for levels up to 8^3 of every kind
 constexpr int kCoarseLdsN = 16;                   // largest level: 2 pairs per thread of 1024
+constexpr int kCoarseLdsWideN = 20;               // the same with 4 pairs per thread
 constexpr int kCoarseNT = 1024, kCoarseNTSmall = 256;
+static_assert(kCoarseLdsN * kCoarseLdsN * kCoarseLdsN / 2 <= 2 * kCoarseNT &&
+                  kCoarseLdsWideN * kCoarseLdsWideN * kCoarseLdsWideN / 2 <= 4 * kCoarseNT && 8 * 8 * 8 / 2 <= kCoarseNTSmall,
+              "a thread has a place for each of its pairs");
 static_assert(kCoarseSweeps >= 20, "the closed form of the 2^3 Poisson sweeps");
 
 // Offsets (in values) of one level's arrays in LDS.
@@ -243,10 +247,10 @@ template <int KIND, int BC> __host__ __device__ inline size_t coarse_lds_bytes(i
     return (size_t)lds_level<KIND, BC>(n0, nl - 1).end * sizeof(double);
 }
 
-// bytes of LDS, or 0 where the cycle does not fit
-template <int KIND, int BC> __host__ __device__ inline size_t coarse_lds_need(int n0, int nl)
+// bytes of LDS, or 0 where the cycle does not fit (largest: the side that the threads take)
+template <int KIND, int BC> __host__ __device__ inline size_t coarse_lds_need(int n0, int nl, int largest = kCoarseLdsN)
 {
-    if (n0 > kCoarseLdsN) return 0;
+    if (n0 > largest) return 0;
     const size_t b = coarse_lds_bytes<KIND, BC>(n0, nl);
     return b <= kCoarseLdsBytes ? b : 0;
 }
@@ -537,13 +541,13 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-template <int KIND, int BC, int NT, typename TG, typename T>
+// CPL: pairs per thread of the largest level (2 for 16^3 and 4 for 20^3 with 1024 threads, 1 for 8^3 with 256)
+template <int KIND, int BC, int NT, int CPL, typename TG, typename T>
 __device__ void coarse_cycle_body(T *s, const CoarseLevelsT<TG> &G, int nu1, int nu2, OpConst oc, const T Fb0,
                                   const T fs0)
 {
     constexpr bool LIN = KIND >= K_LIN_POISSON;
     constexpr int NC = kNumCoef<KIND>();
-    constexpr int CPL = NT >= 1024 ? 2 : 1; // pairs per thread of the largest level (16^3; 8^3 with 256 threads)
     const int L = G.nl, n0 = G.n[0];
     // down to the coarsest level and back up in one loop: every phase's code is there once
 #pragma unroll 1
@@ -684,7 +688,7 @@ __device__ void coarse_cycle_body(T *s, const CoarseLevelsT<TG> &G, int nu1, int
 // s: the workgroup's LDS, at least coarse_lds_bytes; called by NT threads.  Only for
 // levels that coarse_lds_need accepts: a larger first level has more pairs than the threads
 // take and runs past the LDS.
-template <int KIND, int BC, int NT, typename TG, typename T>
+template <int KIND, int BC, int NT, typename TG, typename T, int CPL = (NT >= 1024 ? 2 : 1)>
 __device__ void coarse_cycle_lds(T *s, const CoarseLevelsT<TG> &G, int nu1, int nu2, OpConst oc, T Fb0, T fs0)
 {
     constexpr int NC = kNumCoef<KIND>();
@@ -704,7 +708,7 @@ __device__ void coarse_cycle_lds(T *s, const CoarseLevelsT<TG> &G, int nu1, int 
         }
     }
     __syncthreads();
-    coarse_cycle_body<KIND, BC, NT, TG, T>(s, G, nu1, nu2, oc, Fb0, fs0);
+    coarse_cycle_body<KIND, BC, NT, CPL, TG, T>(s, G, nu1, nu2, oc, Fb0, fs0);
     const int W0 = G.n[0] + 2 * BC, P0 = W0 * W0 * W0;
     for (int q = threadIdx.x; q < P0; q += NT) G.phi[0][q] = TG(s[q]);
 }

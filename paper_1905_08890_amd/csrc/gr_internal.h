@@ -84,8 +84,9 @@ template <typename T> struct CoarseLevelsT {
 void launch_coarse_vcycle(int kind, hipStream_t s, const CoarseLevelsT<double> &C, int nu1, int nu2, OpConst oc,
                           const double *fbar0, const double *fshift0, const int *stop = nullptr);
 bool coarse_cycle_in_lds(int kind, int n0, int nl); // whether launch_coarse_vcycle runs from LDS
+// wide: FP64 scratch of the coarsest level's size, for one that does not fit the LDS
 void launch_coarse_vcycle_f32(int kind, hipStream_t s, const CoarseLevelsT<float> &C, int nu1, int nu2, OpConst oc,
-                              const double *zero);
+                              const double *zero, double *wide);
 
 // ---- small_level.hip: a whole leg of the V-cycle on a small level in one launch ----
 // (nu = 1 or 2 sweeps, n even, 8 or at least 12, at most 64; in and out are different arrays, in may be null for a

@@ -742,7 +742,7 @@ int vcycle32_body(gr_grid g, int lkind, int l, int nu1, int nu2, OpConst oc, boo
             C.c2[i] = W.a;
             C.tmp[i] = W.tmp;
         }
-        launch_coarse_vcycle_f32(lkind, s, C, nu1, nu2, oc, g->scal + S_ZERO);
+        launch_coarse_vcycle_f32(lkind, s, C, nu1, nu2, oc, g->scal + S_ZERO, g->lev[g->nlev - 1].phi0);
         LAUNCHCHK();
         return GR_OK;
     }

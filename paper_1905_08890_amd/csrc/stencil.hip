@@ -665,7 +665,7 @@ __global__ void __launch_bounds__(CTPB) k_coarse_vcycle(CoarseLevelsT<T> C, int 
     coarse_vcycle_body<KIND, T>(C, nu1, nu2, oc, T(*fbar0), T(*fshift0));
 }
 
-template <int KIND, typename TG, int NT, size_t BYTES>
+template <int KIND, typename TG, int NT, int CPL, size_t BYTES>
 __global__ void __launch_bounds__(NT) k_coarse_vcycle_lds(CoarseLevelsT<TG> G, int nu1, int nu2, OpConst oc,
                                                           const double *__restrict__ fbar0,
                                                           const double *__restrict__ fshift0,
@@ -673,7 +673,18 @@ __global__ void __launch_bounds__(NT) k_coarse_vcycle_lds(CoarseLevelsT<TG> G, i
 {
     __shared__ double s[BYTES / sizeof(double)];
     if (stop && *stop) return;
-    coarse_cycle_lds<KIND, kPeriodic, NT, TG, double>(s, G, nu1, nu2, oc, *fbar0, *fshift0);
+    coarse_cycle_lds<KIND, kPeriodic, NT, TG, double, CPL>(s, G, nu1, nu2, oc, *fbar0, *fshift0);
+}
+
+// x: the iterate's FP64 scratch where it does not fit the LDS, else null
+template <int KIND>
+__global__ void __launch_bounds__(CTPB) k_coarsest_wide(float *__restrict__ e, const float *__restrict__ f,
+                                                        const float *__restrict__ c1, const float *__restrict__ c2, int n,
+                                                        double inv_h2, OpConst oc, double *__restrict__ x)
+{
+    __shared__ double s[kCoarseLdsBytes / sizeof(double)];
+    if (x) coarsest_wide<KIND>(x, n, inv_h2, oc, f, c1, c2, e);
+    else coarsest_wide<KIND>(s, n, inv_h2, oc, f, c1, c2, e);
 }
 
 // ------------------------------------------------ mixed-precision outer steps
@@ -1403,17 +1414,24 @@ bool coarse_cycle_in_lds(int kind, int n0, int nl)
                                    : coarse_lds_need<GR_KIND_HAMILTONIAN, kPeriodic>(n0, nl) != 0;
 }
 
-// the cycle from LDS where its levels fit (GRMG_COARSE_LDS=0: never)
+// The cycle from LDS where its levels fit (GRMG_COARSE_LDS=0: never).  Four pairs a thread above
+// 16^3, for the FP32 corrections alone, so that those levels too are solved in FP64: 18^3 (the coarsest level
+// of sides 18, 36, 72, ...) of the Poisson and CMC kinds, and 20^3 where a threshold asks for it.
 template <int KIND, typename TG>
 static bool coarse_in_lds(hipStream_t s, const CoarseLevelsT<TG> &C, int nu1, int nu2, OpConst oc, const double *fbar0,
                           const double *fshift0, const int *stop)
 {
-    if (!coarse_lds_on() || !coarse_lds_need<KIND, kPeriodic>(C.n[0], C.nl)) return false;
+    constexpr bool LIN = KIND >= K_LIN_POISSON;
+    if (!coarse_lds_on() || !coarse_lds_need<KIND, kPeriodic>(C.n[0], C.nl, LIN ? kCoarseLdsWideN : kCoarseLdsN))
+        return false;
     if (C.n[0] <= 8)
-        k_coarse_vcycle_lds<KIND, TG, kCoarseNTSmall, kCoarseLdsSmall>
+        k_coarse_vcycle_lds<KIND, TG, kCoarseNTSmall, 1, kCoarseLdsSmall>
             <<<1, kCoarseNTSmall, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0, stop);
-    else
-        k_coarse_vcycle_lds<KIND, TG, kCoarseNT, kCoarseLdsBytes>
+    else if (C.n[0] <= kCoarseLdsN)
+        k_coarse_vcycle_lds<KIND, TG, kCoarseNT, 2, kCoarseLdsBytes>
+            <<<1, kCoarseNT, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0, stop);
+    else if constexpr (LIN)
+        k_coarse_vcycle_lds<KIND, TG, kCoarseNT, 4, kCoarseLdsBytes>
             <<<1, kCoarseNT, 0, s>>>(C, nu1, nu2, oc, fbar0, fshift0, stop);
     return true;
 }
@@ -1429,14 +1447,29 @@ void launch_coarse_vcycle(int kind, hipStream_t s, const CoarseLevelsT<double> &
 }
 
 void launch_coarse_vcycle_f32(int kind, hipStream_t s, const CoarseLevelsT<float> &C, int nu1, int nu2, OpConst oc,
-                              const double *zero)
+                              const double *zero, double *wide)
 {
-    // FP32 arrays, the cycle in FP64 in LDS (the global-memory fallback, for
-    // thresholds whose levels do not fit, computes in FP32)
-    const bool done = kind == K_LIN_POISSON ? coarse_in_lds<K_LIN_POISSON>(s, C, nu1, nu2, oc, zero, zero, nullptr)
-                      : kind == K_LIN_HAM ? coarse_in_lds<K_LIN_HAM>(s, C, nu1, nu2, oc, zero, zero, nullptr)
-                                          : coarse_in_lds<K_LIN_CMC>(s, C, nu1, nu2, oc, zero, zero, nullptr);
-    if (!done) GR_DISPATCH_KT(kind, float, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, zero, zero);
+    // FP32 arrays, the cycle in FP64
+    if (kind == K_LIN_POISSON ? coarse_in_lds<K_LIN_POISSON>(s, C, nu1, nu2, oc, zero, zero, nullptr)
+        : kind == K_LIN_HAM   ? coarse_in_lds<K_LIN_HAM>(s, C, nu1, nu2, oc, zero, zero, nullptr)
+                              : coarse_in_lds<K_LIN_CMC>(s, C, nu1, nu2, oc, zero, zero, nullptr))
+        return;
+    // A coarsest level alone that does not fit there (sides 18, 22, 26, ...): one cycle of a
+    // Poisson field at 44^3 296 us, 444 in FP32 from global memory, at 30^3 (iterate in
+    // global memory) 691 and 683; 18^3 takes 123 from LDS and 184 this way.
+    const int n = C.n[0];
+    if (C.nl == 1 && n > kCoarseLdsN && coarse_lds_on()) {
+        double *x = sizeof(double) * n * n * n <= kCoarseLdsBytes ? nullptr : wide;
+        if (kind == K_LIN_POISSON)
+            k_coarsest_wide<K_LIN_POISSON><<<1, CTPB, 0, s>>>(C.phi[0], C.f[0], nullptr, nullptr, n, C.inv_h2[0], oc, x);
+        else if (kind == K_LIN_HAM)
+            k_coarsest_wide<K_LIN_HAM><<<1, CTPB, 0, s>>>(C.phi[0], C.f[0], C.c1[0], C.c2[0], n, C.inv_h2[0], oc, x);
+        else
+            k_coarsest_wide<K_LIN_CMC><<<1, CTPB, 0, s>>>(C.phi[0], C.f[0], C.c1[0], nullptr, n, C.inv_h2[0], oc, x);
+        return;
+    }
+    // thresholds (GRMG_COARSE_N32, GRMG_COARSE_NP) whose levels do not fit: in FP32 from global memory
+    GR_DISPATCH_KT(kind, float, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, zero, zero);
 }
 
 void launch_ir_residual(int kind, hipStream_t s, const double *phi, const double *f, const double *coef, int n,

@@ -134,3 +134,57 @@ def test_c3_all_fields_256_mixed_vs_fp64_floor():
     assert O.cycle_residual(O.HAMILTONIAN, psi, 1.5 * p.a * p.omega_m * (s0 - 1.0), AA, prm=p) <= 1.0001e-12
     m2, fxi = O.build_cmc(psi, s0, gm.get_field("sm").cpu().numpy(), AA, prm=p)
     assert O.cycle_residual(O.CMC, gm.get_field("xi").cpu().numpy(), fxi, m2, prm=p) <= 1.0001e-12
+
+
+@pytest.mark.parametrize("how", ["grid", "batch"])
+@pytest.mark.parametrize("n", [6, 10, 14, 18, 22, 30])
+def test_coarsest_correction_is_computed_in_fp64(n, how):
+    """A side that is twice an odd number is its own coarsest level: one refinement step
+    from a zero field is the 32 sweeps of the correction, less their mean.  The source here is
+    exact in FP32, so computed in FP64 the step is the oracle's sweeps with one rounding to
+    FP32 at the end: 2^-24 of the value itself, and of the largest value for the mean of
+    the rounded correction.  Sweeps in FP32 leave several times that."""
+    print(f"[gpu] coarsest correction {how} n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    k = rng.integers(-512, 512, n ** 3 // 2)
+    k = np.concatenate([k, -k])   # zero mean, exactly
+    rng.shuffle(k)
+    s = (k / 1024.0).reshape(n, n, n)
+    prm = dict(a=1.0, omega_m=0.25, c_tilde=synth.C_TILDE)   # the source of V_x is 0.75 s
+    if how == "grid":
+        g = grmg.Grid(n, **prm)
+        g.set_field("rhs", 0.75 * s)
+        g.solve_equation(O.POISSON, "Vx", rtol=0, max_cycles=1, precision="mixed")
+        out = g.get_field("Vx").cpu().numpy()
+    else:
+        B = grmg.Batch([n], **prm)
+        for name, v in zip(("s0", "sx", "sy", "sz", "sm"), (np.ones_like(s), s, s, s, np.zeros_like(s))):
+            B.set_field(0, name, v)
+        B.solve(rtol=0, max_cycles=1, precision="mixed")
+        out = B.get_field(0, "Vx").cpu().numpy()
+    ref = np.zeros_like(s)
+    for _ in range(32):
+        ref = O.rb_sweep(O.POISSON, ref, 0.75 * s, prm=O.params(**prm))
+    ref = ref - ref.mean()
+    eps = 2.0 ** -24
+    assert np.all(np.abs(out - ref) <= eps * np.abs(ref) + 0.1 * eps * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("n", [18, 36, 44, 72])
+def test_mixed_solves_of_sides_with_a_wide_coarsest_level(n):
+    """Sides whose coarsest level is 18^3 or 22^3: the refinement steps stay within two of
+    the FP64 cycles, without fallback, and the fields agree."""
+    print(f"[gpu] mixed, wide coarsest level n={n}", flush=True)
+    g = grmg.Grid(n, **DEFAULT)
+    for name, v in zip(("s0", "sx", "sy", "sz", "sm"), synth._matter_sources(n, 840 + n, 0.4)):
+        g.set_field(name, v)
+    r64 = g.solve_constraints(rtol=1e-10)
+    r32 = g.solve_constraints(rtol=1e-10, precision="mixed")
+    assert r32["fallback"] == 0
+    assert all(abs(a - b) <= 2 for a, b in zip(r32["cycles"], r64["cycles"])), (r32["cycles"], r64["cycles"])
+    g.solve_constraints(rtol=1e-12)
+    ref = [g.get_field(f) for f in range(10)]
+    g.solve_constraints(rtol=1e-12, precision="mixed")
+    for f in range(10):
+        x = g.get_field(f)
+        assert float((x - ref[f]).abs().max()) <= MIXED_TOL * float(ref[f].abs().max()), f
