@@ -70,6 +70,9 @@ struct Axis {
 // particle touch: the 8 cloud corners as corner(p, w, wx, wy, wz), the weights
 // of the value and of the three differences, and per axis the 8 outer cells as
 // outer(axis, p, w).  (Corner by corner the differences would read 8 x 6 cells.)
+// The weights of a difference sum to zero, so the callers take the values relative to
+// the cloud's first corner: they then round like differences of neighbours, not
+// like the values themselves.
 // One z plane per trip of a loop that is kept: with all 32 cells' loads in flight
 // the kick needs 354 registers (one wavefront per SIMD).
 template <class C, class O>
@@ -153,11 +156,14 @@ __global__ void __launch_bounds__(TPB) k_kick(Metric M, double a, double c, cons
     double uq[3] = {u[3 * q], u[3 * q + 1], u[3 * q + 2]};
     double Phi = 0.0, Psi = 0.0;
     double g[5][3] = {}; // d_i of Phi, Psi, beta^x, beta^y, beta^z, times 2h
+    const long p0 = X.i[1] + ((long)Z.i[1] * M.n + Y.i[1]) * M.n;
+    const double2 s0 = M.pp[p0], v0 = M.bxy[p0];
+    const double z0 = M.bz[p0];
     visit_cloud(
         X, Y, Z, M.n,
         [&](long p, double w, double wx, double wy, double wz) {
             const double2 s = M.pp[p], v = M.bxy[p];
-            const double f[5] = {s.x, s.y, v.x, v.y, M.bz[p]};
+            const double f[5] = {s.x - s0.x, s.y - s0.y, v.x - v0.x, v.y - v0.y, M.bz[p] - z0};
             Phi += w * s.x;
             Psi += w * s.y;
 #pragma unroll
@@ -169,7 +175,7 @@ __global__ void __launch_bounds__(TPB) k_kick(Metric M, double a, double c, cons
         },
         [&](int d, long p, double w) {
             const double2 s = M.pp[p], v = M.bxy[p];
-            const double f[5] = {s.x, s.y, v.x, v.y, M.bz[p]};
+            const double f[5] = {s.x - s0.x, s.y - s0.y, v.x - v0.x, v.y - v0.y, M.bz[p] - z0};
 #pragma unroll
             for (int k = 0; k < 5; ++k) g[k][d] += w * f[k];
         });
@@ -242,15 +248,16 @@ __global__ void __launch_bounds__(TPB) k_newton_kick(int n, const double *__rest
     if (q >= np) return;
     const Axis X(pos[3 * q], n), Y(pos[3 * q + 1], n), Z(pos[3 * q + 2], n);
     double grad[3] = {0.0, 0.0, 0.0};
+    const double f0 = phiN[X.i[1] + ((long)Z.i[1] * n + Y.i[1]) * n];
     visit_cloud(
         X, Y, Z, n,
         [&](long p, double, double wx, double wy, double wz) {
-            const double f = phiN[p];
+            const double f = phiN[p] - f0;
             grad[0] += wx * f;
             grad[1] += wy * f;
             grad[2] += wz * f;
         },
-        [&](int d, long p, double w) { grad[d] += w * phiN[p]; });
+        [&](int d, long p, double w) { grad[d] += w * (phiN[p] - f0); });
     for (int d = 0; d < 3; ++d) u[3 * q + d] -= dt * (grad[d] * inv2h);
 }
 
