@@ -252,7 +252,6 @@ __global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, doubl
         ps[i] = psi[lin(x[0], x[1], x[2], n)];
     }
     __syncthreads();
-    const double h = 1.0 / n, vol = h * h * h, qs = mass / (c * vol);
     for (unsigned e = first + threadIdx.x; e < last; e += DNT) {
         const long q = list[e];
         int i0[3], i1[3], at[3];
@@ -278,7 +277,7 @@ __global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, doubl
         const double chi2 = chi * chi;
         const double g_uu = (ux * ux + uy * uy + uz * uz) / (a * a * chi2 * chi2); // gamma^ij u_i u_j
         const double W = sqrt(c * c + g_uu);
-        const double Q[5] = {qs * W, qs * ux, qs * uy, qs * uz, qs * (g_uu / W)}; // the last: stress trace gamma^ij s_ij
+        const double Q[5] = {W, ux, uy, uz, g_uu / W}; // times mass / (c h^3); the last: stress trace gamma^ij s_ij
 #pragma unroll
         for (int cc = 0; cc < 8; ++cc) {
             const int ox = cc & 1, oy = (cc >> 1) & 1, oz = cc >> 2;
@@ -290,13 +289,18 @@ __global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, doubl
         }
     }
     __syncthreads();
+    // the common factor once a point, not rounded into one factor: a lattice of particles at rest gives exactly 1
+    const double h = 1.0 / n, cvol = c * (h * h * h);
     double *const out[5] = {s0, sx, sy, sz, sm};
     for (int r = threadIdx.x; r < DP; r += DNT) {
         const int x = DT * T[0] + r % DT, y = DT * T[1] + (r / DT) % DT, z = DT * T[2] + r / (DT * DT);
         if (x >= n || y >= n || z >= n) continue;
         const long g = lin(x, y, z, n);
 #pragma unroll
-        for (int f = 0; f < 5; ++f) out[f][g] = ADD ? out[f][g] + acc[f][r] : acc[f][r];
+        for (int f = 0; f < 5; ++f) {
+            const double v = mass * acc[f][r] / cvol;
+            out[f][g] = ADD ? out[f][g] + v : v;
+        }
     }
 }
 

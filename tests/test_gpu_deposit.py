@@ -54,3 +54,17 @@ def test_one_dense_lump():
     pos = rng.uniform(0, 1, (8000, 3))
     pos[:6000] = 0.3 + 0.01 * rng.standard_normal((6000, 3))
     _check(n, pos, 3)
+
+
+@pytest.mark.parametrize("n", [8, 16, 32])
+@pytest.mark.parametrize("c_tilde", [49.0, 2997.92458 / 256.0, 1.5])
+def test_lattice_at_rest_gives_exactly_one(n, c_tilde):
+    """A particle of mass n^-3 at rest at every cell centre: every factor of s0 =
+    m W / (c h^3) with W = c is exact, so s0 is 1 and the other sources 0, to the bit."""
+    print(f"[gpu] deposit, lattice at rest n={n} c={c_tilde}", flush=True)
+    g = grmg.Grid(n, a=1.0, omega_m=0.3, c_tilde=c_tilde)
+    x = (np.arange(n) + 0.5) / n
+    pos = np.stack([a.ravel() for a in np.meshgrid(x, x, x, indexing="ij")], axis=1)
+    g.deposit_sources(pos, np.zeros_like(pos), 1.0 / n ** 3)
+    for name, want in zip(("s0", "sx", "sy", "sz", "sm"), (1.0, 0.0, 0.0, 0.0, 0.0)):
+        assert np.all(g.get_field(name).cpu().numpy() == want), name
