@@ -83,7 +83,7 @@ struct gr_grid_s {
     // components 1 and 2 of a vector equation concurrently with component 0.
     bool solver_only = false;
     gr_grid_s *sub[2]{};
-    void *cic = nullptr;    // cell-ordered deposit scratch for up to n^3 particles
+    void *cic = nullptr;    // the deposit's tile lists; the autotuner's operands
     double *partials = nullptr;
     double *scal = nullptr;
     hipStream_t stream = nullptr;
@@ -173,6 +173,10 @@ int num_levels(int n)
     return L;
 }
 
+// fine FP64 arrays that gr_autotune lays over the deposit's scratch: iterate in and out,
+// source, coefficient (the five FP32 arrays of the correction kinds take less)
+constexpr size_t kTuneArrays = 4;
+
 // Carve the workspace; with base == nullptr only count bytes.
 size_t layout(gr_grid g, char *base)
 {
@@ -199,7 +203,8 @@ size_t layout(gr_grid g, char *base)
         for (int f = 0; f < 10; ++f) g->alt[f] = take(fb);
         for (int f = 0; f < 10; ++f) g->hist[f] = take(fb);
         g->gtmp = take(3 * fb / 4);
-        g->cic = take(cic_bytes(g->n));
+        // the lists stop growing at 2^28 particles, the autotuner's four operands do not
+        g->cic = take(std::max(cic_bytes(g->n), kTuneArrays * fb));
     }
     for (int l = 0; l < g->nlev; ++l) {
         Level &L = g->lev[l];
@@ -1710,7 +1715,7 @@ int gr_autotune(gr_grid g, char *report, size_t report_bytes)
         // every level the fused sweep can tile (the size threshold is for untuned grids)
         if (!g->fused || !fused_sweep_ok(L.n, 32)) continue;
         const long M = L.N;
-        double *d = static_cast<double *>(g->cic); // scratch: 8 n^3 doubles
+        double *d = static_cast<double *>(g->cic); // scratch: kTuneArrays n^3 doubles
         float *fl = static_cast<float *>(g->cic);
         for (int kind = 0; kind < 6 && st == GR_OK; ++kind) {
             FusedCfg best = g->fcfg;

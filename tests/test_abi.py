@@ -171,3 +171,29 @@ def test_multiply_high_division_is_exact_where_the_coarse_cycle_uses_it():
         t = np.concatenate([small, stride, edges])
         q = (t * m) >> np.uint64(32)
         assert np.array_equal(q, t // np.uint64(d)), d
+
+
+def _hierarchy_bytes(n):
+    """Level arrays of one solver hierarchy: FP64 source, coefficient, scratch, R phi
+    and (below the finest level) the iterate; five FP32 arrays; reductions."""
+    total, side, finest = 8 * 4 * 4096 + 8 * 32, n, True
+    while True:
+        total += side ** 3 * (8 * (4 if finest else 5) + 4 * 5)
+        if side % 4:
+            return total
+        side, finest = side // 2, False
+
+
+@pytest.mark.parametrize("n", [256, 512, 640, 672, 768, 1024])
+def test_workspace_holds_the_autotuners_operands(n):
+    """The autotuner times sweeps on four fine FP64 arrays laid over the deposit's
+    scratch: what the other arrays (45 3/4 fine ones, three hierarchies) leave of the
+    workspace holds them at every side."""
+    g = grmg.create_grid(n, 1.0, 0.3072, 11.7)
+    try:
+        left = grmg.workspace_bytes(g) - int(45.75 * 8 * n ** 3) - 3 * _hierarchy_bytes(n)
+    finally:
+        grmg.destroy_grid(g)
+    slack = 256 * 256   # the arrays start at multiples of 256 bytes
+    assert left >= 4 * 8 * n ** 3
+    assert left <= max(64 * n ** 3, 4 * 8 * n ** 3) + n ** 3 // 8 + slack + (1 << 20)
