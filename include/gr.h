@@ -154,8 +154,10 @@ int gr_create_grid(const gr_grid_desc *desc, const gr_params *prm, gr_grid *out)
 /* Bytes of device workspace the grid needs (all levels, all fields). */
 int gr_workspace_bytes(gr_grid g, size_t *bytes);
 
-/* Bind caller-owned device memory (>= gr_workspace_bytes, 256-byte aligned)
- * and a hipStream_t (may be NULL).  Zero-fills every field and source.
+/* Bind caller-owned device memory (gr_workspace_bytes, 256-byte aligned)
+ * and a hipStream_t (may be NULL).  Below 64^3 a smaller workspace is taken too,
+ * down to what the fields, levels and one pass of 2 n^3 particles need: vector
+ * equations then solve their components in turn and large deposits take more passes.  Zero-fills every field and source.
  * Re-binding replaces both. */
 int gr_bind(gr_grid g, void *d_workspace, size_t bytes, void *hip_stream);
 

@@ -210,11 +210,13 @@ void launch_extrapolate(hipStream_t s, double *field, double *hist, double *alt,
 void launch_cubic_pass(hipStream_t s, const double *in, int nx, int ny, int nz, int dim, double *out);
 
 // ---- sources.hip launchers ----
-// CIC deposit of any number of particles; scratch of cic_bytes(n), 16-byte aligned
-size_t cic_bytes(int n);
+// CIC deposit of any number of particles, `pass` of them at a time; scratch of
+// cic_bytes(n, pass), 16-byte aligned
+long cic_pass(int n, bool small);
+size_t cic_bytes(int n, long pass);
 void launch_cic_deposit(hipStream_t s, int n, double a, double c_tilde, const double *pos, const double *u,
-                        double mass, long np, const double *psi, void *scratch, double *s0, double *sx, double *sy,
-                        double *sz, double *sm);
+                        double mass, long np, const double *psi, void *scratch, long pass, double *s0, double *sx,
+                        double *sy, double *sz, double *sm);
 void launch_shift_scale(hipStream_t s, double *out, const double *in, long N, double scale,
                         const double *mean);
 void launch_div_quarter(hipStream_t s, double *out, const double *gx, const double *gy, const double *gz,

@@ -83,7 +83,8 @@ struct gr_grid_s {
     // components 1 and 2 of a vector equation concurrently with component 0.
     bool solver_only = false;
     gr_grid_s *sub[2]{};
-    void *cic = nullptr;    // the deposit's tile lists; the autotuner's operands
+    void *cic = nullptr;    // the deposit's tile lists (cic_pass particles); the autotuner's operands
+    long cic_pass = 0;
     double *partials = nullptr;
     double *scal = nullptr;
     hipStream_t stream = nullptr;
@@ -101,7 +102,11 @@ struct gr_grid_s {
     int skew = 0;          // workspace array skew in bytes (see layout)
     double stall_ratio = 0.5; // mixed precision: a refinement step that keeps more than this
                               // fraction of the residual counts as stalled (two in a row: FP64)
-    size_t ws_bytes = 0;
+    // A workspace of ws_bytes is what the grid asks for; from ws_least on it is taken all
+    // the same, without what only saves time (small: the helper hierarchies of a grid below
+    // 64^3, long deposit passes on small grids).
+    size_t ws_bytes = 0, ws_least = 0;
+    bool small = false;
     // Solves run on a private stream (joined to the caller's by events) so that
     // each cycle body can be captured once into a hipGraph and replayed.
     hipStream_t user_stream = nullptr;
@@ -178,7 +183,7 @@ int num_levels(int n)
 constexpr size_t kTuneArrays = 4;
 
 // Carve the workspace; with base == nullptr only count bytes.
-size_t layout(gr_grid g, char *base)
+size_t layout(gr_grid g, char *base, bool small = false)
 {
     size_t off = 0;
     int count = 0;
@@ -204,7 +209,8 @@ size_t layout(gr_grid g, char *base)
         for (int f = 0; f < 10; ++f) g->hist[f] = take(fb);
         g->gtmp = take(3 * fb / 4);
         // the lists stop growing at 2^28 particles, the autotuner's four operands do not
-        g->cic = take(std::max(cic_bytes(g->n), kTuneArrays * fb));
+        g->cic_pass = cic_pass(g->n, small);
+        g->cic = take(std::max(cic_bytes(g->n, g->cic_pass), kTuneArrays * fb));
     }
     for (int l = 0; l < g->nlev; ++l) {
         Level &L = g->lev[l];
@@ -227,7 +233,7 @@ size_t layout(gr_grid g, char *base)
     g->partials = take(sizeof(double) * kReduceBlocks * 4);
     g->scal = take(sizeof(double) * S_NUM);
     for (auto *h : g->sub)
-        if (h) off += align_up(layout(h, base ? base + off : nullptr));
+        if (h && !(small && g->n < 64)) off += align_up(layout(h, base ? base + off : nullptr));
     return off;
 }
 
@@ -1114,7 +1120,7 @@ int gr_create_grid(const gr_grid_desc *desc, const gr_params *prm, gr_grid *out)
     // GRMG_CONCURRENT=0: solve the components of vector equations one after another
     // Above 32^3: the three components of a 48^3 vector equation take 3.0 instead of 5.7 ms.
     // On smaller grids, where a solve is ~1 ms, the helpers' arrays would add a quarter to
-    // the workspace.
+    // the workspace (below 64^3 they add a fifth; a smaller workspace is bound without them).
     bool conc = n > 32;
     if (const char *e = std::getenv("GRMG_CONCURRENT")) conc = conc && std::atoi(e) != 0;
     if (conc)
@@ -1146,6 +1152,7 @@ int gr_create_grid(const gr_grid_desc *desc, const gr_params *prm, gr_grid *out)
             h->skew = g->skew;
         }
     g->ws_bytes = layout(g, nullptr);
+    g->ws_least = layout(g, nullptr, true);
     *out = g;
     return GR_OK;
 }
@@ -1160,7 +1167,7 @@ int gr_workspace_bytes(gr_grid g, size_t *bytes)
 int gr_bind(gr_grid g, void *d_ws, size_t bytes, void *stream)
 {
     if (!g || !d_ws) return fail(GR_EINVAL, "null argument");
-    if (bytes < g->ws_bytes) return fail(GR_EINVAL, "workspace %zu bytes < required %zu", bytes, g->ws_bytes);
+    if (bytes < g->ws_least) return fail(GR_EINVAL, "workspace %zu bytes < required %zu", bytes, g->ws_bytes);
     if (reinterpret_cast<uintptr_t>(d_ws) % kAlign) return fail(GR_EINVAL, "workspace not 256-byte aligned");
     hipPointerAttribute_t attr;
     if (hipPointerGetAttributes(&attr, d_ws) != hipSuccess || attr.type != hipMemoryTypeDevice) {
@@ -1179,9 +1186,11 @@ int gr_bind(gr_grid g, void *d_ws, size_t bytes, void *stream)
                              hipHostMallocMapped | hipHostMallocCoherent));
         HIPCHK(hipHostGetDevicePointer(reinterpret_cast<void **>(&g->d_norms), g->h_norms, 0));
     }
+    g->small = bytes < g->ws_bytes;
     for (auto *h : g->sub) {
         if (!h) continue;
         h->drop_graphs();
+        if (g->small && g->n < 64) continue; // no room for it: not used (solve3)
         if (!h->work) {
             HIPCHK(hipStreamCreateWithFlags(&h->work, hipStreamNonBlocking));
             HIPCHK(hipEventCreateWithFlags(&h->ev_in, hipEventDisableTiming));
@@ -1195,9 +1204,9 @@ int gr_bind(gr_grid g, void *d_ws, size_t bytes, void *stream)
         h->stream = g->user_stream;
         h->bound = true;
     }
-    layout(g, reinterpret_cast<char *>(d_ws));
+    const size_t used = layout(g, reinterpret_cast<char *>(d_ws), g->small);
     for (int f = 0; f < 10; ++f) g->alt_valid[f] = g->hist_valid[f] = false;
-    launch_fill(g->stream, reinterpret_cast<double *>(d_ws), (long)(g->ws_bytes / sizeof(double)), 0.0);
+    launch_fill(g->stream, reinterpret_cast<double *>(d_ws), (long)(used / sizeof(double)), 0.0);
     LAUNCHCHK();
     g->bound = true;
     return GR_OK;
@@ -1215,7 +1224,7 @@ int gr_deposit_sources(gr_grid g, const double *d_pos, const double *d_u, double
     if (np < 0 || (np > 0 && (!d_pos || !d_u))) return fail(GR_EINVAL, "bad particle arrays");
     if (!std::isfinite(mass)) return fail(GR_EINVAL, "mass not finite");
     launch_cic_deposit(g->stream, g->n, g->prm.a, g->prm.c_tilde, d_pos, d_u, mass, (long)np, g->field[GR_PSI],
-                       g->cic, g->src[0], g->src[1], g->src[2], g->src[3], g->src[4]);
+                       g->cic, g->cic_pass, g->src[0], g->src[1], g->src[2], g->src[3], g->src[4]);
     LAUNCHCHK();
     return GR_OK;
 }
@@ -1508,7 +1517,8 @@ int gr_solve_constraints(gr_grid g, const gr_solve_opts *opts, gr_solve_report *
     auto solve3 = [&](int fid0, const std::function<int(int, double *)> &build) -> int {
         gr_grid H[3] = {g, g->sub[0], g->sub[1]};
         const unsigned three = (mask >> fid0) & 7u;
-        if (!g->sub[0] || !g->sub[1] || (three & (three - 1)) == 0) { // one component or none: no threads
+        // no helpers, or none in this workspace, or one component at most: no threads
+        if (!g->sub[0] || !g->sub[1] || (g->small && g->n < 64) || (three & (three - 1)) == 0) {
             for (int d = 0; d < 3; ++d) {
                 if (!(mask & (1u << (fid0 + d)))) continue;
                 CHK(build(d, fine_f));

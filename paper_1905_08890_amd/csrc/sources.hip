@@ -409,8 +409,9 @@ inline unsigned blocks_for(long count) { return (unsigned)((count + TPB - 1) / T
 } // namespace
 
 // Particles that one pass takes: as many as the lists hold in the worst case (every cloud
-// over eight tiles).  Twice the cells, so that a usual run needs one pass.
-static long cic_pass(long N) { return std::min(std::max(2 * N, 1L << 16), 1L << 28); }
+// over eight tiles).  Twice the cells, so that a usual run needs one pass, and 65536 on
+// small grids (small: not there, so that the scratch stays below 76 bytes a cell and 2 KB).
+long cic_pass(int n, bool small) { return std::min(std::max(2L * n * n * n, small ? 64L : 1L << 16), 1L << 28); }
 static long cic_tiles(int n)
 {
     const long nt = (n + DT - 1) / DT;
@@ -419,9 +420,9 @@ static long cic_tiles(int n)
 // tiles with long lists that are taken first
 static unsigned cic_room(long nt3) { return (unsigned)std::min(1 + nt3 / 8, 4096L); }
 
-size_t cic_bytes(int n)
+size_t cic_bytes(int n, long pass)
 {
-    return sizeof(unsigned) * (size_t)(8 * cic_pass((long)n * n * n) + 3 * (cic_tiles(n) + 4) + 1 + cic_room(cic_tiles(n)));
+    return sizeof(unsigned) * (size_t)(8 * pass + 3 * (cic_tiles(n) + 4) + 1 + cic_room(cic_tiles(n)));
 }
 
 // A table with a counter per tile up to 32768 of them (256^3, 128 KB of LDS), a hash table
@@ -442,12 +443,12 @@ static void cic_bin(hipStream_t s, int n, int nt, const double *pos, long np, un
 }
 
 void launch_cic_deposit(hipStream_t s, int n, double a, double c_tilde, const double *pos, const double *u,
-                        double mass, long np, const double *psi, void *scratch, double *s0, double *sx, double *sy,
-                        double *sz, double *sm)
+                        double mass, long np, const double *psi, void *scratch, long pass, double *s0, double *sx,
+                        double *sy, double *sz, double *sm)
 {
     const double kap = 1.0 / (2.0 * a * a * c_tilde * c_tilde);
     const int nt = (n + DT - 1) / DT;
-    const long nt3 = cic_tiles(n), pass = cic_pass((long)n * n * n);
+    const long nt3 = cic_tiles(n);
     const long row = (nt3 + 4) / 4 * 4; // nt3 + 1 at least
     const unsigned room = cic_room(nt3);
     unsigned *list = static_cast<unsigned *>(scratch), *cnt = list + 8 * pass, *next = cnt + row, *start = next + row,

@@ -68,3 +68,44 @@ def test_lattice_at_rest_gives_exactly_one(n, c_tilde):
     g.deposit_sources(pos, np.zeros_like(pos), 1.0 / n ** 3)
     for name, want in zip(("s0", "sx", "sy", "sz", "sm"), (1.0, 0.0, 0.0, 0.0, 0.0)):
         assert np.all(g.get_field(name).cpu().numpy() == want), name
+
+
+@pytest.mark.parametrize("n,nbytes", [(2, 148224), (8, 392960), (16, 2194176), (20, 4147200), (30, 13474816),
+                                      (34, 19560448), (48, 55713280), (62, 117871360)])
+def test_workspace_without_room_for_the_extras(n, nbytes):
+    """Workspaces of the sizes that grids asked for before helper hierarchies below 64^3
+    and long deposit passes on small grids: bound and used to the last byte, deposits in
+    several passes, vector components in turn.  Solves are the same bit for bit, a smaller
+    buffer is refused, and a larger one bound again brings the helpers back."""
+    print(f"[gpu] small workspace n={n}", flush=True)
+    h = grmg.create_grid(n, PRM["a"], PRM["omega_m"], PRM["c_tilde"])
+    full = grmg.Grid(n, **PRM)
+    try:
+        assert nbytes <= grmg.workspace_bytes(h)
+        guard = 4096
+        ws = torch.full((nbytes + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+        stream = torch.cuda.current_stream().cuda_stream
+        with pytest.raises(grmg.GrError):
+            grmg.bind(h, ws[:nbytes * 3 // 4 // 256 * 256], stream)
+        rng = np.random.default_rng(n)
+        count = 5 * n ** 3 + 100
+        pos = torch.tensor(rng.uniform(0, 1, (count, 3)), device="cuda")
+        u = torch.tensor(1e-2 * rng.standard_normal((count, 3)), device="cuda")
+        ref = O.cic_deposit(n, pos.cpu().numpy(), u.cpu().numpy(), 1.0 / count, prm=O.params(**PRM))
+        for buf in (ws[:nbytes], torch.empty(grmg.workspace_bytes(h), dtype=torch.uint8, device="cuda"), ws[:nbytes]):
+            grmg.bind(h, buf, stream)
+            grmg.deposit_sources(h, pos, u, 1.0 / count)
+            x = torch.empty((n, n, n), dtype=torch.float64, device="cuda")
+            for k, name in enumerate(("s0", "sx", "sy", "sz", "sm")):
+                grmg.get_field(h, grmg.FIELD_IDS[name], x, grmg.F64)
+                assert float((x.cpu() - torch.tensor(ref[k])).abs().max()) <= 1e-12 * np.abs(ref[k]).max(), name
+                full.set_field(name, x)
+            grmg.solve_constraints(h, grmg.default_opts(rtol=0.0, max_cycles=2))
+            full.solve_constraints(rtol=0.0, max_cycles=2)
+            for f in range(10):
+                grmg.get_field(h, f, x, grmg.F64)
+                assert torch.equal(x, full.get_field(f)), f
+        assert bool((ws[nbytes:] == 0x5A).all())
+    finally:
+        torch.cuda.synchronize()
+        grmg.destroy_grid(h)
