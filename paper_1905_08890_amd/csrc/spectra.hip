@@ -402,7 +402,7 @@ int ilog2(int v)
 
 struct gr_spectra_s {
     int n = 0, logn = 0, nbins = 0;
-    size_t off_a = 0, off_b = 0, off_tw = 0, off_part = 0, off_out = 0, bytes = 0;
+    size_t off_a = 0, off_b = 0, off_tw = 0, off_out = 0, bytes = 0;
     char *ws = nullptr;
     hipStream_t stream = nullptr;
     bool bound = false;
@@ -456,13 +456,11 @@ int gr_create_spectra(int n, int nbins, gr_spectra *out)
     size_t off = 0;
     S->off_a = off; // x pass output, then the mode cube
     off += al256(2 * (size_t)n * n * side * sizeof(double2));
-    S->off_b = off; // y pass output
-    off += al256(2 * (size_t)n * side * side * sizeof(double2));
+    S->off_b = off; // y pass output, then (the z pass has read it) the shells' partial sums
+    off += std::max(al256(2 * (size_t)n * side * side * sizeof(double2)), al256(side * kRows * nbins * sizeof(double)));
     off = std::max(off, 2 * al256((size_t)n * n * n * sizeof(double2))); // the size callers have always been told
     S->off_tw = off;
     off += al256((size_t)(n / 2) * sizeof(double2));
-    S->off_part = off;
-    off += al256(side * kRows * nbins * sizeof(double));
     S->off_out = off;
     off += al256((size_t)kRows * nbins * sizeof(double));
     S->bytes = off;
@@ -507,7 +505,7 @@ int gr_vector_spectra(gr_spectra S, const double *d_vx, const double *d_vy, cons
     double2 *bufa = reinterpret_cast<double2 *>(S->ws + S->off_a);
     double2 *bufb = reinterpret_cast<double2 *>(S->ws + S->off_b);
     const double2 *tw = reinterpret_cast<const double2 *>(S->ws + S->off_tw);
-    double *part = reinterpret_cast<double *>(S->ws + S->off_part);
+    double *part = reinterpret_cast<double *>(S->ws + S->off_b);
     double *out = reinterpret_cast<double *>(S->ws + S->off_out);
     const Fields src{d_vx, d_vy, d_vz};
     switch (S->logn) {

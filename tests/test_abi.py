@@ -197,3 +197,25 @@ def test_workspace_holds_the_autotuners_operands(n):
     slack = 256 * 256   # the arrays start at multiples of 256 bytes
     assert left >= 4 * 8 * n ** 3
     assert left <= max(64 * n ** 3, 4 * 8 * n ** 3) + n ** 3 // 8 + slack + (1 << 20)
+
+
+def _spectra_bytes_of_two_cubes(n, nbins):
+    """Two complex n^3 arrays, twiddles, the partial sums of chunks of 256 modes in at most
+    512 blocks, the result; each from a multiple of 256 bytes."""
+    up = lambda x: -(-x // 256) * 256
+    chunks = -(-(2 * nbins + 1) ** 3 // 256)
+    blocks = -(-chunks // -(-chunks // 512))
+    return 2 * up(16 * n ** 3) + up(16 * (n // 2)) + up(8 * 6 * nbins * blocks) + up(8 * 6 * nbins)
+
+
+def test_spectra_workspace_does_not_exceed_two_cubes_and_tables():
+    """Callers may hold a buffer of the size that the full transforms needed."""
+    lib = grmg.load_library()
+    for n in (8, 16, 32, 64, 128, 256, 512, 1024):
+        for nbins in range(1, n // 4 + 1):
+            h = C.c_void_p()
+            assert lib.gr_create_spectra(n, nbins, C.byref(h)) == grmg.OK
+            nbytes = C.c_size_t()
+            assert lib.gr_spectra_workspace_bytes(h, C.byref(nbytes)) == grmg.OK
+            assert lib.gr_destroy_spectra(h) == grmg.OK
+            assert nbytes.value <= _spectra_bytes_of_two_cubes(n, nbins), (n, nbins)
