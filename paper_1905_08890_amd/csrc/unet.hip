@@ -930,6 +930,7 @@ int pad32(int k) { return (k + 31) / 32 * 32; }
 constexpr int kWgradBlocks = 64; // most partial sums of a weight gradient of 128 x 64 channels
 
 constexpr int kWgradRows = 512;  // most partial sums of any
+static_assert(kWgradRows * 64 <= 32 * 32 * 32, "the bias partials fit one channel of the smallest grid");
 
 // k_conv3 with the channel steps unrolled for the counts that networks have
 template <int NT, int VG, bool RELU, bool BIAS, typename... A>
@@ -1055,10 +1056,10 @@ size_t unet_layout(gr_unet U, char *base)
     // taps x cout x cin) or the head's (one block per 256 voxels x its parameters)
     const size_t head_part = (size_t)((N + TPB - 1) / TPB) * (size_t)(U->d.out_ch * U->c[0] + U->d.out_ch);
     U->wg_part = takeF(std::max((size_t)kWgradBlocks * 27 * WG_MAXC * 64, head_part));
-    U->wg_bpart = takeF((size_t)kWgradRows * 64);
     U->y = takeF((size_t)U->d.out_ch * N);
     U->gy = takeF((size_t)U->d.out_ch * N);
     U->lq = takeF((size_t)U->d.out_ch * N);
+    U->wg_bpart = U->lq; // the loss has read its Laplacian before the backward pass starts
     U->x0 = takeB((size_t)N * 16);
     auto act = [&](Act &a, int lvl, int ch) {
         a.n = n >> lvl;

@@ -219,3 +219,20 @@ def test_spectra_workspace_does_not_exceed_two_cubes_and_tables():
             assert lib.gr_spectra_workspace_bytes(h, C.byref(nbytes)) == grmg.OK
             assert lib.gr_destroy_spectra(h) == grmg.OK
             assert nbytes.value <= _spectra_bytes_of_two_cubes(n, nbins), (n, nbins)
+
+
+@pytest.mark.parametrize("max_n,out_ch,nbytes", [(32, 1, 82226432), (32, 16, 88128768), (64, 10, 239162624),
+                                                 (128, 10, 1466324224), (512, 1, 75326442752)])
+def test_network_workspace_does_not_exceed_its_first_size(max_n, out_ch, nbytes):
+    """Callers may hold a buffer of the size that the 16/32/32/32-channel network asked for
+    when each block of a weight gradient left 64 channels of bias sums in 64 rows."""
+    lib = grmg.load_library()
+    d = grmg.GrUnetDesc()
+    d.in_ch, d.out_ch, d.lap_weight, d.clip_norm = 4, out_ch, 0.1, 0.0
+    d.c[0], d.c[1], d.c[2], d.c[3] = 16, 32, 32, 32
+    h = C.c_void_p()
+    assert lib.gr_unet_create(C.byref(d), max_n, C.byref(h)) == grmg.OK
+    size = C.c_size_t()
+    assert lib.gr_unet_workspace_bytes(h, C.byref(size)) == grmg.OK
+    assert size.value <= nbytes
+    assert lib.gr_destroy_unet(h) == grmg.OK
