@@ -178,3 +178,68 @@ def test_concurrent_vector_components_match_sequential(precision, monkeypatch):
         assert rc["rel_res"] == rs["rel_res"]
         for f in range(10):
             assert torch.equal(conc.get_field(f), seq.get_field(f)), (k, f)
+
+
+# Small FP64 grids launch their cycles ahead of the stopping test, kernel by kernel, and small
+# levels run a leg of the V-cycle in a launch; with both off (GRMG_AHEAD=0, GRMG_SMALL_N=0) or
+# from 96^3 on, cycles are captured and replayed and the 64^3 level is swept fused.
+
+
+@pytest.mark.parametrize("n,ahead", [(32, "0"), (64, "0"), (96, "1")])
+def test_captured_fp64_cycles_replay_like_eager(n, ahead, monkeypatch):
+    print(f"[gpu] captured fp64 cycles n={n} ahead={ahead}", flush=True)
+    monkeypatch.setenv("GRMG_AHEAD", ahead)
+    graph, eager = _pair(n, monkeypatch)
+    for k, (pos, u, mass) in enumerate(synth.zeldovich_trajectory(n, 13, [0.8, 1.0, 1.2])):
+        graph.deposit_sources(pos, u, mass)
+        _same_sources(eager, graph)
+        guess = "zero" if k == 0 else "current"
+        rg = graph.solve_constraints(rtol=1e-10, guess=guess)
+        re = eager.solve_constraints(rtol=1e-10, guess=guess)
+        assert rg["cycles"] == re["cycles"] and rg["rel_res"] == re["rel_res"]
+        for f in range(10):
+            assert torch.equal(graph.get_field(f), eager.get_field(f)), (k, f)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_captured_cycles_follow_the_sweep_counts(precision, monkeypatch):
+    """Graphs of several (nu1, nu2) side by side, each found again."""
+    n = 32
+    print(f"[gpu] captured cycles, sweep counts {precision}", flush=True)
+    monkeypatch.setenv("GRMG_AHEAD", "0")
+    graph, eager = _pair(n, monkeypatch)
+    pos, u, mass = synth.zeldovich(n, 4, 0.5)
+    graph.deposit_sources(pos, u, mass)
+    _same_sources(eager, graph)
+    seen = set()
+    for nu in ((2, 2), (1, 1), (2, 2), (1, 3), (2, 1), (1, 1), (2, 2)):
+        rg = graph.solve_constraints(rtol=1e-10, nu1=nu[0], nu2=nu[1], precision=precision)
+        re = eager.solve_constraints(rtol=1e-10, nu1=nu[0], nu2=nu[1], precision=precision)
+        assert rg["cycles"] == re["cycles"], nu
+        seen.add(tuple(rg["cycles"]))
+        for f in range(10):
+            assert torch.equal(graph.get_field(f), eager.get_field(f)), (nu, f)
+    assert len(seen) > 1   # the counts differ, so a graph of other counts would be noticed
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("tile,pf", [("2", "3"), ("1", "2"), ("3", "2")])
+def test_forced_launch_shapes_down_to_64(precision, tile, pf, monkeypatch):
+    """The 64^3 level swept fused in every tile: the same bits as one launch per colour."""
+    n = 128
+    print(f"[gpu] forced shapes, fused 64^3 level {precision} tile={tile}", flush=True)
+    monkeypatch.setenv("GRMG_SMALL_N", "0")
+    monkeypatch.setenv("GRMG_FUSED_MIN", "128")
+    a = grmg.Grid(n, **PRM)
+    monkeypatch.setenv("GRMG_FUSED_MIN", "64")
+    monkeypatch.setenv("GRMG_FUSED_TILE", tile)
+    monkeypatch.setenv("GRMG_FUSED_PF", pf)
+    b = grmg.Grid(n, **PRM)
+    pos, u, mass = synth.zeldovich(n, 6, 0.5)
+    a.deposit_sources(pos, u, mass)
+    _same_sources(b, a)
+    ra = a.solve_constraints(rtol=1e-10, precision=precision)
+    rb = b.solve_constraints(rtol=1e-10, precision=precision)
+    assert ra["cycles"] == rb["cycles"]
+    for f in range(10):
+        assert torch.equal(a.get_field(f), b.get_field(f)), f
