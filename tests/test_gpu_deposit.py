@@ -109,3 +109,18 @@ def test_workspace_without_room_for_the_extras(n, nbytes):
     finally:
         torch.cuda.synchronize()
         grmg.destroy_grid(h)
+
+
+@pytest.mark.parametrize("corners", [False, True])
+def test_hash_table_of_tiles(corners):
+    """Above 32768 tiles (33^3 here) a workgroup counts its tiles in a hash table of 8192
+    slots: particles in random order reach about 9800 tiles a workgroup, clouds over
+    tile corners 30000, so entries without a slot count in memory in both."""
+    n = 264
+    print(f"[gpu] deposit hash table corners={corners}", flush=True)
+    rng = np.random.default_rng(17)
+    if corners:
+        pos = (8 * rng.integers(0, n // 8, (20000, 3)) + rng.uniform(-0.45, 0.45, (20000, 3))) / n
+    else:
+        pos = rng.uniform(0.0, 1.0, (30000, 3))
+    _check(n, pos, 17)
