@@ -261,7 +261,6 @@ __global__ void __launch_bounds__(TPB) k_newton_kick(int n, const double *__rest
     for (int d = 0; d < 3; ++d) u[3 * q + d] -= dt * (grad[d] * inv2h);
 }
 
-// workgroups for np particles, a multiple of 8
 // side of a cube of particles that 16 x 4 x 4 blocks tile, else 0
 inline int lattice_side(long np)
 {
@@ -269,6 +268,7 @@ inline int lattice_side(long np)
     return s * s * s == np && s % 16 == 0 && s < 32768 ? (int)s : 0;
 }
 
+// workgroups for np particles, a multiple of 8
 inline unsigned particle_blocks(long np) { return (unsigned)(((np + TPB - 1) / TPB + 7) / 8 * 8); }
 
 } // namespace

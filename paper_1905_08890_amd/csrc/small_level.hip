@@ -131,10 +131,7 @@ template <int H, int TS> __device__ __forceinline__ bool region_pair(int t, cons
     return on;
 }
 
-// Sums of NC values per thread over a grid of at most 4096 workgroups, in a fixed order:
-// each workgroup leaves its partial sums and the one that arrives last adds them
-// all (thread t adds slots t, t + NT, ..., then a tree).  True in that workgroup,
-// whose thread 0 has the sums.  The counter is left at zero.
+// Sums of NC values per thread over a workgroup, to every thread.
 template <int NC, int NT>
 __device__ __forceinline__ void block_sum_all(double (&v)[NC])
 {
@@ -153,14 +150,21 @@ __device__ __forceinline__ void block_sum_all(double (&v)[NC])
     }
     __syncthreads();
 }
+// Sums of NC values per thread over a grid of at most 4096 workgroups, in a fixed order:
+// each workgroup leaves its partial sums and the one that arrives last adds them
+// all (thread t adds slots t, t + NT, ..., then a tree).  True in that workgroup,
+// whose thread 0 has the sums.  The counter is left at zero.
+// Partials and counter are relaxed atomics of device scope: on gfx950 such a store is
+// written through and such a load is taken from where all eight L2s agree, and s_waitcnt
+// vmcnt(0) returns when the stores have got there, so the count cannot be seen before
+// them.  (The language would ask for release and acquire; their fences write back
+// and invalidate a whole L2: 5 us instead of 1.)
 template <int NC, int NT>
 __device__ __forceinline__ bool grid_sum(double (&v)[NC], double *partials, unsigned *count, int nblocks, int block)
 {
     __shared__ bool last;
     block_sum_all<NC, NT>(v);
     if (threadIdx.x == 0) {
-        // device-scope stores, acknowledged before the arrival is counted (a fence here
-        // would write the whole L2 back: 5 us instead of 1)
         for (int c = 0; c < NC; ++c)
             __hip_atomic_store(partials + c * kReduceBlocks + block, v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

@@ -108,3 +108,25 @@ def test_concurrent_components_of_small_grids(n, precision, monkeypatch):
         assert ra["cycles"] == rb["cycles"]
         for f in range(10):
             assert torch.equal(a.get_field(f), b.get_field(f)), f
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("n", [12, 20, 28, 32, 48, 64, 128])
+def test_small_legs_give_the_bits_of_the_per_launch_path(n, kind, precision, monkeypatch):
+    """With the cycles measured alike (GRMG_AHEAD=0: queued ahead, the frozen means and
+    norms are summed in another order) a leg in one launch changes no bit: its updates, its
+    residuals and the sums of its restriction are in the per-launch order."""
+    print(f"[gpu] small legs bit for bit n={n} {kind} {precision}", flush=True)
+    f, coef = _problem(KINDS[kind], n)
+    monkeypatch.setenv("GRMG_AHEAD", "0")
+    a = _grid(n, f, coef)
+    monkeypatch.setenv("GRMG_SMALL_N", "0")
+    b = _grid(n, f, coef)
+    for nu1, nu2 in ((2, 2), (1, 2)):
+        out = []
+        for g in (a, b):
+            g.set_field("Vx", np.zeros((n, n, n)))
+            g.solve_equation(KINDS[kind], "Vx", rtol=0, max_cycles=3, nu1=nu1, nu2=nu2, precision=precision)
+            out.append(g.get_field("Vx"))
+        assert torch.equal(out[0], out[1]), (nu1, nu2)
