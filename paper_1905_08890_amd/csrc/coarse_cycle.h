@@ -356,9 +356,9 @@ template <int BC, bool QUADS> __device__ __forceinline__ LdsPair lds_pair_of(int
     }
 }
 
-// Sum of the six neighbours of cell w of a pair, the face value b in the place of an
-// extrapolated one counted twice (2 b - phi without the phi)
-template <int BC, typename T> __device__ __forceinline__ T pair_nbs2b(const T *phi, const LdsPair &P, int w)
+// Sum of the six neighbours of cell w of a pair (its own value ph: across a boundary
+// face the neighbour is 2 b - ph, added as b + (b - ph))
+template <int BC, typename T> __device__ __forceinline__ T pair_nbs(const T *phi, const LdsPair &P, int w, T ph)
 {
     const int p = P.p + w;
     const T vxm = phi[w ? P.p : P.xm], vxp = phi[w ? P.xp : P.p + 1];
@@ -366,29 +366,33 @@ template <int BC, typename T> __device__ __forceinline__ T pair_nbs2b(const T *p
     T nbs = vxm + vxp + vym + vyp + vzm + vzp;
     if constexpr (BC == kFaces) {
         const bool x0 = !w && P.fx0, x1 = P.fx1 && (w || !P.odd);
-        if (x0 || x1) nbs += x0 ? vxm : vxp;
-        if (P.fy) nbs += P.fy < 0 ? vym : vyp;
-        if (P.fz) nbs += P.fz < 0 ? vzm : vzp;
+        if (x0 || x1) nbs += (x0 ? vxm : vxp) - ph;
+        if (P.fy) nbs += (P.fy < 0 ? vym : vyp) - ph;
+        if (P.fz) nbs += (P.fz < 0 ? vzm : vzp) - ph;
     }
     return nbs;
 }
 
 // `sweeps` red-black sweeps of a level by NTH threads, CPL pairs each.  NTH = 64:
 // one wavefront, whose LDS accesses are done in order, so a phase needs no barrier.
-// The linear kinds take the Gauss-Seidel value itself, (a nbs / h^2 - f) / D with the
-// diagonal D = 6 a / h^2 - c (plus 1 / h^2 per face), as alpha nbs + beta: one
-// division per cell and visit, and six dependent operations a phase instead of ten
-// (phases are latency-bound).
+// One division per cell and visit, by the diagonal D = 6 a / h^2 - c (plus 1 / h^2 per
+// face).  The corrections (which start from zero) take the Gauss-Seidel value itself,
+// (a nbs / h^2 - f) / D, as alpha nbs + beta: six dependent operations a phase
+// instead of ten (phases are latency-bound).  The FAS kinds hold the whole field, whose
+// smooth part alpha's rounding would damp (converged FP64 Poisson solves were 1.4 to 4
+// times further from the exact ones): they add the change alpha (nbs - 6 ph) + beta,
+// whose first difference is exact for smooth fields: eight operations.
 template <int KIND, int BC, int CPL, int NTH, bool QUADS, typename T>
 __device__ __forceinline__ void lds_sweeps(T *s, const LdsLevel &V, int sweeps, T inv_h2, OpConst oc, T Fb, T fs)
 {
     constexpr int NC = kNumCoef<KIND>();
-    constexpr bool HAM = KIND == GR_KIND_HAMILTONIAN;
+    constexpr bool HAM = KIND == GR_KIND_HAMILTONIAN, FAS = KIND < K_LIN_POISSON, CMC = KIND == GR_KIND_CMC;
     const int n = V.n;
     const float rhalf = rcp_small((n + 1) >> 1), rn = rcp_small(n);
     T *phi = s + V.phi;
     LdsPair P[CPL];
     T u[CPL][2], v[CPL][2]; // per cell: alpha and beta; Hamiltonian: f and the coefficient
+    T m[CPL][2];            // CMC: the mass term's share of the change, -m2 / D
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
         P[c] = lds_pair_of<BC, QUADS>(threadIdx.x + NTH * c, n, rhalf, rn, rhalf);
@@ -410,6 +414,7 @@ __device__ __forceinline__ void lds_sweeps(T *s, const LdsLevel &V, int sweeps, 
                 const T rD = T(1) / D;
                 u[c][w] = a * inv_h2 * rD;
                 v[c][w] = -f * rD;
+                if (CMC) m[c][w] = -c1 * rD;
             }
         }
     }
@@ -425,8 +430,13 @@ __device__ __forceinline__ void lds_sweeps(T *s, const LdsLevel &V, int sweeps, 
                 int nf;
                 const T L = pair_op<KIND, BC, T>(phi, P[c], w, inv_h2, vc, T(0), oc, Fb, J, ph, nf);
                 x[c] = ph - (L - uc) / J;
+            } else if constexpr (FAS) {
+                const T ph = phi[P[c].p + w];
+                const T d = pair_nbs<BC, T>(phi, P[c], w, ph) - T(6) * ph;
+                const T b = CMC ? (w ? m[c][1] : m[c][0]) * ph + vc : vc;
+                x[c] = ph + (uc * d + b);
             } else {
-                x[c] = uc * pair_nbs2b<BC, T>(phi, P[c], w) + vc;
+                x[c] = uc * pair_nbs<BC, T>(phi, P[c], w, T(0)) + vc;
             }
         }
         if (NTH == 64) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); // no reordering by the compiler
@@ -504,11 +514,12 @@ __device__ void coarsest_two(T *s, const LdsLevel &V, T inv_h2, OpConst oc, T Fb
         ph = walsh_stage<2>(walsh_stage<1>(walsh_stage<0>(c, l), l), l);
     } else {
         const T c1 = NC >= 1 ? s[V.c1 + l] : T(0), c2 = NC >= 2 ? s[V.c2 + l] : T(0);
-        T al = T(0), be = T(0); // as lds_sweeps
+        T al = T(0), be = T(0), ma = T(0); // as lds_sweeps
         if constexpr (KIND != GR_KIND_HAMILTONIAN) {
             const T a = KIND == K_LIN_HAM ? c2 : T(1), rD = T(1) / (T(6) * a * inv_h2 + (KIND == GR_KIND_CMC ? c1 : -c1));
             al = a * inv_h2 * rD;
             be = -f * rD;
+            ma = -c1 * rD;
         }
         for (int it = 0; it < kCoarseSweeps; ++it)
 #pragma unroll
@@ -520,6 +531,9 @@ __device__ void coarsest_two(T *s, const LdsLevel &V, T inv_h2, OpConst oc, T Fb
                     T J;
                     const T L = op_point<KIND, T>(ph, nbs, inv_h2, c1, c2, oc, Fb, J);
                     v = ph - (L - f) / J;
+                } else if constexpr (KIND == GR_KIND_CMC) {
+                    const T d = nbs - T(6) * ph;
+                    v = ph + (al * d + (ma * ph + be));
                 } else {
                     v = al * nbs + be;
                 }
