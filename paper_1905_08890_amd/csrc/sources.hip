@@ -23,6 +23,7 @@ __device__ __forceinline__ int wrap_any(long i, int n)
 // (i0, i0+1), periodic.  chi at the particle from the CIC-interpolated Psi;
 // W^2 = c^2 + a^-2 chi^-4 u.u.
 //
+// (Small counts and grids: k_chain_tile.)
 // The grid points are cut into tiles of 8^3.  A particle is listed with every tile that
 // its cloud reaches (1.4 on average, at most 8): the entries are counted per tile, the
 // counts scanned, and the particles' numbers written to their tiles' lists.  A workgroup
@@ -214,33 +215,18 @@ __global__ void __launch_bounds__(SCNT) k_cic_scan(unsigned *__restrict__ cnt, i
     }
 }
 
-// One tile: the sources of its points from the particles of its list (added to what is
-// there: ADD).  Bound by the LDS adds (40 a particle); the first `room` workgroups take
-// the dense lumps, which would otherwise be the tail.
-template <bool ADD>
-__global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, double c, double kap,
-                                                  const double *__restrict__ pos, const double *__restrict__ u,
-                                                  double mass, const double *__restrict__ psi,
-                                                  const unsigned *__restrict__ start, const unsigned *__restrict__ list,
-                                                  const unsigned *__restrict__ listed,
-                                                  const unsigned *__restrict__ heavy, int room, double *__restrict__ s0, double *__restrict__ sx,
-                                                  double *__restrict__ sy, double *__restrict__ sz,
-                                                  double *__restrict__ sm)
+// One tile: the sources of its points from particles handed to `take` (which calls its
+// argument with each particle's number), summed in LDS.  Bound by the LDS adds (40 a
+// particle).  Each point is stored; ADD: added to what is there; SPLIT: other
+// workgroups add to it at the same time.
+template <bool ADD, bool SPLIT, class Take>
+__device__ __forceinline__ void cic_tile(int b, int n, int nt, double a, double c, double kap,
+                                         const double *__restrict__ pos, const double *__restrict__ u, double mass,
+                                         const double *__restrict__ psi, double *const (&out)[5], Take take)
 {
     __shared__ double acc[5][DP];
     __shared__ double ps[DS * DS * DS];
-    int b = blockIdx.x;
-    if (b < room) {
-        if ((unsigned)b >= heavy[0]) return;
-        b = (int)heavy[1 + b];
-    } else {
-        const int G = gridDim.x - room;
-        b -= room;
-        if ((G & 7) == 0) b = (b & 7) * (G >> 3) + (b >> 3); // runs of tiles per XCD: neighbours share particles
-        if (listed[b]) return;
-    }
     const int T[3] = {b % nt, (b / nt) % nt, b / (nt * nt)};
-    const unsigned first = start[b], last = start[b + 1];
     for (int i = threadIdx.x; i < 5 * DP; i += DNT) (&acc[0][0])[i] = 0.0;
     for (int i = threadIdx.x; i < DS * DS * DS; i += DNT) {
         int x[3] = {i % DS, (i / DS) % DS, i / (DS * DS)};
@@ -252,8 +238,7 @@ __global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, doubl
         ps[i] = psi[lin(x[0], x[1], x[2], n)];
     }
     __syncthreads();
-    for (unsigned e = first + threadIdx.x; e < last; e += DNT) {
-        const long q = list[e];
+    take([&](long q) {
         int i0[3], i1[3], at[3];
         double t[3];
         cic_cells(pos, q, n, i0, i1, t);
@@ -287,11 +272,10 @@ __global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, doubl
 #pragma unroll
             for (int f = 0; f < 5; ++f) unsafeAtomicAdd(&acc[f][r], w * Q[f]);
         }
-    }
+    });
     __syncthreads();
     // the common factor once a point, not rounded into one factor: a lattice of particles at rest gives exactly 1
     const double h = 1.0 / n, cvol = c * (h * h * h);
-    double *const out[5] = {s0, sx, sy, sz, sm};
     for (int r = threadIdx.x; r < DP; r += DNT) {
         const int x = DT * T[0] + r % DT, y = DT * T[1] + (r / DT) % DT, z = DT * T[2] + r / (DT * DT);
         if (x >= n || y >= n || z >= n) continue;
@@ -299,9 +283,89 @@ __global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, doubl
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
             const double v = mass * acc[f][r] / cvol;
-            out[f][g] = ADD ? out[f][g] + v : v;
+            if constexpr (SPLIT) {
+                if (v != 0.0) unsafeAtomicAdd(out[f] + g, v); // NaN too
+            } else {
+                out[f][g] = ADD ? out[f][g] + v : v;
+            }
         }
     }
+}
+
+// The tiles' particles from their lists; the first `room` workgroups take the dense
+// lumps, which would otherwise be the tail.
+template <bool ADD>
+__global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, double c, double kap,
+                                                  const double *__restrict__ pos, const double *__restrict__ u,
+                                                  double mass, const double *__restrict__ psi,
+                                                  const unsigned *__restrict__ start, const unsigned *__restrict__ list,
+                                                  const unsigned *__restrict__ listed,
+                                                  const unsigned *__restrict__ heavy, int room, double *__restrict__ s0, double *__restrict__ sx,
+                                                  double *__restrict__ sy, double *__restrict__ sz,
+                                                  double *__restrict__ sm)
+{
+    int b = blockIdx.x;
+    if (b < room) {
+        if ((unsigned)b >= heavy[0]) return;
+        b = (int)heavy[1 + b];
+    } else {
+        const int G = gridDim.x - room;
+        b -= room;
+        if ((G & 7) == 0) b = (b & 7) * (G >> 3) + (b >> 3); // runs of tiles per XCD: neighbours share particles
+        if (listed[b]) return;
+    }
+    const unsigned first = start[b], last = start[b + 1];
+    double *const out[5] = {s0, sx, sy, sz, sm};
+    cic_tile<ADD, false>(b, n, nt, a, c, kap, pos, u, mass, psi, out, [&](auto put) {
+        for (unsigned e = first + threadIdx.x; e < last; e += DNT) put((long)list[e]);
+    });
+}
+
+// ---- few particles on a small grid: chains instead of lists ----
+//
+// Counting, scanning and placing are three passes of a few latencies each, which is all
+// that 3e4 particles cost.  Here every tile has 512 chains (512 `parts` of them), one a thread
+// of its workgroups: a particle is put at the head of a chain of each tile it reaches,
+// by a hash of its number, in one pass with one memory atomic an entry.  `parts`
+// workgroups share a tile where the tiles are too few for the chip (measured: chains_ok).
+__global__ void k_chain_begin(unsigned *__restrict__ head, long nh, long N, double *__restrict__ s0, double *__restrict__ sx,
+                              double *__restrict__ sy, double *__restrict__ sz, double *__restrict__ sm)
+{
+    const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < nh) head[p] = ~0u;
+    if (p < N) s0[p] = sx[p] = sy[p] = sz[p] = sm[p] = 0.0; // N = 0: the tiles store every point
+}
+// entry e = 8 q + c: particle q in the c-th of its tiles; next[e]: the entry behind it
+__global__ void __launch_bounds__(TPB) k_chain_place(int n, int nt, int chains, const double *__restrict__ pos, long np,
+                                                     unsigned *__restrict__ head, unsigned *__restrict__ next)
+{
+    const long q = (long)blockIdx.x * TPB + threadIdx.x;
+    if (q >= np) return;
+    const unsigned h = (unsigned)(((unsigned long long)((unsigned)q * 2654435769u) * (unsigned)chains) >> 32);
+    unsigned e = 8u * (unsigned)q;
+    for_tiles(cic_span(pos, q, np, n), nt, [&](int k) {
+        next[e] = atomicExch(head + (unsigned)k * (unsigned)chains + h, e);
+        ++e;
+    });
+}
+template <bool ADD, bool SPLIT>
+__global__ void __launch_bounds__(DNT) k_chain_tile(int n, int nt, double a, double c, double kap,
+                                                    const double *__restrict__ pos, const double *__restrict__ u,
+                                                    double mass, const double *__restrict__ psi,
+                                                    const unsigned *__restrict__ head, const unsigned *__restrict__ next,
+                                                    int parts, double *__restrict__ s0, double *__restrict__ sx,
+                                                    double *__restrict__ sy, double *__restrict__ sz, double *__restrict__ sm)
+{
+    const int b = SPLIT ? (int)blockIdx.x / parts : (int)blockIdx.x;
+    unsigned e = head[(long)blockIdx.x * DNT + threadIdx.x];
+    double *const out[5] = {s0, sx, sy, sz, sm};
+    cic_tile<ADD, SPLIT>(b, n, nt, a, c, kap, pos, u, mass, psi, out, [&](auto put) {
+        while (e != ~0u) {
+            const unsigned q = e >> 3;
+            e = next[e];
+            put((long)q);
+        }
+    });
 }
 
 __global__ void k_fill_u32(unsigned *__restrict__ x, long N)
@@ -425,6 +489,29 @@ size_t cic_bytes(int n, long pass)
     return sizeof(unsigned) * (size_t)(8 * pass + 3 * (cic_tiles(n) + 4) + 1 + cic_room(cic_tiles(n)));
 }
 
+// Workgroups a tile of the chains: 256 particles each, together at most 24, whose adds to memory
+// (2560 each) stay below 3 us, and chain heads in at most half of the scratch.
+static int cic_parts(long nt3, long np, long pass)
+{
+    return (int)std::max(1L, std::min({np / (256 * nt3), 24 / nt3, 4 * pass / (DNT * nt3)}));
+}
+// particles of a pass by chains, next to the heads of as many chains as a tile can have
+static long chain_pass(long nt3, long pass) { return pass - nt3 * DNT * cic_parts(nt3, pass, pass) / 8; }
+// Chains where there are few tiles, or few particles on a small grid.  Measured back to back (us;
+// sort by cell or scatter of the first version / lists / chains):
+//   8^3      5120 particles   24.7 / 71.7 / 15.1;  1e6   1913 / 8549 / 701
+//   16^3     4096             30.3 / 36.3 / 23.0;  1e6   1638 / 1957 / 1089
+//   32^3    32768             32.7 / 36.8 / 30.0;  65000  123 / 42.4 / as lists (no room for the heads)
+//   64^3    65000             39.0 / 33.9 / 29.8;  1e6   1728 /  150 / as lists
+// Lists from 24^3 and 65536 particles on: 24^3 130000 123 / 150, and their heads cost a pass
+// over 4096 tiles at 128^3.
+constexpr long kChainFewTiles = 8, kChainTiles = 512, kChainMax = 1L << 16;
+static bool chains_ok(long nt3, long np, long pass)
+{
+    return 4 * pass >= nt3 * DNT &&
+           (nt3 <= kChainFewTiles || (nt3 <= kChainTiles && np <= std::min(kChainMax, chain_pass(nt3, pass))));
+}
+
 // A table with a counter per tile up to 32768 of them (256^3, 128 KB of LDS), a hash table
 // beyond.  8192 particles a workgroup from 2^20 on, so that few workgroups count into the
 // same tile, 2048 below, so that the chip has enough workgroups.
@@ -453,6 +540,26 @@ void launch_cic_deposit(hipStream_t s, int n, double a, double c_tilde, const do
     const unsigned room = cic_room(nt3);
     unsigned *list = static_cast<unsigned *>(scratch), *cnt = list + 8 * pass, *next = cnt + row, *start = next + row,
              *heavy = start + row;
+    if (chains_ok(nt3, np, pass)) {
+        const long most = std::max(1L, std::min(np, chain_pass(nt3, pass))); // no particle: one round too
+        for (long q = 0; q == 0 || q < np; q += most) {
+            const long m = std::min(most, np - q);
+            const double *x = m > 0 ? pos + 3 * q : nullptr, *v = m > 0 ? u + 3 * q : nullptr;
+            const int parts = cic_parts(nt3, m, pass);
+            const long nh = nt3 * DNT * parts, zero = q == 0 && parts > 1 ? (long)n * n * n : 0;
+            unsigned *head = list + 8 * m;
+            k_chain_begin<<<blocks_for(std::max(nh, zero)), TPB, 0, s>>>(head, nh, zero, s0, sx, sy, sz, sm);
+            if (m > 0) k_chain_place<<<blocks_for(m), TPB, 0, s>>>(n, nt, DNT * parts, x, m, head, list);
+            auto tile = [&](auto k) {
+                k<<<(unsigned)(nt3 * parts), DNT, 0, s>>>(n, nt, a, c_tilde, kap, x, v, mass, psi, head, list, parts, s0, sx,
+                                                          sy, sz, sm);
+            };
+            if (parts > 1) tile(k_chain_tile<false, true>);
+            else if (q == 0) tile(k_chain_tile<false, false>);
+            else tile(k_chain_tile<true, false>);
+        }
+        return;
+    }
     for (long q = 0; q == 0 || q < np; q += pass) {
         const long m = std::min(pass, np - q);
         const double *x = m > 0 ? pos + 3 * q : nullptr, *v = m > 0 ? u + 3 * q : nullptr;

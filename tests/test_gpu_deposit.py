@@ -124,3 +124,17 @@ def test_hash_table_of_tiles(corners):
     else:
         pos = rng.uniform(0.0, 1.0, (30000, 3))
     _check(n, pos, 17)
+
+
+@pytest.mark.parametrize("n,count", [(2, 0), (2, 64001), (6, 255), (8, 0), (8, 256), (8, 512), (8, 6144), (8, 130001),
+                                     (12, 4096), (12, 64000), (14, 70000), (16, 2047), (16, 64000), (16, 64001), (18, 40000),
+                                     (24, 40000), (24, 65537), (32, 32768), (32, 61440), (32, 61441), (64, 65536),
+                                     (64, 65537), (66, 5000)])
+def test_chains_and_lists(n, count):
+    """Chains instead of lists: one and several workgroups a tile, one and several passes,
+    the largest counts and grids that take them and the next larger."""
+    print(f"[gpu] deposit chains n={n} count={count}", flush=True)
+    rng = np.random.default_rng(1000 * n + count)
+    pos = rng.uniform(-0.5, 1.5, (count, 3))
+    pos[: count // 3] = 0.4 + 0.02 * rng.standard_normal((count // 3, 3))   # a lump: long chains
+    _check(n, pos, n)
