@@ -735,7 +735,7 @@ template <int KIND, typename TG>
 __device__ __forceinline__ void coarsest_wide(double *x, int n, double inv_h2, OpConst oc, const TG *__restrict__ f,
                                               const TG *__restrict__ c1, const TG *__restrict__ c2, TG *__restrict__ e)
 {
-    const int N = n * n * n, half = n >> 1, tot = n * n * half;
+    const int n2 = n * n, N = n2 * n, half = n >> 1, tot = n2 * half;
     const SmallDiv dh(half, tot), dn(n);
     const double rJ = poisson_inv_diag(inv_h2);
     for (int q = threadIdx.x; q < N; q += kCoarseThreads) x[q] = (double)e[q];
@@ -743,11 +743,13 @@ __device__ __forceinline__ void coarsest_wide(double *x, int n, double inv_h2, O
     for (int h = 0; h < 2 * kCoarseSweeps; ++h) {
         for (int t = threadIdx.x; t < tot; t += kCoarseThreads) {
             const int r = dh.div(t), z = dn.div(r), y = r - z * n;
-            const int i = 2 * (t - r * half) + ((y + z + h) & 1);
-            const long p = lin(i, y, z, n);
+            const int i = 2 * (t - r * half) + ((y + z + h) & 1), p = r * n + i; // below 2^31
             const double ph = x[p];
+            const double nbs = x[i ? p - 1 : p + n - 1] + x[i < n - 1 ? p + 1 : p - i] + x[y ? p - n : p + n2 - n] +
+                               x[y < n - 1 ? p + n : p - n2 + n] + x[z ? p - n2 : p + N - n2] +
+                               x[z < n - 1 ? p + n2 : p - N + n2];
             double J;
-            const double L = op_point<KIND, double>(ph, nb_sum(x, i, y, z, n), inv_h2, (double)load_c1<KIND>(c1, p),
+            const double L = op_point<KIND, double>(ph, nbs, inv_h2, (double)load_c1<KIND>(c1, p),
                                                     (double)load_c2<KIND>(c2, p), oc, 0.0, J);
             x[p] = newton_update<KIND, double>(ph, L, (double)f[p], J, rJ);
         }

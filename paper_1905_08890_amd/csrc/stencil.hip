@@ -1454,11 +1454,13 @@ void launch_coarse_vcycle_f32(int kind, hipStream_t s, const CoarseLevelsT<float
         : kind == K_LIN_HAM   ? coarse_in_lds<K_LIN_HAM>(s, C, nu1, nu2, oc, zero, zero, nullptr)
                               : coarse_in_lds<K_LIN_CMC>(s, C, nu1, nu2, oc, zero, zero, nullptr))
         return;
-    // A coarsest level alone that does not fit there (sides 18, 22, 26, ...): one cycle of a
-    // Poisson field at 44^3 296 us, 444 in FP32 from global memory, at 30^3 (iterate in
-    // global memory) 691 and 683; 18^3 takes 123 from LDS and 184 this way.
+    // A coarsest level alone that does not fit there (sides 18, 22, 26, ...), up to 58^3, where its
+    // arrays still fit one XCD's L2 in FP64.  A refinement step of V_x / Psi in us, FP32 from
+    // global memory / this: 44^3 (22^3) 455 / 214 and 540 / 285, 60^3 (30^3, the iterate in
+    // global memory) 426 / 409 and 733 / 721, 100^3 1353 / 1329 and 2232 / 2173, 132^3 2916 / 2911 and
+    // 5231 / 5361; 18^3 takes 121 from LDS with four pairs a thread and 184 this way.
     const int n = C.n[0];
-    if (C.nl == 1 && n > kCoarseLdsN && coarse_lds_on()) {
+    if (C.nl == 1 && n > kCoarseLdsN && 20L * n * n * n <= 4L << 20 && coarse_lds_on()) {
         double *x = sizeof(double) * n * n * n <= kCoarseLdsBytes ? nullptr : wide;
         if (kind == K_LIN_POISSON)
             k_coarsest_wide<K_LIN_POISSON><<<1, CTPB, 0, s>>>(C.phi[0], C.f[0], nullptr, nullptr, n, C.inv_h2[0], oc, x);
@@ -1468,7 +1470,7 @@ void launch_coarse_vcycle_f32(int kind, hipStream_t s, const CoarseLevelsT<float
             k_coarsest_wide<K_LIN_CMC><<<1, CTPB, 0, s>>>(C.phi[0], C.f[0], C.c1[0], nullptr, n, C.inv_h2[0], oc, x);
         return;
     }
-    // thresholds (GRMG_COARSE_N32, GRMG_COARSE_NP) whose levels do not fit: in FP32 from global memory
+    // wider, or thresholds (GRMG_COARSE_N32, GRMG_COARSE_NP) whose levels do not fit: in FP32 from global memory
     GR_DISPATCH_KT(kind, float, k_coarse_vcycle, 1, CTPB, C, nu1, nu2, oc, zero, zero);
 }
 
