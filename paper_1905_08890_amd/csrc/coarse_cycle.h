@@ -193,7 +193,7 @@ __device__ void coarse_vcycle_body(const CoarseLevelsT<T> &C, int nu1, int nu2, 
 // of ~85); the four pairs of a coarse cell sit in adjacent lanes, so restriction
 // sums by DPP; the coarsest sweeps run in one wavefront without barriers, and on
 // 2^3 in registers.  Per cycle from 16^3, Poisson (FP32 arrays, three streams) 57.9 ->
-// 29.6 us; from 8^3, Hamiltonian 38.6 -> 21.8 us; patches from 9-16^3 81 -> 41 us.
+// 28.8 us; from 8^3, Hamiltonian 38.6 -> 20.6 us; patches from 9-16^3 81 -> 43 us.
 //
 // BC = kPeriodic: dense n^3 levels, neighbours wrap.  BC = kFaces: Dirichlet
 // patch levels, the iterate padded by one cell whose values are the face values

@@ -142,11 +142,12 @@ __device__ __forceinline__ double lorentz_W(double a, double c, double Psi, cons
 
 // Five substeps of u_i += dt c_j (f_j)_i (see gr_kick); c_j from the velocity
 // as updated by the substeps before it.  Bound by the gathers: 32 cells of 40
-// bytes a particle, no two neighbours alike once displaced, so the L1 (32 KB, 64
-// bytes a cycle) misses and stalls.  256^3 particles on 256^3: 4.79 ms gathering
+// bytes a particle, no two neighbours alike once displaced, so the L1 serves one access
+// a clock from end to end (842e6 in 1.46 ms; it waits for a miss in a third of the
+// clocks).  256^3 particles on 256^3: 4.79 ms gathering
 // five arrays corner by corner (8 x 35 values), 2.22 ms over the packed cells with all
 // loads in flight (one wavefront per SIMD), 1.92 ms plane by plane (three), 1.70 ms
-// with 16 x 4 x 4 blocks of a lattice.
+// with 16 x 4 x 4 blocks of a lattice, 1.46 ms with values relative to the first corner.
 __global__ void __launch_bounds__(TPB) k_kick(Metric M, double a, double c, const double *__restrict__ pos,
                                               double *__restrict__ u, long np, double dt, int order, int side)
 {
@@ -203,7 +204,7 @@ __global__ void __launch_bounds__(TPB) k_kick(Metric M, double a, double c, cons
 }
 
 // x^i += dt V^i with the fields at the old position, wrapped into [0, 1)
-// (256^3 particles: 0.92 -> 0.75 ms)
+// (256^3 particles: 0.92 -> 0.75 ms; the L1 waits for misses in two thirds of the clocks)
 __global__ void __launch_bounds__(TPB) k_drift(Metric M, double a, double c, double *__restrict__ pos,
                                                const double *__restrict__ u, long np, double dt, int side)
 {

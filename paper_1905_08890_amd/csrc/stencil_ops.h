@@ -67,7 +67,9 @@ __device__ __forceinline__ T op_point(T ph, T nbs, T inv_h2, T c1, T c2, OpConst
 // The point update ph - (L - fe) / J of every smoother.  The Poisson kinds have
 // the constant diagonal J = -6/h^2: there the update multiplies by its
 // reciprocal rJ (formed once per kernel from inv_h2), within an ulp of the
-// division and a third of the point's instructions.
+// division and a third of the point's instructions.  A sweep still rests where
+// L = fe: converged FP64 fields are as far from the exact ones as with the division
+// (V_x at 64^3 6.4e-16 and 6.9e-16, 24 solves).
 template <typename T> __device__ __forceinline__ T poisson_inv_diag(T inv_h2) { return T(1) / (T(-6) * inv_h2); }
 
 template <int KIND, typename T>

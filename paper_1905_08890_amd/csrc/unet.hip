@@ -151,9 +151,9 @@ __global__ void __launch_bounds__(256) k_conv3(const bf16 *__restrict__ in, int 
 // 16 (x) x 4 (y) x 4 (z) tile of output voxels and 16 NT channels (blockIdx.y picks
 // them); wave w takes the plane z0 + w and its product group q the row y0 + q.  For
 // each chunk of CW input channels the block copies the tile's 18 x 6 x 6 input halo
-// into LDS; the next chunk is loaded meanwhile.  Voxel strides of 32 and 96 bytes are
-// free of bank conflicts with the lanes that a 16-byte read takes together (lanes 0-3,
-// 12-15, 20-27; 48 and 80 bytes doubled the LDS cycles).  CW = 32: one
+// into LDS; the next chunk is loaded meanwhile.  Voxel strides of 32 and 96 bytes suit
+// the lanes that a 16-byte read takes together (lanes 0-3, 12-15, 20-27): no cycle of
+// the LDS is lost to bank conflicts at 32 bytes and 21 % at 96 (48 and 80 bytes: half).  CW = 32: one
 // v_mfma_f32_16x16x32_bf16 per tap, all lanes on the same tap; a plane's six rows are
 // read once for the three dy, and the weights are loaded
 // a row of taps ahead (NT = 2) or all at once (NT = 1: 17 -> 12 us a layer of the 64^3 network).
@@ -323,8 +323,8 @@ __global__ void __launch_bounds__(256, MARCH ? 3 : 2)
 // its partial sums, and k_wgrad_reduce adds the partials in a fixed order.  db comes
 // from products with ones in the waves that have one tap less.
 // A block a tap, staged 27 times and transposed by 2-byte stores, took 73 us a layer
-// (64^3 network, 14 layers); this 8-18 us (48 -> 16 at 64^3: 40), bound by latency and, at 16
-// channels, by the LDS reads.
+// (64^3 network, 14 layers); this 8-18 us (48 -> 16 at 64^3: 43), bound by latency and, at 16
+// channels, by the LDS reads: half of the cycles of the LDS are bank conflicts.
 constexpr int WG_MAXC = 128;              // largest channel count of either side
 typedef __attribute__((address_space(3))) shortx4 *lds_s4;
 union WgOperand {
