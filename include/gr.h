@@ -170,7 +170,8 @@ int gr_bind(gr_grid g, void *d_workspace, size_t bytes, void *hip_stream);
  * (s_m = gamma^ij s_ij += w m a^-2 chi^-4 u_i u_i/(W c h^3)).  Positions
  * outside [0,1) are wrapped.  The particles are listed by the 8^3 tiles of
  * points that their clouds reach and each tile is summed in LDS and stored
- * once; the order of a point's terms is not fixed. */
+ * once (where there are few tiles, added by several workgroups); the order of
+ * a point's terms is not fixed. */
 int gr_deposit_sources(gr_grid g, const double *d_pos, const double *d_u, double mass,
                        int64_t n_particles);
 

@@ -219,8 +219,11 @@ __global__ void __launch_bounds__(SCNT) k_cic_scan(unsigned *__restrict__ cnt, i
 // argument with each particle's number), summed in LDS.  Bound by the LDS adds (40 a
 // particle).  Each point is stored; ADD: added to what is there; SPLIT: other
 // workgroups add to it at the same time.
+struct CicVolume { // c h^3 and its reciprocal
+    double v, r;
+};
 template <bool ADD, bool SPLIT, class Take>
-__device__ __forceinline__ void cic_tile(int b, int n, int nt, double a, double c, double kap,
+__device__ __forceinline__ void cic_tile(int b, int n, int nt, double a, double c, double kap, CicVolume V,
                                          const double *__restrict__ pos, const double *__restrict__ u, double mass,
                                          const double *__restrict__ psi, double *const (&out)[5], Take take)
 {
@@ -274,15 +277,17 @@ __device__ __forceinline__ void cic_tile(int b, int n, int nt, double a, double 
         }
     });
     __syncthreads();
-    // the common factor once a point, not rounded into one factor: a lattice of particles at rest gives exactly 1
-    const double h = 1.0 / n, cvol = c * (h * h * h);
+    // The common factor m / (c h^3) once a point, not rounded into one number: a lattice of particles at
+    // rest gives exactly 1.  The quotient by V.v = c h^3 from its rounded reciprocal and one
+    // correction, which rounds as the division does (Markstein).
     for (int r = threadIdx.x; r < DP; r += DNT) {
         const int x = DT * T[0] + r % DT, y = DT * T[1] + (r / DT) % DT, z = DT * T[2] + r / (DT * DT);
         if (x >= n || y >= n || z >= n) continue;
         const long g = lin(x, y, z, n);
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
-            const double v = mass * acc[f][r] / cvol;
+            const double t = mass * acc[f][r], q = t * V.r;
+            const double v = isfinite(q) ? __builtin_fma(__builtin_fma(-q, V.v, t), V.r, q) : q;
             if constexpr (SPLIT) {
                 if (v != 0.0) unsafeAtomicAdd(out[f] + g, v); // NaN too
             } else {
@@ -295,7 +300,7 @@ __device__ __forceinline__ void cic_tile(int b, int n, int nt, double a, double 
 // The tiles' particles from their lists; the first `room` workgroups take the dense
 // lumps, which would otherwise be the tail.
 template <bool ADD>
-__global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, double c, double kap,
+__global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, double c, double kap, CicVolume V,
                                                   const double *__restrict__ pos, const double *__restrict__ u,
                                                   double mass, const double *__restrict__ psi,
                                                   const unsigned *__restrict__ start, const unsigned *__restrict__ list,
@@ -316,7 +321,7 @@ __global__ void __launch_bounds__(DNT) k_cic_tile(int n, int nt, double a, doubl
     }
     const unsigned first = start[b], last = start[b + 1];
     double *const out[5] = {s0, sx, sy, sz, sm};
-    cic_tile<ADD, false>(b, n, nt, a, c, kap, pos, u, mass, psi, out, [&](auto put) {
+    cic_tile<ADD, false>(b, n, nt, a, c, kap, V, pos, u, mass, psi, out, [&](auto put) {
         for (unsigned e = first + threadIdx.x; e < last; e += DNT) put((long)list[e]);
     });
 }
@@ -349,7 +354,7 @@ __global__ void __launch_bounds__(TPB) k_chain_place(int n, int nt, int chains, 
     });
 }
 template <bool ADD, bool SPLIT>
-__global__ void __launch_bounds__(DNT) k_chain_tile(int n, int nt, double a, double c, double kap,
+__global__ void __launch_bounds__(DNT) k_chain_tile(int n, int nt, double a, double c, double kap, CicVolume V,
                                                     const double *__restrict__ pos, const double *__restrict__ u,
                                                     double mass, const double *__restrict__ psi,
                                                     const unsigned *__restrict__ head, const unsigned *__restrict__ next,
@@ -359,7 +364,7 @@ __global__ void __launch_bounds__(DNT) k_chain_tile(int n, int nt, double a, dou
     const int b = SPLIT ? (int)blockIdx.x / parts : (int)blockIdx.x;
     unsigned e = head[(long)blockIdx.x * DNT + threadIdx.x];
     double *const out[5] = {s0, sx, sy, sz, sm};
-    cic_tile<ADD, SPLIT>(b, n, nt, a, c, kap, pos, u, mass, psi, out, [&](auto put) {
+    cic_tile<ADD, SPLIT>(b, n, nt, a, c, kap, V, pos, u, mass, psi, out, [&](auto put) {
         while (e != ~0u) {
             const unsigned q = e >> 3;
             e = next[e];
@@ -533,7 +538,8 @@ void launch_cic_deposit(hipStream_t s, int n, double a, double c_tilde, const do
                         double mass, long np, const double *psi, void *scratch, long pass, double *s0, double *sx,
                         double *sy, double *sz, double *sm)
 {
-    const double kap = 1.0 / (2.0 * a * a * c_tilde * c_tilde);
+    const double kap = 1.0 / (2.0 * a * a * c_tilde * c_tilde), h = 1.0 / n, vol = c_tilde * (h * h * h);
+    const CicVolume V{vol, 1.0 / vol};
     const int nt = (n + DT - 1) / DT;
     const long nt3 = cic_tiles(n);
     const long row = (nt3 + 4) / 4 * 4; // nt3 + 1 at least
@@ -551,7 +557,7 @@ void launch_cic_deposit(hipStream_t s, int n, double a, double c_tilde, const do
             k_chain_begin<<<blocks_for(std::max(nh, zero)), TPB, 0, s>>>(head, nh, zero, s0, sx, sy, sz, sm);
             if (m > 0) k_chain_place<<<blocks_for(m), TPB, 0, s>>>(n, nt, DNT * parts, x, m, head, list);
             auto tile = [&](auto k) {
-                k<<<(unsigned)(nt3 * parts), DNT, 0, s>>>(n, nt, a, c_tilde, kap, x, v, mass, psi, head, list, parts, s0, sx,
+                k<<<(unsigned)(nt3 * parts), DNT, 0, s>>>(n, nt, a, c_tilde, kap, V, x, v, mass, psi, head, list, parts, s0, sx,
                                                           sy, sz, sm);
             };
             if (parts > 1) tile(k_chain_tile<false, true>);
@@ -568,10 +574,10 @@ void launch_cic_deposit(hipStream_t s, int n, double a, double c_tilde, const do
         k_cic_scan<<<1, SCNT, 0, s>>>(cnt, (int)nt3, start, next, heavy, room);
         cic_bin<true>(s, n, nt, x, m, next, list);
         if (q == 0)
-            k_cic_tile<false><<<(unsigned)nt3 + room, DNT, 0, s>>>(n, nt, a, c_tilde, kap, x, v, mass, psi, start, list, cnt, heavy, (int)room, s0, sx,
+            k_cic_tile<false><<<(unsigned)nt3 + room, DNT, 0, s>>>(n, nt, a, c_tilde, kap, V, x, v, mass, psi, start, list, cnt, heavy, (int)room, s0, sx,
                                                             sy, sz, sm);
         else
-            k_cic_tile<true><<<(unsigned)nt3 + room, DNT, 0, s>>>(n, nt, a, c_tilde, kap, x, v, mass, psi, start, list, cnt, heavy, (int)room, s0, sx,
+            k_cic_tile<true><<<(unsigned)nt3 + room, DNT, 0, s>>>(n, nt, a, c_tilde, kap, V, x, v, mass, psi, start, list, cnt, heavy, (int)room, s0, sx,
                                                            sy, sz, sm);
     }
 }
